@@ -292,13 +292,14 @@ dstd_status check_conv(const dstd_conv_shape *cs, int64_t B, int M, dstd::ConvGe
     G.dv_p = dstd::fast_div((uint32_t)G.P);
     G.dv_kw = dstd::fast_div((uint32_t)G.KW);
     G.dv_pc = dstd::fast_div((uint32_t)G.PC);
+    G.dv_howo = dstd::fast_div((uint32_t)(G.Ho * G.Wo));
+    G.dv_wo = dstd::fast_div((uint32_t)G.Wo);
     return DSTD_OK;
 }
 
 struct ConvWs {
     size_t wt, key, L, R, off;                        // both passes
-    size_t px, src, P, dL, dR;                        // backward sort extras
-    size_t row, eL, eR, crlive, gam, uq, q, rend, part, zlive, dq;   // backward
+    size_t P, ev, crlive, tri, rend, part, zlive, dq;  // backward
     size_t total;
 };
 
@@ -319,26 +320,24 @@ ConvWs conv_ws_layout(int M, const dstd::ConvGeom &g, int64_t B, bool backward) 
     w.R = off; off += align_up(nr * sizeof(float));
     w.off = off; off += align_up((size_t)B * g.Hp * (size_t)dstd::conv_off_stride(R, g) * sizeof(int));
     if (backward) {
-        w.px = off; off += align_up(nr * sizeof(int));
-        w.src = off; off += align_up(nr * sizeof(int));
-        w.P = off; off += align_up(nr * (size_t)(g.KH * g.KW) * sizeof(float));
-        w.dL = off; off += align_up(nr * sizeof(float));
-        w.dR = off; off += align_up(nr * sizeof(float));
-        w.row = off; off += align_up(n * sizeof(int));
-        w.eL = off; off += align_up(n * sizeof(float));
-        w.eR = off; off += align_up(n * sizeof(float));
+        // (scalar loads of an input group may run a few slots past the events,
+        // into the arrays after them)
+        const dstd::ConvBackPlan dp = dstd::plan_conv_back(g, B, M);
+        w.ev = off; off += align_up(n * 5 * sizeof(float));
+        w.P = off; off += align_up(n * (size_t)(g.KH * dp.kg * dp.tiles_dt) * sizeof(float));
         w.crlive = off; off += align_up((size_t)B * g.Hp * sizeof(int));
-        w.gam = off; off += align_up(nout * sizeof(float));
-        w.uq = off; off += align_up(nout * sizeof(float));
-        w.q = off; off += align_up(nout * sizeof(int));
+        w.tri = off; off += align_up(3 * nout * sizeof(float));
         w.rend = off; off += align_up((size_t)B * g.Ho * g.Wo * sizeof(int));
         w.dq = off; off += align_up((size_t)g.C_out * sizeof(float));  // dead-neuron term per channel
-        dstd::ConvDwPlan dp = dstd::plan_conv_dw(g, B, M);
         w.part = off; off += align_up((size_t)dp.nsplit * nw * sizeof(float));
         w.zlive = off; off += align_up((size_t)dp.nsplit * sizeof(int));
     }
     w.total = off;
     return w;
+}
+
+dstd::CellEv cell_events(void *ws, const ConvWs &L) {
+    return dstd::CellEv{at<float>(ws, L.ev), at<int>(ws, L.crlive)};
 }
 
 // Synfire terms of a backward call (NULL: off).
@@ -642,16 +641,9 @@ dstd_status dstd_lif_conv_forward(const dstd_lif_params *p, const dstd_conv_shap
     if (B == 0) return DSTD_OK;
     LifConst C = make_const(p);
     dstd::ConvSorted srt{at<int>(ws, L.key), at<float>(ws, L.L), at<float>(ws, L.R),
-                         at<int>(ws, L.off), nullptr, nullptr, nullptr, nullptr, nullptr};
-    dstd::CellEv ev{nullptr, nullptr, nullptr, nullptr};
-    if (keep) {
-        srt.px = at<int>(ws, L.px);
-        srt.src = at<int>(ws, L.src);
-        srt.dL = at<float>(ws, L.dL);
-        srt.dR = at<float>(ws, L.dR);
-        ev = dstd::CellEv{at<int>(ws, L.row), at<float>(ws, L.eL), at<float>(ws, L.eR),
-                          at<int>(ws, L.crlive)};
-    }
+                         at<int>(ws, L.off)};
+    dstd::CellEv ev{};
+    if (keep) ev = cell_events(ws, L);
     hipError_t e = dstd::launch_conv_forward(C, g, B, W, w_dtype == DSTD_BF16, at<float>(ws, L.wt),
                                              srt, ev, t_in, t_out, slope, q_idx,
                                              static_cast<hipStream_t>(stream));
@@ -737,20 +729,13 @@ dstd_status conv_backward(const dstd_lif_params *p, const dstd_synfire_params *s
     if ((s = check_ws(ws, ws_bytes, L.total)) != DSTD_OK) return s;
     LifConst C = make_const(p);
     dstd::ConvBwdWs bw;
-    bw.row = at<int>(ws, L.row);
-    bw.L = at<float>(ws, L.eL);
-    bw.R = at<float>(ws, L.eR);
-    bw.gam = at<float>(ws, L.gam);
-    bw.uq = at<float>(ws, L.uq);
-    bw.q = at<int>(ws, L.q);
+    bw.ev = cell_events(ws, L);
+    bw.tri = at<float>(ws, L.tri);
     bw.rend = at<int>(ws, L.rend);
-    bw.crlive = at<int>(ws, L.crlive);
+    bw.P = at<float>(ws, L.P);
     bw.part = at<float>(ws, L.part);
     bw.zlive = at<int>(ws, L.zlive);
     bw.wt = at<float>(ws, L.wt);
-    bw.srt = dstd::ConvSorted{at<int>(ws, L.key), at<float>(ws, L.L), at<float>(ws, L.R),
-                              at<int>(ws, L.off), at<int>(ws, L.px), at<int>(ws, L.src),
-                              at<float>(ws, L.P), at<float>(ws, L.dL), at<float>(ws, L.dR)};
     const bool reuse = (p->flags & DSTD_FLAG_CONV_REUSE) != 0;
     // With B == 0 the dW kernel still runs (one empty split) and writes zeros.
     hipError_t e = dstd::launch_conv_backward(C, g, B, W, w_dtype == DSTD_BF16, t_in, t_out, slope,

@@ -1,0 +1,208 @@
+// dstd_back.h -- the backward contraction over one sample's events (device
+// code shared by the dense and conv backward passes).
+//
+// G[m][i] = dL/dw^_m of one sample's neurons i (dense: a batch element; conv:
+// an output position of one) lives in LDS as a table of rows r = m + 1, lanes
+// = neurons. A wave owns some inputs and NT neurons per lane; the dW sums and
+// the weights of those pairs stay in its registers over all samples of the
+// block. An input's event (row, L, R, dL, dR) is the same for every lane:
+// one or two vector loads bring a wave's events, a sample ahead, with lanes =
+// (field, input); an active input's fields then come as scalars by readlane.
+//   - An input without events, or whose row lies past the last spike that
+//     passes gradient, costs one scalar branch (the causal half of the pairs
+//     and the silent inputs are never multiplied);
+//   - its two G rows are one conflict-free two-address LDS read;
+//   - dW takes 2 and dt_in 2 multiply-adds per lane, neuron and tap from those
+//     reads, and no weight is loaded again;
+//   - dt_in's sum over the lanes is taken once per input, for all its taps.
+// What bounds it is the vector ALU.
+#pragma once
+
+#include "dstd_internal.h"
+
+#include <utility>
+
+namespace dstd {
+
+// Rows of one neuron's G from its triple (gK, gE, q) = (gamma K(t - T_q),
+// gamma e^{-(t - T_q)/ti}, q): with d = q - m >= 0,
+//   G[m] = gamma K(t - T_q + d dt) = a_d gK + k_d gE,
+// a_d = e^{-d dt/tv}, k_d = K(d dt) (terms of one sign: no cancellation).
+// The pairs (a_d, k_d) are tabulated in LDS for d = -(M+2) .. M, zero for
+// d < 0, once per block.
+__host__ __device__ __forceinline__ int g_table_len(int M) { return 2 * M + 4; }
+
+__device__ __forceinline__ void g_table_fill(const LifConst &C, float2 *tab) {
+    for (int k = threadIdx.x; k < g_table_len(C.M); k += blockDim.x) {
+        const int d = k - (C.M + 2);
+        const float u = static_cast<float>(d) * C.dt;
+        tab[k] = (d >= 0) ? make_float2(expf(-u * C.inv_tv), kern(C, u)) : make_float2(0.f, 0.f);
+    }
+}
+
+struct GradTriple { float gK, gE; int q; };
+
+__device__ __forceinline__ GradTriple grad_triple(const LifConst &C, float t, float slope, int q,
+                                                  float g) {
+    const GradPrep p = grad_prep(C, t, slope, q, g);
+    if (p.q < 0) return GradTriple{0.f, 0.f, -1};
+    return GradTriple{p.gam * kern(C, p.uq), p.gam * expf(-p.uq * C.inv_ti), p.q};
+}
+
+template <int NT> struct GTri { float gK[NT], gE[NT]; int q[NT]; };
+
+// NT consecutive floats in LDS as one read or write
+template <int NT> __device__ __forceinline__ void lds_get(const float *p, float (&v)[NT]) {
+    if constexpr (NT == 4) {
+        const float4 x = *reinterpret_cast<const float4 *>(p);
+        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+    } else if constexpr (NT == 2) {
+        const float2 x = *reinterpret_cast<const float2 *>(p);
+        v[0] = x.x; v[1] = x.y;
+    } else {
+        v[0] = p[0];
+    }
+}
+template <int NT> __device__ __forceinline__ void lds_put(float *p, const float (&v)[NT]) {
+    if constexpr (NT == 4) *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    else if constexpr (NT == 2) *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+    else p[0] = v[0];
+}
+
+// rows 1 .. r_end + 1 of one sample's G (row 0 is zero for good), wave w of nw
+// taking rows 1 + w, 1 + w + nw, ..., four at a time (their table reads in
+// flight together); gl = the table + NT * lane
+template <int NT>
+__device__ __forceinline__ void g_rows(int M, const float2 *tab, const GTri<NT> &t, int r_end,
+                                       int w, int nw, float *gl) {
+    for (int r0 = 1 + w; r0 <= r_end + 1; r0 += 4 * nw) {
+        float2 e[4][NT];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = min(r0 + u * nw, r_end + 1);
+#pragma unroll
+            for (int c = 0; c < NT; ++c) e[u][c] = tab[t.q[c] + M + 3 - r];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = r0 + u * nw;
+            if (r > r_end + 1) break;
+            float v[NT];
+#pragma unroll
+            for (int c = 0; c < NT; ++c) {
+                const float x = fmaf(t.gK[c], e[u][c].x, t.gE[c] * e[u][c].y);
+                v[c] = (t.q[c] >= r - 1) ? x : 0.f;
+            }
+            lds_put<NT>(gl + r * (NT * kWave), v);
+        }
+    }
+}
+
+// f(0), ..., f(N - 1) with compile-time arguments: array elements named by
+// them are registers from the start (a loop unrolled later had left the
+// accumulators of skipped inputs behind as 8-wide vector copies).
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void static_for(F &&f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// x is in its register here
+__device__ __forceinline__ void settle(float &x) { asm volatile("" : "+v"(x)); }
+
+__device__ __forceinline__ void opaque(unsigned &x) { asm volatile("" : "+s"(x)); }
+
+// A wave's events of one item: with TJ inputs, lane f TJ + k of the registers
+// e[0], e[1], ... holds field f of input k (row as int bits, L, R, dL, dR).
+constexpr int kBackGroup = 8;
+constexpr int kEvFields = 5;
+template <int TJ> constexpr int ev_regs() { return (kEvFields * TJ + kWave - 1) / kWave; }
+template <int TJ> struct EvRegs { float e[ev_regs<TJ>()]; };
+
+// Offsets (floats) of a lane's events from the first input's row, the fields fs
+// floats apart; lanes past the fields, or inputs past nj >= 1, take a field or
+// input that exists.
+template <int TJ> struct EvOffs { unsigned o[ev_regs<TJ>()]; };
+template <int TJ> __device__ __forceinline__ EvOffs<TJ> ev_offs(int fs, int nj, int lane) {
+    EvOffs<TJ> r;
+#pragma unroll
+    for (int h = 0; h < ev_regs<TJ>(); ++h) {
+        const int x = h * kWave + lane;
+        r.o[h] = static_cast<unsigned>(min(x / TJ, kEvFields - 1) * fs + min(x % TJ, nj - 1));
+    }
+    return r;
+}
+// p: the first input's row (scalar)
+template <int TJ>
+__device__ __forceinline__ EvRegs<TJ> ev_load(const float *p, const EvOffs<TJ> &o) {
+    EvRegs<TJ> r;
+#pragma unroll
+    for (int h = 0; h < ev_regs<TJ>(); ++h) r.e[h] = p[o.o[h]];
+    return r;
+}
+template <int TJ> __device__ __forceinline__ int ev_bits(const EvRegs<TJ> &r, int f, int k) {
+    const int x = f * TJ + k;  // compile-time
+    return __builtin_amdgcn_readlane(__float_as_int(r.e[x / kWave]), x % kWave);
+}
+template <int TJ> __device__ __forceinline__ float ev_at(const EvRegs<TJ> &r, int f, int k) {
+    return __int_as_float(ev_bits<TJ>(r, f, k));
+}
+
+// Inputs 8 G .. 8 G + 7 of a wave, act: bit k set where input k's row is in
+// 0 .. r_end. gl[i]: the G table of tap i + NT * lane. acc += dW contributions;
+// returns (dt_in) the wave's sum over its neurons and taps of input 8 G + k on
+// lanes 8k .. 8k + 7. The empty asm keeps each skip a branch (selects would do
+// the work anyway). kB inputs' reads are in flight before their sums.
+template <int NT, int KW, int TJ, int G, bool DW, bool DT>
+__device__ __forceinline__ float back_group(const float *(&gl)[KW], int lane, unsigned act,
+                                            const EvRegs<TJ> &ev,
+                                            const float (&w)[kBackGroup][KW][NT],
+                                            float (&acc)[kBackGroup][KW][NT]) {
+    constexpr int kB = (NT * KW == 1) ? 8 : (NT * KW <= 3) ? 4 : 2;
+    float v[kBackGroup];
+    static_for<kBackGroup / kB>([&](auto h) {
+        float g0[kB][KW][NT], g1[kB][KW][NT];
+        opaque(act);  // tested bit by bit where it is used, no masks kept
+        static_for<kB>([&](auto j) {
+            constexpr int k = G * kBackGroup + h * kB + j;
+            if (act & (1u << k)) {
+                const int o = ev_bits<TJ>(ev, 0, k) * (NT * kWave);
+                static_for<KW>([&](auto i) {
+                    lds_get<NT>(gl[i] + o, g0[j][i]);
+                    lds_get<NT>(gl[i] + o + NT * kWave, g1[j][i]);
+                });
+                asm volatile("");
+            }
+        });
+        opaque(act);
+        static_for<kB>([&](auto j) {
+            constexpr int kl = h * kB + j, k = G * kBackGroup + kl;
+            v[kl] = 0.f;
+            if (act & (1u << k)) {
+                asm volatile("");
+                float a = 0.f, b = 0.f, L = 0.f, R = 0.f;
+                if constexpr (DW) {
+                    L = ev_at<TJ>(ev, 1, k);
+                    R = ev_at<TJ>(ev, 2, k);
+                }
+                static_for<KW>([&](auto i) {
+                    static_for<NT>([&](auto c) {
+                        const float x = g0[j][i][c], y = g1[j][i][c];
+                        if constexpr (DW) acc[kl][i][c] = fmaf(x, L, fmaf(y, R, acc[kl][i][c]));
+                        if constexpr (DT) {
+                            a = (i == 0 && c == 0) ? w[kl][i][c] * x : fmaf(w[kl][i][c], x, a);
+                            b = (i == 0 && c == 0) ? w[kl][i][c] * y : fmaf(w[kl][i][c], y, b);
+                        }
+                    });
+                });
+                if constexpr (DT) v[kl] = fmaf(a, ev_at<TJ>(ev, 3, k), b * ev_at<TJ>(ev, 4, k));
+            }
+        });
+    });
+    if constexpr (DT) return wave_sum8(v, lane);
+    return 0.f;
+}
+
+}  // namespace dstd

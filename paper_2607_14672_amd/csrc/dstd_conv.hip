@@ -14,16 +14,14 @@
 // The inputs of one cell row (b, py) that have events are bucketed by (event
 // row r, cell column px) -- a counting sort, stable in j' -- so the records
 // of row r under the KW cells of an output position's kernel row form ONE
-// contiguous segment. Both the forward and the dt_in backward walk, per
-// output position, the event rows in grid order and read KH segments per row.
-//  - forward: lanes = output channels; row sums feed the interval scan as
-//    rows close (the weighted events never exist in memory);
-//  - dt_in: lanes = output channels carry G[m] = dL/dw^_m computed in place
-//    from (gamma = -g/slope, t - T_q, q); every record gets the channel sum of
-//    W (dL G[r-1] + dR G[r]) for the tap that joins it to this position, as
-//    one partial per (record, tap), gathered in tap order afterwards.
-// dW reduces over (b, position) samples with lanes = (tap, input channel),
-// G again computed in place.
+// contiguous segment, and the forward walks, per output position, the event
+// rows in grid order and reads KH segments per row: lanes = output channels;
+// row sums feed the interval scan as rows close (the weighted events never
+// exist in memory).
+// The backward needs no order: it takes the cell-major events as they are
+// (dstd_back.h), dW summed over the (b, position) samples and dt_in stored as
+// one partial per (input, tap), gathered in tap order afterwards.
+#include "dstd_back.h"
 #include "dstd_internal.h"
 #include "dstd_kernels.h"
 #include "dstd_profile.h"
@@ -134,8 +132,8 @@ __device__ __forceinline__ int64_t cell_row_input(const ConvGeom &g, int b, int 
 // Wave w owns cells px = w, w + 4, ... (each bucket is ranked by one wave
 // only); where a cell has fewer than 64 inputs a wave takes several of its
 // cells per pass. Records of a bucket keep the input order (j' ascending).
-// The cell row's events (ev) are written too: every input's row, and L, R
-// where the row is >= 0.
+// With ev set the cell row's events are written too: every input's row, and
+// the halves and their derivatives where the row is >= 0.
 __host__ __device__ __forceinline__ int sort_stage_floats(int M, const ConvGeom &g) {
     const int per = g.Wp * g.PC;
     return ((M + 3) * g.Wp + 256 + per) * 4 <= 64 * 1024 ? per : 0;
@@ -151,6 +149,21 @@ __host__ __device__ __forceinline__ int sort_list_ints(int M, const ConvGeom &g)
     return (stage > 0 && ((M + 3) * g.Wp + 256 + stage + cap) * 4 <= 64 * 1024) ? cap : 0;
 }
 
+// the event of cell-major input slot k = cell * PC + d * C_in + ci: its row
+// (int bits), and the halves and their derivatives (read only where it is >= 0)
+__device__ __forceinline__ float *event_at(const CellEv &ev, const ConvGeom &g, int64_t cell, int j) {
+    const int d = fdiv(j, g.dv_cin);
+    return ev.ev + (cell * g.P + d) * 5 * g.C_in + (j - d * g.C_in);
+}
+__device__ __forceinline__ void put_event(const CellEv &ev, const ConvGeom &g, int64_t cell, int j,
+                                          const Event &e) {
+    float *p = event_at(ev, g, cell, j);
+    p[g.C_in] = e.L;
+    p[2 * g.C_in] = e.R;
+    p[3 * g.C_in] = e.dL;
+    p[4 * g.C_in] = e.dR;
+}
+
 __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float *__restrict__ t_in,
                               const ConvSorted &cs, const CellEv &ev, int cr, int *sh) {
     const int R = rows_of(C);
@@ -160,7 +173,6 @@ __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float 
     const int b = cr / g.Hp, py = cr % g.Hp;
     const int nb = R * g.Wp;  // buckets, flat f = r * Wp + px
     const int noff = conv_off_stride(R, g);
-    const bool fwd = cs.L != nullptr, bwd = cs.dL != nullptr;
     int *hist = sh;
     int *part = sh + nb;
     float *tl = sort_stage_floats(C.M, g) > 0 ? reinterpret_cast<float *>(part + 256) : nullptr;
@@ -195,7 +207,7 @@ __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float 
             }
         }
         if (!__syncthreads_or(any)) {
-            if (ev.row && threadIdx.x == 0) ev.live[cr] = 0;
+            if (ev.ev && threadIdx.x == 0) ev.live[cr] = 0;
             int *off0 = cs.off + static_cast<int64_t>(cr) * noff;
             for (int f = threadIdx.x; f < noff; f += blockDim.x) off0[f] = 0;
             return;
@@ -213,7 +225,7 @@ __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float 
     const int cpi = (g.PC < kWave) ? kWave / g.PC : 1;  // cells per pass
     const int lsub = (g.PC < kWave) ? lane / g.PC : 0;
     const int lj = (g.PC < kWave) ? lane % g.PC : lane;
-    const int64_t rb = static_cast<int64_t>(cr) * g.Wp * g.PC;
+    const int64_t cb = static_cast<int64_t>(cr) * g.Wp, rb = cb * g.PC;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     // List form (the row staged and the lists fitting): the histogram pass
     // also appends each event input (slot px * PC + j, row r) to its wave's
@@ -233,7 +245,7 @@ __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float 
             int r = -1;
             if (cell_ok && j < g.PC) {
                 r = bin_row(C, t_at(px, j));
-                if (lst && ev.row) ev.row[rb + px * g.PC + j] = r;
+                if (lst && ev.ev) *event_at(ev, g, cb + px, j) = __int_as_float(r);
                 if (r >= 0) {
                     atomicAdd(&hist[r * g.Wp + px], 1);
                     has = true;
@@ -247,7 +259,7 @@ __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float 
         }
     }
     has = __syncthreads_or(has);
-    if (ev.row && threadIdx.x == 0) ev.live[cr] = has;
+    if (ev.ev && threadIdx.x == 0) ev.live[cr] = has;
     if (!has) {
         // no input of this cell row has events: empty buckets
         int *off0 = cs.off + static_cast<int64_t>(cr) * noff;
@@ -334,22 +346,11 @@ __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float 
             }
             __builtin_amdgcn_wave_barrier();
             if (ok) {
-                if (ev.row) {
-                    ev.L[rb + slot] = e.L;
-                    ev.R[rb + slot] = e.R;
-                }
+                if (ev.ev) put_event(ev, g, cb + px, j, e);
                 const int64_t o = rb + pos;
                 cs.key[o] = px * g.C_in + (j - fdiv(j, g.dv_cin) * g.C_in);
-                if (fwd) {
-                    cs.L[o] = e.L;
-                    cs.R[o] = e.R;
-                }
-                if (bwd) {
-                    cs.dL[o] = e.dL;
-                    cs.dR[o] = e.dR;
-                    cs.px[o] = (r << 16) | px;
-                    cs.src[o] = slot;
-                }
+                cs.L[o] = e.L;
+                cs.R[o] = e.R;
             }
         }
         return;
@@ -364,14 +365,9 @@ __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float 
             int f = -1;
             if (cell_ok && j < g.PC) {
                 e = bin_event(C, t_at(px, j));
-                const int64_t k = rb + static_cast<int64_t>(px) * g.PC + j;
-                if (ev.row) {
-                    // (L, R) are read only where the row is >= 0
-                    ev.row[k] = e.row;
-                    if (e.row >= 0) {
-                        ev.L[k] = e.L;
-                        ev.R[k] = e.R;
-                    }
+                if (ev.ev) {
+                    *event_at(ev, g, cb + px, j) = __int_as_float(e.row);
+                    if (e.row >= 0) put_event(ev, g, cb + px, j, e);
                 }
                 if (e.row >= 0) f = e.row * g.Wp + px;
             }
@@ -392,42 +388,45 @@ __device__ void sort_cell_row(const LifConst &C, const ConvGeom &g, const float 
             if (f >= 0) {
                 const int64_t o = rb + pos;
                 cs.key[o] = px * g.C_in + (j - fdiv(j, g.dv_cin) * g.C_in);
-                if (fwd) {
-                    cs.L[o] = e.L;
-                    cs.R[o] = e.R;
-                }
-                if (bwd) {
-                    cs.dL[o] = e.dL;
-                    cs.dR[o] = e.dR;
-                    cs.px[o] = (e.row << 16) | px;
-                    cs.src[o] = px * g.PC + j;
-                }
+                cs.L[o] = e.L;
+                cs.R[o] = e.R;
             }
         }
     }
 }
 
-// The events of one cell row without the sort (dW wanted, dt_in not), read
-// in NCHW order.
+// The events of one cell row without the sort (the backward without a kept
+// forward): read in NCHW order, staged in LDS where the row fits, written in
+// cell-major order (both coalesced). A row without events writes only its flag.
+__host__ __device__ __forceinline__ int events_stage_floats(const ConvGeom &g) {
+    return g.Wp * g.PC * 4 <= 48 * 1024 ? g.Wp * g.PC : 0;
+}
+
 __device__ void events_cell_row(const LifConst &C, const ConvGeom &g,
-                                const float *__restrict__ t_in, const CellEv &ev, int cr) {
+                                const float *__restrict__ t_in, const CellEv &ev, int cr,
+                                float *tl) {
     const int b = cr / g.Hp, py = cr % g.Hp;
     const int per = g.Wp * g.PC;
-    const int64_t rb = static_cast<int64_t>(cr) * per;
+    const int64_t cb = static_cast<int64_t>(cr) * g.Wp;
+    const bool staged = events_stage_floats(g) > 0;
     bool has = false;
     for (int t = threadIdx.x; t < per; t += blockDim.x) {
         int slot;
-        const int64_t src = cell_row_input(g, b, py, t, slot);
-        const Event e = bin_event(C, t_in[src]);
-        ev.row[rb + slot] = e.row;
-        if (e.row >= 0) {  // (L, R) are read only where the row is >= 0
-            ev.L[rb + slot] = e.L;
-            ev.R[rb + slot] = e.R;
-        }
-        has = has || e.row >= 0;
+        const float v = t_in[cell_row_input(g, b, py, t, slot)];
+        has = has || bin_row(C, v) >= 0;
+        if (staged) tl[slot] = v;
     }
     has = __syncthreads_or(has);
     if (threadIdx.x == 0) ev.live[cr] = has;
+    if (!has) return;
+    for (int t = threadIdx.x; t < per; t += blockDim.x) {
+        int slot = t;
+        const float v = staged ? tl[t] : t_in[cell_row_input(g, b, py, t, slot)];
+        const Event e = bin_event(C, v);
+        const int px = fdiv(slot, g.dv_pc), j = slot - px * g.PC;
+        *event_at(ev, g, cb + px, j) = __int_as_float(e.row);
+        if (e.row >= 0) put_event(ev, g, cb + px, j, e);
+    }
 }
 
 // ------------------------------------------------------ weight layout ----
@@ -525,20 +524,6 @@ struct PosWalk {
             oa[ky] = vky[ky] ? min(max(o[xa * R], 0), per) : 0;
             ob[ky] = vky[ky] ? min(max(o[xb * R], oa[ky]), per) : 0;
         }
-    }
-
-    // segment starts and lengths of event row r (load_offs of its 64-row
-    // chunk done); returns the total length
-    __device__ __forceinline__ int segments(int r, int *s0, int *n0) const {
-        const int l = r & (kWave - 1);
-        int n = 0;
-#pragma unroll
-        for (int ky = 0; ky < KHT; ++ky) {
-            s0[ky] = __builtin_amdgcn_readlane(oa[ky], l);
-            n0[ky] = __builtin_amdgcn_readlane(ob[ky], l) - s0[ky];
-            n += n0[ky];
-        }
-        return n;
     }
 
     // byte offset of a record's weight row; stale keys read past a segment
@@ -1250,11 +1235,11 @@ __global__ __launch_bounds__(256) void conv_fwd_list_kernel(LifConst C, ConvGeom
 }
 
 // --------------------------------------------------------- backward ------
-// Gradient triples (gamma, t - T_q, q) of grad_prep for kGradPos output
+// Gradient triples (gK, gE, q) of grad_triple for kGradPos output
 // positions s = b * Ho*Wo + p and one tile of kGradCh channels (block blk =
 // position group * tiles + tile): read from the NCHW outputs with positions
-// along the lanes, staged in LDS and written position-major [s][co] (each
-// position's channels contiguous).
+// along the lanes, staged in LDS and written position-major [s][3][co] (gK, gE
+// and q as int bits; each position's channels contiguous).
 // rend[s] = min(R-2, max q + 1) over the channels of s that pass gradient
 // (G[m] vanishes for m > q, and a record of event row r reads G[r-1] and
 // G[r]), -1 if none does.
@@ -1264,8 +1249,8 @@ constexpr int kGradLdsBytes = (3 * kGradCh * (kGradPos + 1) + kGradPos) * 4;
 __device__ void grad_block(const LifConst &C, const ConvGeom &g, int64_t n_pos, int64_t blk,
                            const float *__restrict__ t_out, const float *__restrict__ slope,
                            const int *__restrict__ q_idx, const float *__restrict__ grad_t,
-                           const Synfire &sf, float *__restrict__ gam, float *__restrict__ uq,
-                           int *__restrict__ qv, int *__restrict__ rend, int *sh) {
+                           const Synfire &sf, float *__restrict__ tri,
+                           int *__restrict__ rend, int *sh) {
     constexpr int kS = kGradPos + 1;
     float *sg = reinterpret_cast<float *>(sh);
     float *su = sg + kGradCh * kS;
@@ -1339,17 +1324,17 @@ __device__ void grad_block(const LifConst &C, const ConvGeom &g, int64_t n_pos, 
         for (int u = 0; u < kCh; ++u) gt[u] = (q[u] >= 0) ? grad_t[o[u]] : 0.f;  // silent: no load
 #pragma unroll
         for (int u = 0; u < kCh; ++u) {
-            GradPrep gp{0.f, 0.f, -1};
+            GradTriple gp{0.f, 0.f, -1};
             if (q[u] >= 0) {
                 // the spike time only where it is used (no gradient: no load)
                 const float t = (sf.on || gt[u] != 0.f) ? t_out[o[u]] : 0.f;
                 float gu = gt[u];
                 if (sf.on) gu += synfire_dt(sf, t);
-                if (gu != 0.f) gp = grad_prep(C, t, slope[o[u]], q[u], gu);
+                if (gu != 0.f) gp = grad_triple(C, t, slope[o[u]], q[u], gu);
             }
             const int cl = cl0 + u * cstep;
-            sg[cl * kS + pl] = gp.gam;
-            su[cl * kS + pl] = gp.uq;
+            sg[cl * kS + pl] = gp.gK;
+            su[cl * kS + pl] = gp.gE;
             sq[cl * kS + pl] = gp.q;
             if (!tiles && gp.q >= 0) atomicMax(&sl[pl], gp.q);
         }
@@ -1359,10 +1344,10 @@ __device__ void grad_block(const LifConst &C, const ConvGeom &g, int64_t n_pos, 
             const int co = c0 + cl;
             const int64_t sp = s0 + pw;
             if (co < g.C_out && sp < n_pos && sl[pw] >= 0) {
-                const int64_t d = sp * g.C_out + co;
-                gam[d] = sg[cl * kS + pw];
-                uq[d] = su[cl * kS + pw];
-                qv[d] = sq[cl * kS + pw];
+                float *d = tri + sp * 3 * g.C_out + co;
+                d[0] = sg[cl * kS + pw];
+                d[g.C_out] = su[cl * kS + pw];
+                d[2 * g.C_out] = __int_as_float(sq[cl * kS + pw]);
             }
         }
         __syncthreads();
@@ -1395,131 +1380,33 @@ __device__ void dead_channel_block(const ConvGeom &g, int64_t B, const int *__re
     if (threadIdx.x == 0) sf.dq[co] = -(sf.gq * sf.scale * static_cast<float>(sh[0]));
 }
 
-// dt_in partials. Wave = output position; lane = output channel, NT tiles of
-// 64 per lane. Rows stop after the last grid point any channel's G reaches.
-// A block of 256 threads takes positions 4 * bx .. 4 * bx + 3.
-template <int KHT, int NT, int KS>
-__device__ __forceinline__ void dtp_block(const LifConst &C, const ConvGeom &g, int64_t n_pos,
-                                          const float *__restrict__ Wt, const ConvSorted &cs,
-                                          const float *__restrict__ gam,
-                                          const float *__restrict__ uq,
-                                          const int *__restrict__ qv,
-                                          const int *__restrict__ rend, int64_t bx) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = uniform(threadIdx.x >> 6);
-    const int64_t p = bx * 4 + wave;
-    if (p >= n_pos) return;  // wave-uniform; no block barrier below
-    const int r_end = *as_const(rend + p);  // rows r <= r_end need G[r-1], G[r]
-    if (r_end < 0) return;                  // no channel here passes gradient
-    const int R = rows_of(C);
-    const int KT = g.KH * g.KW;
-    PosWalk<KHT> wk;
-    wk.init(C, g, p);
-    if (wk.cell_records(cs) == 0) return;  // no records to receive gradient
-    const int64_t nbase = (static_cast<int64_t>(wk.b) * g.Ho * g.Wo + wk.pos) * g.C_out;
-    float gm[NT], ua[NT], gA[NT], gB[NT];
-    int qa[NT], voff[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int co = t * kWave + lane;
-        const int cc = min(co, g.C_out - 1);
-        const bool ok = co < g.C_out;
-        gm[t] = ok ? gam[nbase + cc] : 0.f;
-        ua[t] = ok ? uq[nbase + cc] : 0.f;
-        qa[t] = ok ? qv[nbase + cc] : -1;
-        voff[t] = cc * static_cast<int>(sizeof(float));
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        gA[t] = 0.f;
-        gB[t] = g_at<KS>(C, gm[t], ua[t], qa[t], 0);
-    }
-    const __amdgpu_buffer_rsrc_t wr = make_rsrc(
-        Wt, static_cast<uint32_t>(static_cast<int64_t>(wk.wlim + 1) * g.C_out * sizeof(float)));
-    const int rstride = g.C_out * static_cast<int>(sizeof(float));
-    for (int r = 0; r <= r_end; ++r) {
-        if ((r & (kWave - 1)) == 0) wk.load_offs(g, cs, R, r, lane);
-        int s0[KHT], n0[KHT];
-        if (wk.segments(r, s0, n0) > 0) {
-#pragma unroll
-            for (int ky = 0; ky < KHT; ++ky) {
-                for (int k0 = 0; k0 < n0[ky]; k0 += kCBatch) {
-                    const int64_t o = wk.recb[ky] + s0[ky] + k0;
-                    const int nk = n0[ky] - k0;
-                    float v[kCBatch];
-#pragma unroll
-                    for (int kk = 0; kk < kCBatch; ++kk) {
-                        const int wo = wk.wrow(as_const(cs.key + o)[kk], ky, rstride);
-                        const float dl = as_const(cs.dL + o)[kk], dr = as_const(cs.dR + o)[kk];
-                        float acc = 0.f;
-#pragma unroll
-                        for (int t = 0; t < NT; ++t) {
-                            const float w = BufLoad<float>::get(wr, voff[t], wo);
-                            acc = fmaf(w, fmaf(dl, gA[t], dr * gB[t]), acc);
-                        }
-                        v[kk] = acc;
-                    }
-                    // channel sums: lane 8kk ends with record kk's total and
-                    // stores it as the record's partial for its tap
-                    static_assert(kCBatch == 8, "wave_sum8 reduces eight records");
-                    const float tot = wave_sum8(v, lane);
-                    const int kl = lane >> 3;
-                    if ((lane & 7) == 0 && kl < nk) {
-                        const int kx = min(max((cs.px[o + kl] & 0xffff) - wk.x0, 0), g.KW - 1);
-                        cs.P[(o + kl) * KT + ky * g.KW + kx] = tot;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            gA[t] = gB[t];
-            gB[t] = g_at<KS>(C, gm[t], ua[t], qa[t], r + 1);
-        }
-    }
-}
-
-template <int KHT, int NT, int KS>
-__global__ __launch_bounds__(256) void conv_dtp_kernel(LifConst C, ConvGeom g, int64_t n_pos,
-                                                       const float *__restrict__ Wt,
-                                                       ConvSorted cs,
-                                                       const float *__restrict__ gam,
-                                                       const float *__restrict__ uq,
-                                                       const int *__restrict__ qv,
-                                                       const int *__restrict__ rend) {
-    dtp_block<KHT, NT, KS>(C, g, n_pos, Wt, cs, gam, uq, qv, rend, blockIdx.x);
-}
-
 // dt_in of the raw inputs of cell row cr, slots [s0, s0 + ns) of its
-// cell-major order (kGatherSlots at most; a block per slice). Each record
-// sums its per-tap partials in tap order, taking only the taps through which
-// an output position passed gradient to the record's event row (the entries
-// the dt_in kernel wrote); the sums are staged in LDS at the record's slot,
-// and the slice is written in NCHW order (inputs without events get 0), so
-// consecutive threads write consecutive addresses.
+// cell-major order (kGatherSlots at most; a block per slice). Each input sums
+// its partials P[cell][entry][slot] (entry = (ky, tap group, tile)) over the
+// (ky, tap group)s with a position that passes gradient (the ones written); the
+// sums are staged in LDS, and the slice is written in NCHW order, so
+// consecutive threads read and write consecutive addresses. A cell row without
+// events, or none of whose output rows passes gradient, writes zeros at once.
 constexpr int kGatherSlots = 4096;
+struct ConvGatherArgs { const int *cr_live, *rend; const float *P; int kwt, kg, n_tile; };
 
-__device__ void dt_gather_block(const ConvGeom &g, int R, const ConvSorted &cs,
-                                const int *__restrict__ rend, float *__restrict__ dt_in, int cr,
-                                int s0, float *buf) {
+__device__ void dt_gather_block(const ConvGeom &g, const ConvGatherArgs &a,
+                                float *__restrict__ dt_in, int cr, int s0, float *buf) {
     const int per = g.Wp * g.PC;
     const int ns = min(kGatherSlots, per - s0);
-    const int nb1 = conv_off_stride(R, g);
-    const int nrec = uniform(min(max(cs.off[static_cast<int64_t>(cr) * nb1 + nb1 - 1], 0), per));
     const int b = cr / g.Hp, py = cr % g.Hp;
-    const int64_t pos0 = static_cast<int64_t>(b) * g.Ho * g.Wo;
-    // output rows oy whose kernel row ky = py + pad - oy * stride is in
-    // range, walked with ky ascending (the tap order of the sum)
-    const int ny0 = py + g.pad;
-    const int oy_hi = min(g.Ho - 1, ny0 / g.stride);
-    const int oy_lo = (max(0, ny0 - g.KH + 1) + g.stride - 1) / g.stride;
-    // no record, or no output position of those rows passes gradient: the
-    // cell row's dt_in is 0
-    bool live = false;
-    if (nrec > 0)
-        for (int k = threadIdx.x; k < (oy_hi - oy_lo + 1) * g.Wo; k += blockDim.x)
-            live = live || rend[pos0 + static_cast<int64_t>(oy_lo) * g.Wo + k] >= 0;
-    if (!__syncthreads_or(live)) {
+    // the kernel rows ky (bit mask) whose output row exists and passes gradient
+    unsigned kys = 0;
+    if (a.cr_live[cr])
+        for (int ky = 0; ky < g.KH; ++ky) {
+            const int y = py + g.pad - ky, oy = y / g.stride;
+            if (y < 0 || oy * g.stride != y || oy >= g.Ho) continue;
+            bool any = false;
+            for (int x = threadIdx.x; x < g.Wo; x += blockDim.x)
+                any = any || a.rend[(static_cast<int64_t>(b) * g.Ho + oy) * g.Wo + x] >= 0;
+            if (__syncthreads_or(any)) kys |= 1u << ky;
+        }
+    if (kys == 0) {
         for (int t = threadIdx.x; t < per; t += blockDim.x) {
             int slot;
             const int64_t dst = cell_row_input(g, b, py, t, slot);
@@ -1527,27 +1414,31 @@ __device__ void dt_gather_block(const ConvGeom &g, int R, const ConvSorted &cs,
         }
         return;
     }
-    for (int t = threadIdx.x; t < ns; t += blockDim.x) buf[t] = 0.f;
-    __syncthreads();
-    const int64_t rb = static_cast<int64_t>(cr) * per;
-    const int KT = g.KH * g.KW;
-    for (int k = threadIdx.x; k < nrec; k += blockDim.x) {
-        const int src = cs.src[rb + k];
-        if (src < s0 || src >= s0 + ns) continue;
-        const int pr = cs.px[rb + k];
-        const int px = pr & 0xffff, row = pr >> 16;
-        const int nx0 = px + g.pad;
-        const int ox_hi = min(g.Wo - 1, nx0 / g.stride);
-        const int ox_lo = (max(0, nx0 - g.KW + 1) + g.stride - 1) / g.stride;
-        const float *P = cs.P + (rb + k) * KT;
+    const int entries = g.KH * a.kg * a.n_tile;
+    for (int t = threadIdx.x; t < ns; t += blockDim.x) {
+        const int slot = s0 + t;
+        const int px = fdiv(slot, g.dv_pc), j = slot - px * g.PC;
+        const float *pc = a.P + (static_cast<int64_t>(cr) * g.Wp + px) * entries * g.PC + j;
         float acc = 0.f;
-        for (int oy = oy_hi; oy >= oy_lo; --oy) {
-            const int ky = ny0 - oy * g.stride;
-            const int *rr = rend + pos0 + static_cast<int64_t>(oy) * g.Wo;
-            for (int ox = ox_hi; ox >= ox_lo; --ox)
-                if (row <= rr[ox]) acc += P[ky * g.KW + nx0 - ox * g.stride];
+        for (int ky = 0; ky < g.KH; ++ky) {
+            if (!((kys >> ky) & 1u)) continue;
+            const int *rr = a.rend + (static_cast<int64_t>(b) * g.Ho + (py + g.pad - ky) / g.stride) * g.Wo;
+            for (int kg = 0; kg < a.kg; ++kg) {
+                // the group's first tap meets position x / stride (one-tap
+                // groups), or its taps meet positions x - kwt + 1 .. x
+                const int x = px + g.pad - kg * a.kwt, ox = x / g.stride;
+                bool on = false;
+                if (a.kwt == 1)
+                    on = x >= 0 && ox * g.stride == x && ox < g.Wo && rr[ox] >= 0;
+                else
+                    for (int i = 0; i < a.kwt; ++i)
+                        on = on || (x - i >= 0 && x - i < g.Wo && rr[x - i] >= 0);
+                if (!on) continue;
+                for (int ti = 0; ti < a.n_tile; ++ti)
+                    acc += pc[static_cast<int64_t>((ky * a.kg + kg) * a.n_tile + ti) * g.PC];
+            }
         }
-        buf[src - s0] = acc;
+        buf[t] = acc;
     }
     __syncthreads();
     for (int t = threadIdx.x; t < per; t += blockDim.x) {
@@ -1557,176 +1448,280 @@ __device__ void dt_gather_block(const ConvGeom &g, int R, const ConvSorted &cs,
     }
 }
 
-// dW[co, ci, k] = (1/P) sum_{b, p} sum_d (G[b, r, p, co] L + G[b, r+1, p, co] R)
-// over the raw inputs d of the cell that tap k of position p reads.
-// Lane = (k, ci); a block covers 256 of them and a tile of TI channels whose
-// sums stay in registers over its share of the (b, p) samples. G[b, :, p,
-// tile] is computed in place from (gamma, t - T_q, q) -- each thread owns one
-// channel and a fixed set of rows; channels without gradient cost no
-// exponential -- and staged in LDS as rows G[r][channel] of TI + 1 floats,
-// double buffered (an event's two halves G[r][i], G[r+1][i] are TI + 1 dwords
-// apart: one two-address LDS read; rows R-1 and R stay zero), the next
-// sample's values in registers (NPER per thread) during this one's sums. A
-// sample whose tile is all zero is skipped.
-// Block (bx, by, bz): inputs 256 bx .., channel tile by, batch split bz.
-// gs: the dynamic LDS ([2][R + 1][TI + 1], then the live sample list);
-// n_live_w: four ints of LDS.
-struct ConvDwArgs {
-    int64_t n_samp;
-    int s_per_split;
-    const float *gam, *uq;
-    const int *qv, *rend, *cr_live, *ev_row;
-    const float *ev_L, *ev_R;
-    float *part;
+// dW and the dt_in partials of one layer (dstd_back.h). A block walks output
+// rows (b, oy) that pass gradient, position by position; its waves share the
+// positions' G tables and own one kernel row ky, KWT neighbouring taps of it
+// and TJ input channels each. At step n the table of position ox = n is new,
+// and a wave's cell px = n stride - pad + kx0 meets the KWT tables n, n - 1, ...
+// at once (stride 1): its events are read once and its inputs' lane sums taken
+// once for KWT taps. The waves write the next position's table meanwhile, into a
+// ring, one barrier per step. KWT = 1 (other strides, 1-wide kernels, and grids
+// whose ring would not fit) gives every tap its own waves.
+// Only the runs of steps whose tables include one with gradient are walked (a
+// row's positions without gradient further than KWT from one with it cost
+// nothing); inside a run a position without gradient is a table of zeros, so a
+// tap needs no test of its own. Tables reach the row's largest rend.
+// dW: partial sums part[z][co][k * C_in + ci] per split z of the rows. dt_in:
+// P[cell][entry][slot], entry = (ky, tap group, channel tile of the launch),
+// written for the walked cells whose row has events; the gather adds the
+// entries. Further launches (more tiles than entries fit) add to theirs, in
+// order.
+// Against the forms before it (dW with lanes = inputs and G gathered from LDS;
+// dt_in with a weight row loaded and a wave reduced per (record, position)):
+// a 64 -> 64 channel 32 x 32 layer, batch 64, M = 32: 2.10 ms -> 0.77 ms.
+struct ConvBackArgs {
+    int n_rows, rows_per_split;  // output rows (b, oy)
+    int cpt, n_chunk;        // input-channel chunks per (ky, tap group); chunks in all
+    int kg;                  // tap groups per kernel row
+    int tile0, n_tile, add;  // channel tiles tile0 .. + n_tile - 1; add to P
+    const float *tri;
+    const int *rend, *cr_live;
+    const float *ev, *Wt;
+    float *P, *part;
     int *zlive;
 };
-template <int TI, int NPER, int KS>
-__device__ __forceinline__ void dw_block(const LifConst &C, const ConvGeom &g,
-                                         const ConvDwArgs &a, int bx, int by, int bz,
-                                         float *gs, int *n_live_w) {
-    const int64_t n_samp = a.n_samp;
-    const int s_per_split = a.s_per_split;
-    const float *__restrict__ gam = a.gam;
-    const float *__restrict__ uq = a.uq;
-    const int *__restrict__ qv = a.qv;
-    const int *__restrict__ rend = a.rend;
-    const int *__restrict__ cr_live = a.cr_live;
-    const int *__restrict__ ev_row = a.ev_row;
-    const float *__restrict__ ev_L = a.ev_L;
-    const float *__restrict__ ev_R = a.ev_R;
-    constexpr int kStr = TI + 1;
-    const int R = rows_of(C);
-    const int gbuf = (R + 1) * kStr;
-    const int NJ = g.KH * g.KW * g.C_in;
-    const int jj = bx * 256 + threadIdx.x;
-    const int co0 = by * TI;
-    const int ni = min(TI, g.C_out - co0);
-    const int64_t s_lo = static_cast<int64_t>(bz) * s_per_split;
-    const int64_t s_hi = min(n_samp, s_lo + s_per_split);
-    const bool j_ok = jj < NJ;
-    const int k = (j_ok ? jj : 0) / g.C_in, ci = (j_ok ? jj : 0) % g.C_in;
-    const int ky = k / g.KW, kx = k % g.KW;
-    const int HoWo = g.Ho * g.Wo;
-    float acc[TI];
+constexpr int kBackWaves = 12;
+constexpr int kBackRowList = 256;  // output rows listed at a time
+
+// G tables: those of a step and the next one's
+constexpr int back_ring(int kwt) { return kwt == 1 ? 2 : 4; }
+
+template <int KWT, int NT, int TJ, bool DW, bool DT>
+__global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst C, ConvGeom g,
+                                                                       ConvBackArgs a) {
+    constexpr int kG = TJ / kBackGroup;
+    constexpr int kRow = NT * kWave;
+    constexpr int kRing = back_ring(KWT);
+    extern __shared__ float gs[];  // G [kRing][R][kRow], pairs (a_d, k_d)
+    __shared__ int row_top[kBackRowList];  // largest rend of each listed row
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = uniform(threadIdx.x >> 6);
+    const int nw = static_cast<int>(blockDim.x) >> 6;
+    const int z = blockIdx.y;
+    const int tile = a.tile0 + static_cast<int>(blockIdx.z);
+    const int r_lo = z * a.rows_per_split;
+    const int r_hi = min(a.n_rows, r_lo + a.rows_per_split);
+    // the largest rend of rows rl .. rl + nl - 1 (rows of -1 are skipped);
+    // returns whether any passes gradient
+    auto list_rows = [&](int rl, int nl) {
+        bool any = false;
+        for (int l = wave; l < nl; l += nw) {
+            int m = -1;
+            for (int x = lane; x < g.Wo; x += kWave)
+                m = max(m, a.rend[static_cast<int64_t>(rl + l) * g.Wo + x]);
 #pragma unroll
-    for (int ii = 0; ii < TI; ++ii) acc[ii] = 0.f;
-    const int total = R * TI;
-    // element c of this thread: row r = r_first + c * (256 / TI), channel l
-    const int l_own = threadIdx.x % TI, r_first = threadIdx.x / TI;
-    constexpr int kRowStep = 256 / TI;
-    const GStep gst = g_step<KS>(C, kRowStep);
-    float pre[NPER];
-    // G[b, :, p, tile] of sample s; returns whether any value is nonzero
-    auto fetch = [&](int64_t s) {
-        const int64_t nb = s * g.C_out + co0 + min(l_own, ni - 1);
-        const bool own = l_own < ni;
-        const float gm = own ? gam[nb] : 0.f;
-        const float u = own ? uq[nb] : 0.f;
-        const int q = own ? qv[nb] : -1;
-        g_strided<NPER, KS>(C, gst, gm, u, q, r_first - 1, kRowStep, pre);
-        bool nz = false;
-#pragma unroll
-        for (int c = 0; c < NPER; ++c) nz = nz || pre[c] != 0.f;
-        return nz;
-    };
-    auto store = [&](float *buf) {
-#pragma unroll
-        for (int c = 0; c < NPER; ++c) {
-            const int kk = threadIdx.x + c * 256;
-            if (kk < total) {
-                const int r = kk / TI, l = kk % TI;
-                if (r < R - 1) buf[r * kStr + l] = pre[c];
-            }
+            for (int o = kWave / 2; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o));
+            if (lane == 0) row_top[l] = m;
+            any = any || m >= 0;
         }
+        return __syncthreads_or(any) != 0;
     };
-    for (int t = threadIdx.x; t < 2 * 2 * kStr; t += 256)
-        gs[(t / (2 * kStr)) * gbuf + (R - 1) * kStr + t % (2 * kStr)] = 0.f;
-    // the split's samples through which any gradient flows, in order
-    int *list = reinterpret_cast<int *>(gs + 2 * gbuf);
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int n_live = 0;
-    for (int64_t c0 = s_lo; c0 < s_hi; c0 += 256) {
-        const int64_t sc = c0 + threadIdx.x;
-        const bool f = sc < s_hi && rend[sc] >= 0;
-        const uint64_t m = __ballot(f);
-        if (lane == 0) n_live_w[wave] = __popcll(m);
-        __syncthreads();
-        int base = n_live;
-        for (int w = 0; w < wave; ++w) base += n_live_w[w];
-        if (f) list[base + __popcll(m & below)] = static_cast<int>(sc - s_lo);
-        for (int w = 0; w < 4; ++w) n_live += n_live_w[w];
-        __syncthreads();
+    // the first rows with gradient; a split without any writes no partials (the
+    // reduction skips it)
+    int rl = r_lo;
+    bool any_row = false;
+    for (; rl < r_hi; rl += kBackRowList) {
+        any_row = list_rows(rl, min(kBackRowList, r_hi - rl));
+        if (any_row) break;
+        __syncthreads();  // the list is rewritten
     }
-    // a split without such samples writes no partials (the reduction skips it)
-    if (threadIdx.x == 0 && bx == 0 && by == 0) a.zlive[bz] = n_live > 0;
-    if (n_live == 0) return;
-    bool live = false;  // the staged sample's tile has a nonzero value
-    {
-        live = fetch(s_lo + list[0]);
-        store(gs);
-    }
-    live = __syncthreads_or(live);
-    for (int i = 0; i < n_live; ++i) {
-        const int64_t s = s_lo + list[i];
-        const float *cur = gs + (i & 1) * gbuf;
-        const bool more = i + 1 < n_live;
-        bool live_next = false;
-        if (more) live_next = fetch(s_lo + list[i + 1]);
-        if (live) {
-            const int b = static_cast<int>(s) / HoWo, p = static_cast<int>(s) % HoWo;
-            const int py = (p / g.Wo) * g.stride - g.pad + ky;
-            const int px = (p % g.Wo) * g.stride - g.pad + kx;
-            if (j_ok && py >= 0 && py < g.Hp && px >= 0 && px < g.Wp &&
-                cr_live[static_cast<int64_t>(b) * g.Hp + py]) {
-                const int64_t e0 = ((static_cast<int64_t>(b) * g.Hp + py) * g.Wp + px) * g.PC + ci;
-                for (int d = 0; d < g.P; ++d) {
-                    const int64_t e = e0 + static_cast<int64_t>(d) * g.C_in;
-                    const int r = min(ev_row[e], R - 2);
-                    if (r >= 0) {
-                        const float L = ev_L[e], Rv = ev_R[e];
-                        const float *q = cur + r * kStr;
-#pragma unroll
-                        for (int ii = 0; ii < TI; ++ii)
-                            acc[ii] = fmaf(q[ii], L, fmaf(q[ii + kStr], Rv, acc[ii]));
+    if (DW && threadIdx.x == 0 && blockIdx.x == 0 && tile == 0) a.zlive[z] = any_row;
+    if (!any_row) return;
+    const int R = rows_of(C);
+    const int ts = R * kRow;  // floats of a G table
+    float2 *tab = reinterpret_cast<float2 *>(gs + kRing * ts);
+    // this wave's chunk: kernel row ky, taps kx0 .. kx0 + KWT - 1, channels
+    // ci0 .. ci0 + nj - 1
+    const int chunk = static_cast<int>(blockIdx.x) * nw + wave;
+    const bool mine = chunk < a.n_chunk;
+    const int tg = mine ? chunk / a.cpt : 0;
+    const int ci0 = (mine ? chunk - tg * a.cpt : 0) * TJ;
+    const int nj = mine ? min(TJ, g.C_in - ci0) : 0;
+    const int ky = tg / a.kg, kx0 = (tg - ky * a.kg) * KWT;
+    const int co = tile * kRow + NT * lane;  // this lane's channels co .. co + NT - 1
+    g_table_fill(C, tab);
+    for (int k = threadIdx.x; k < kRing * kRow; k += blockDim.x) gs[(k / kRow) * ts + k % kRow] = 0.f;
+    // channels past C_out: weight 0 and no gradient
+    float acc[kG][kBackGroup][KWT][NT], w[kG][kBackGroup][KWT][NT];
+    static_for<kG>([&](auto h) {
+        static_for<kBackGroup>([&](auto j) {
+            static_for<KWT>([&](auto i) {
+                static_for<NT>([&](auto c) {
+                    acc[h][j][i][c] = 0.f;
+                    w[h][j][i][c] = 0.f;
+                    if constexpr (DT) {
+                        const int ci = min(ci0 + h * kBackGroup + j, g.C_in - 1);
+                        const int k = ky * g.KW + kx0 + i;
+                        if (kx0 + i < g.KW && co + c < g.C_out)
+                            w[h][j][i][c] = a.Wt[static_cast<int64_t>(k * g.C_in + ci) * g.C_out + co + c];
                     }
+                });
+            });
+        });
+    });
+    // loaded before the loops (a load still pending at their entry would make
+    // every step wait for its own prefetches)
+    static_for<kG>([&](auto h) {
+        static_for<kBackGroup>([&](auto j) {
+            static_for<KWT>([&](auto i) {
+                static_for<NT>([&](auto c) { settle(w[h][j][i][c]); });
+            });
+        });
+    });
+    // gradient triples of the position whose triples start at p (scalar)
+    unsigned tri_o[NT];
+    bool ch_ok[NT];
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+        tri_o[c] = static_cast<unsigned>(min(co + c, g.C_out - 1));
+        ch_ok[c] = co + c < g.C_out;
+    }
+    auto load_tri = [&](const float *p) {
+        GTri<NT> t;
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            t.gK[c] = p[tri_o[c]];
+            t.gE[c] = (p + g.C_out)[tri_o[c]];
+            t.q[c] = __float_as_int((p + 2 * g.C_out)[tri_o[c]]);
+        }
+        return t;
+    };
+    auto write_rows = [&](GTri<NT> t, int top, int slot) {
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            t.gK[c] = ch_ok[c] ? t.gK[c] : 0.f;
+            t.gE[c] = ch_ok[c] ? t.gE[c] : 0.f;
+            t.q[c] = ch_ok[c] ? t.q[c] : -1;
+        }
+        g_rows<NT>(C.M, tab, t, top, wave, nw, gs + slot * ts + NT * lane);
+    };
+    // a table without gradient: rows 1 .. top + 1
+    auto zero_rows = [&](int top, int slot) {
+        float *zt = gs + slot * ts + kRow;
+        for (int k = threadIdx.x; k < (top + 1) * kRow; k += blockDim.x) zt[k] = 0.f;
+    };
+    // steps of a row: positions 0 .. Wo - 1, and (KWT > 1) the cells after them
+    const int steps = (KWT == 1) ? g.Wo : min(g.Wp + g.pad, g.Wo + KWT - 1);
+    const int entries = g.KH * a.kg * a.n_tile;
+    const int entry = tg * a.n_tile + static_cast<int>(blockIdx.z);
+    // lane 8j + h of a partial store holds input 8h + j of the wave
+    const int p_off = (lane & 7) < kG ? 4 * ((lane & 7) * kBackGroup + (lane >> 3)) : 1 << 30;
+    const EvOffs<TJ> ev_o = ev_offs<TJ>(g.C_in, max(nj, 1), lane);
+    const int64_t ev_cell = static_cast<int64_t>(kEvFields) * g.PC, p_cell = static_cast<int64_t>(entries) * g.PC;
+    while (true) {
+        const int nl = min(kBackRowList, r_hi - rl);
+        for (int l = 0; l < nl; ++l) {
+            const int top = uniform(row_top[l]);
+            if (top < 0) continue;  // block-uniform
+            const int rw = rl + l;
+            const int b = rw / g.Ho, py = (rw - b * g.Ho) * g.stride - g.pad + ky;
+            const int cr = b * g.Hp + py;
+            const bool live = mine && py >= 0 && py < g.Hp && *as_const(a.cr_live + (py >= 0 && py < g.Hp ? cr : 0));
+            const float *ev_row = a.ev + static_cast<int64_t>(live ? cr : 0) * g.Wp * ev_cell + ci0;
+            float *p_row = a.P + static_cast<int64_t>(live ? cr : 0) * g.Wp * p_cell + static_cast<int64_t>(entry) * g.PC + ci0;
+            // rend of position x, held 64 positions at a time (lane = x mod 64)
+            int er = 0, er0 = -1;
+            auto rend_at = [&](int x) {
+                if (x >= g.Wo) return -1;
+                if ((x >> 6) != er0) {
+                    er0 = x >> 6;
+                    er = a.rend[static_cast<int64_t>(rw) * g.Wo + min(er0 * kWave + lane, g.Wo - 1)];
+                }
+                return __builtin_amdgcn_readlane(er, x & (kWave - 1));
+            };
+            int n = 0;
+            while (true) {
+                // the run's first step: the next position with gradient
+                int e[KWT];  // rend of the step's tables
+                static_for<KWT>([&](auto i) { e[i] = -1; });
+                for (; n < g.Wo && (e[0] = rend_at(n)) < 0; ++n) {}
+                if (n >= g.Wo || n >= steps) break;
+                // items: (step n, raw pixel d), the events of one, and the triples
+                // of the position after its step, loaded during the one before.
+                // Loads and the store are issued whether they are needed or not
+                // (addresses clamped, the store's range empty): a wait then counts
+                // what was issued since, and prefetches stay in flight
+                int d = 0, px = n * g.stride - g.pad + kx0, r_end = e[0];
+                const float *tri_p = a.tri + (static_cast<int64_t>(rw) * g.Wo + n) * 3 * g.C_out;
+                auto here = [&](int x) { return live && x >= 0 && x < g.Wp; };
+                auto item_ev = [&](int x, int dd) {
+                    return ev_load<TJ>(ev_row + min(max(x, 0), g.Wp - 1) * ev_cell + dd * kEvFields * g.C_in, ev_o);
+                };
+                EvRegs<TJ> ev[2];
+                ev[0] = item_ev(px, 0);
+                write_rows(load_tri(tri_p), top, n & (kRing - 1));
+                static_for<KWT - 1>([&](auto i) { zero_rows(top, (n - 1 - i) & (kRing - 1)); });
+                __syncthreads();
+                bool more = true;
+                auto item = [&](auto par) {
+                    constexpr int p = par;
+                    const bool last_d = d + 1 == g.P;
+                    ev[p ^ 1] = item_ev(last_d ? px + g.stride : px, last_d ? 0 : d + 1);
+                    const GTri<NT> t_n = load_tri(tri_p + (n + 1 < g.Wo ? 3 * g.C_out : 0));
+                    float tot[kG];
+                    static_for<kG>([&](auto h) { tot[h] = 0.f; });
+                    if (here(px)) {
+                        const float *gl[KWT];
+                        static_for<KWT>([&](auto i) { gl[i] = gs + ((n - i) & (kRing - 1)) * ts + NT * lane; });
+                        const unsigned act = static_cast<unsigned>(__ballot(
+                            lane < nj && static_cast<unsigned>(__float_as_int(ev[p].e[0])) <= static_cast<unsigned>(r_end)));
+                        static_for<kG>([&](auto h) {
+                            if ((act >> (h * kBackGroup)) & 0xffu)
+                                tot[h] = back_group<NT, KWT, TJ, h, DW, DT>(gl, lane, act, ev[p], w[h], acc[h]);
+                        });
+                    }
+                    if constexpr (DT) {
+                        float v = tot[0];
+                        static_for<kG>([&](auto x) { v = ((lane & 7) == x) ? tot[x] : v; });
+                        float *out = p_row + min(max(px, 0), g.Wp - 1) * p_cell + d * g.C_in;
+                        const __amdgpu_buffer_rsrc_t pr = make_rsrc(out, here(px) ? static_cast<uint32_t>(nj) * 4u : 0u);
+                        if (a.add) v += BufLoad<float>::get(pr, p_off, 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), pr, p_off, 0, 0);
+                    }
+                    ++d;
+                    if (last_d) {
+                        ++n;
+                        static_for<KWT - 1>([&](auto i) { e[KWT - 1 - i] = e[KWT - 2 - i]; });
+                        e[0] = rend_at(n);
+                        r_end = e[0];
+                        static_for<KWT>([&](auto i) { r_end = max(r_end, e[i]); });
+                        more = n < steps && r_end >= 0;
+                        if (more) {
+                            if (KWT == 1 || e[0] >= 0) write_rows(t_n, top, n & (kRing - 1));
+                            else zero_rows(top, n & (kRing - 1));
+                        }
+                        tri_p += 3 * g.C_out;
+                        px += g.stride;
+                        d = 0;
+                        __syncthreads();
+                    }
+                };
+                while (true) {
+                    item(std::integral_constant<int, 0>{});
+                    if (!more) break;
+                    item(std::integral_constant<int, 1>{});
+                    if (!more) break;
                 }
             }
         }
-        if (more) store(gs + ((i + 1) & 1) * gbuf);
-        live = __syncthreads_or(live_next);
+        rl += kBackRowList;
+        if (rl >= r_hi) break;
+        __syncthreads();  // the list's readers
+        list_rows(rl, min(kBackRowList, r_hi - rl));
     }
-    if (!j_ok) return;
-    float *out = a.part + (static_cast<int64_t>(bz) * g.C_out + co0) * NJ + jj;
-#pragma unroll
-    for (int ii = 0; ii < TI; ++ii)
-        if (ii < ni) out[static_cast<int64_t>(ii) * NJ] = acc[ii];
-}
-
-template <int TI, int NPER, int KS>
-__global__ __launch_bounds__(256) void conv_dw_kernel(LifConst C, ConvGeom g, ConvDwArgs a) {
-    extern __shared__ float gs[];
-    __shared__ int n_live_w[4];
-    dw_block<TI, NPER, KS>(C, g, a, blockIdx.x, blockIdx.y, blockIdx.z, gs, n_live_w);
-}
-
-// dW blocks (nbx * nby * nbz of them, x fastest) and then the dt_in partial
-// blocks of the same layer in one launch: the two read the same gradient
-// triples and write disjoint buffers, so they need no order between them.
-template <int TI, int NPER, int KHT, int NT, int KS>
-__global__ __launch_bounds__(256) void conv_dwdt_kernel(LifConst C, ConvGeom g, ConvDwArgs a,
-                                                        int nbx, int nby, int n_dw,
-                                                        int64_t n_pos,
-                                                        const float *__restrict__ Wt,
-                                                        ConvSorted cs) {
-    extern __shared__ float gs[];
-    __shared__ int n_live_w[4];
-    const int id = blockIdx.x;
-    if (id < n_dw) {
-        const int bx = id % nbx, t = id / nbx;
-        dw_block<TI, NPER, KS>(C, g, a, bx, t % nby, t / nby, gs, n_live_w);
-    } else {
-        dtp_block<KHT, NT, KS>(C, g, n_pos, Wt, cs, a.gam, a.uq, a.qv, a.rend, id - n_dw);
+    if constexpr (DW) {
+        const int NJ = g.KH * g.KW * g.C_in;
+        static_for<NT>([&](auto c) {
+            if (co + c >= g.C_out) return;
+            static_for<KWT>([&](auto i) {
+                if (kx0 + i >= g.KW) return;
+                float *out = a.part + (static_cast<int64_t>(z) * g.C_out + co + c) * NJ +
+                             (ky * g.KW + kx0 + i) * g.C_in + ci0;
+                static_for<TJ>([&](auto jj) {
+                    if (jj < nj) out[jj] = acc[jj / kBackGroup][jj % kBackGroup][i][c];
+                });
+            });
+        });
     }
 }
 
@@ -1796,10 +1791,11 @@ __device__ void dw_reduce_block(const ConvGeom &g, int nsplit, const float *__re
 // several microseconds even when its work is tiny).
 // Forward set-up: blocks [0, n_sort) sort cell rows (with ev set, keeping
 // the cell-major events for the backward too), the next n_bin bin the raw
-// inputs of a direct layer once (bin_block), the rest lay out WT.
+// inputs of a direct layer once (bin_block), the next n_ev keep a direct
+// layer's cell-major events, the rest lay out WT.
 template <typename WT>
 __global__ __launch_bounds__(256) void conv_fprep_kernel(LifConst C, ConvGeom g, int n_sort,
-                                                         int n_bin, int64_t n_in,
+                                                         int n_bin, int n_ev, int64_t n_in,
                                                          const float *__restrict__ t_in,
                                                          ConvSorted cs, CellEv ev,
                                                          const WT *__restrict__ W,
@@ -1810,36 +1806,34 @@ __global__ __launch_bounds__(256) void conv_fprep_kernel(LifConst C, ConvGeom g,
         sort_cell_row(C, g, t_in, cs, ev, blk, sh);
     else if (blk < n_sort + n_bin)
         bin_block(C, n_in, t_in, cs, blk - n_sort);
+    else if (blk < n_sort + n_bin + n_ev)
+        events_cell_row(C, g, t_in, ev, blk - n_sort - n_bin, reinterpret_cast<float *>(sh));
     else
-        weights_block<WT>(g, W, Wt, blk - n_sort - n_bin, reinterpret_cast<float (*)[33]>(sh));
+        weights_block<WT>(g, W, Wt, blk - n_sort - n_bin - n_ev, reinterpret_cast<float (*)[33]>(sh));
 }
 
-// Backward set-up: [0, n_cr) cell rows (events for dW; with cs.key set also
-// the sort with derivatives), then n_gr blocks of gradient triples and
-// per-position gradient rows (rend), n_dq blocks of dead-neuron terms (one
-// per channel, synfire terms on) and the WT layout.
+// Backward set-up: [0, n_cr) cell rows' events, then n_gr blocks of gradient
+// triples and per-position gradient rows (rend), n_dq blocks of dead-neuron
+// terms (one per channel, synfire terms on) and the WT layout.
 template <typename WT>
 __global__ __launch_bounds__(256) void conv_bprep_kernel(
     LifConst C, ConvGeom g, int n_cr, int n_gr, int n_dq, const float *__restrict__ t_in,
-    ConvSorted cs, CellEv ev, int64_t n_pos, const float *__restrict__ t_out,
+    CellEv ev, int64_t n_pos, const float *__restrict__ t_out,
     const float *__restrict__ slope, const int *__restrict__ q_idx,
-    const float *__restrict__ grad_t, Synfire sf, float *__restrict__ gam,
-    float *__restrict__ uq, int *__restrict__ qv, int *__restrict__ rend,
+    const float *__restrict__ grad_t, Synfire sf, float *__restrict__ tri,
+    int *__restrict__ rend,
     const WT *__restrict__ W, float *__restrict__ Wt) {
     extern __shared__ int sh[];
     // XCD-aware order: neighbouring gradient blocks read the two halves of
     // the same cache lines of the NCHW outputs
     int blk = xcd_block(blockIdx.x, gridDim.x);
     if (blk < n_cr) {
-        if (cs.key)
-            sort_cell_row(C, g, t_in, cs, ev, blk, sh);
-        else
-            events_cell_row(C, g, t_in, ev, blk);
+        events_cell_row(C, g, t_in, ev, blk, reinterpret_cast<float *>(sh));
         return;
     }
     blk -= n_cr;
     if (blk < n_gr) {
-        grad_block(C, g, n_pos, blk, t_out, slope, q_idx, grad_t, sf, gam, uq, qv, rend, sh);
+        grad_block(C, g, n_pos, blk, t_out, slope, q_idx, grad_t, sf, tri, rend, sh);
         return;
     }
     blk -= n_gr;
@@ -1852,12 +1846,12 @@ __global__ __launch_bounds__(256) void conv_bprep_kernel(
 
 // Backward finish: [0, n_red) dW split reduction, the rest gathers dt_in
 // (nsl blocks per cell row, one per slice of kGatherSlots slots).
-__global__ __launch_bounds__(256) void conv_bfin_kernel(ConvGeom g, int R, int n_red, int nsplit,
+__global__ __launch_bounds__(256) void conv_bfin_kernel(ConvGeom g, int n_red, int nsplit,
                                                         const float *__restrict__ part,
                                                         const int *__restrict__ zlive,
                                                         const float *__restrict__ dq,
                                                         float *__restrict__ dW, int nsl,
-                                                        ConvSorted cs, const int *__restrict__ rend,
+                                                        ConvGatherArgs ga,
                                                         float *__restrict__ dt_in) {
     static_assert(kGatherSlots >= 256, "the reduction shares the gather's LDS");
     __shared__ float lds[kGatherSlots];
@@ -1866,7 +1860,7 @@ __global__ __launch_bounds__(256) void conv_bfin_kernel(ConvGeom g, int R, int n
         dw_reduce_block(g, nsplit, part, zlive, dq, dW, blk, n_red, lds);
     } else {
         const int t = blk - n_red;
-        dt_gather_block(g, R, cs, rend, dt_in, t / nsl, (t % nsl) * kGatherSlots, lds);
+        dt_gather_block(g, ga, dt_in, t / nsl, (t % nsl) * kGatherSlots, lds);
     }
 }
 
@@ -1900,26 +1894,29 @@ hipError_t launch_conv_forward(const LifConst &C, const ConvGeom &g, int64_t B, 
                                float *t_out, float *slope, int *q_idx, hipStream_t st) {
     const int np = conv_fwd_list_np(C.M, g);
     const bool direct = conv_fwd_direct(g, np);
-    const bool keep = cs.dL != nullptr;
-    // the direct walk bins its inputs itself: no cell-row sort, unless the
-    // sort is kept for the backward
-    const int n_sort = (direct && !keep) ? 0 : static_cast<int>(B * g.Hp);
-    // without the sort, a direct layer on plain input has its raw inputs
+    const bool keep = ev.ev != nullptr;
+    // the direct walk bins its inputs itself: no cell-row sort (a keeping
+    // call leaves the events for the backward all the same)
+    const int n_sort = direct ? 0 : static_cast<int>(B * g.Hp);
+    const int n_ev = (direct && keep) ? static_cast<int>(B * g.Hp) : 0;
+    // a direct layer on plain input has its raw inputs
     // binned once here, in NCHW order, in the sort's key/L/R arrays (as many
     // slots as raw inputs), and its positions load those events
     const int64_t n_in = B * g.C_in * g.H * g.W;
-    const int pre = (direct && !keep && g.pool == 1) ? 1 : 0;
+    const int pre = (direct && g.pool == 1) ? 1 : 0;
     const int n_bin = pre ? static_cast<int>((n_in + kBinPerBlock - 1) / kBinPerBlock) : 0;
     {
         ProfScope prof("conv_fprep", st);
-        const unsigned blocks = static_cast<unsigned>(n_sort + n_bin + weight_tiles(g));
-        const int lds = std::max(n_sort > 0 ? conv_sort_lds_bytes(C.M, g) : 0, kWtLdsBytes);
+        const unsigned blocks = static_cast<unsigned>(n_sort + n_bin + n_ev + weight_tiles(g));
+        const int lds = std::max({n_sort > 0 ? conv_sort_lds_bytes(C.M, g) : 0, kWtLdsBytes,
+                                  n_ev > 0 ? events_stage_floats(g) * static_cast<int>(sizeof(float)) : 0});
         if (bf16)
             hipLaunchKernelGGL(conv_fprep_kernel<uint16_t>, dim3(blocks), dim3(256), lds, st, C, g,
-                               n_sort, n_bin, n_in, t_in, cs, ev, static_cast<const uint16_t *>(W), Wt);
+                               n_sort, n_bin, n_ev, n_in, t_in, cs, ev, static_cast<const uint16_t *>(W),
+                               Wt);
         else
             hipLaunchKernelGGL(conv_fprep_kernel<float>, dim3(blocks), dim3(256), lds, st, C, g,
-                               n_sort, n_bin, n_in, t_in, cs, ev, static_cast<const float *>(W), Wt);
+                               n_sort, n_bin, n_ev, n_in, t_in, cs, ev, static_cast<const float *>(W), Wt);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1976,36 +1973,61 @@ hipError_t launch_conv_forward(const LifConst &C, const ConvGeom &g, int64_t B, 
     return hipGetLastError();
 }
 
-// channel tile: 32 for narrow layers or where two 64-wide G buffers would
-// pass 48 KB of LDS
-static int conv_dw_ti(const ConvGeom &g, int M) {
-    if (g.C_out <= 32) return 32;
-    return (2 * (M + 4) * 65 * 4 <= 48 * 1024) ? 64 : 32;
-}
+// The shape of the backward contraction. KWT = 3 taps per wave for kernels
+// wider than 1 at stride 1 (a 5- or 7-wide kernel row takes 2 or 3 such groups),
+// as far as its four G tables of 64 channels fit kBackLds; else 1.
+// NT = 2 channels per lane for layers of more than 64, where those fit too.
+// KWT NT TJ = 48 pairs per lane (32 with one tap): their sums and weights take
+// two thirds of the 168 registers that three waves per SIMD leave; 8 inputs per
+// wave where a tap has no more. Blocks of up to 12 waves, evenly filled (the
+// more inputs share a position's table the better), and splits of the output
+// rows for two blocks and 16 waves per CU, with >= 16 positions per split and bounded
+// partial sums: 64 MiB, and 1024 pieces of 256 (tap, input) rows x 64 channels
+// (32 for narrow layers and long grids).
+constexpr int kBackLds = 152 * 1024;
 
-static int conv_dw_nper(int M, int ti) {
-    const int need = ((M + 3) * ti + 255) / 256;
-    for (int n : {5, 9, 17, 33}) if (need <= n) return n;
-    return -1;
-}
-
-ConvDwPlan plan_conv_dw(const ConvGeom &g, int64_t B, int M) {
-    ConvDwPlan p;
-    p.ti = conv_dw_ti(g, M);
-    const int64_t nj = static_cast<int64_t>(g.KH) * g.KW * g.C_in;
-    const int64_t n_samp = B * g.Ho * g.Wo;
-    const int64_t tiles = ((nj + 255) / 256) * ((g.C_out + p.ti - 1) / p.ti);
-    const int64_t nw = nj * g.C_out;
+ConvBackPlan plan_conv_back(const ConvGeom &g, int64_t B, int M) {
+    ConvBackPlan p;
+    const int tab = g_table_len(M) * static_cast<int>(sizeof(float2));
+    auto lds = [&](int kwt, int nt) {
+        return back_ring(kwt) * (M + 3) * nt * kWave * 4 + tab;
+    };
+    p.kwt = (g.KW > 1 && g.stride == 1 && lds(3, 1) <= kBackLds) ? 3 : 1;
+    p.nt = (g.C_out > kWave && lds(p.kwt, 2) <= kBackLds) ? 2 : 1;
+    p.tj = (g.C_in <= 8 || (p.kwt == 3 && p.nt == 2)) ? 8 : 16;
+    if (p.kwt == 1 && p.nt == 2) p.tj = 16;
+    p.kg = (g.KW + p.kwt - 1) / p.kwt;
+    p.tiles = (g.C_out + p.nt * kWave - 1) / (p.nt * kWave);
+    // dt_in entries per input: at most KH * KW + 1 at a time
+    p.tiles_dt = std::min(p.tiles, (g.KH * g.KW + 1) / (g.KH * p.kg));
+    p.cpt = (g.C_in + p.tj - 1) / p.tj;
+    p.n_chunk = p.cpt * g.KH * p.kg;
+    p.groups = (p.n_chunk + kBackWaves - 1) / kBackWaves;
+    p.waves = (p.n_chunk + p.groups - 1) / p.groups;
+    const int64_t nw = static_cast<int64_t>(g.KH) * g.KW * g.C_in * g.C_out;
+    const int64_t n_rows = B * g.Ho, n_samp = n_rows * g.Wo;
+    const int64_t pieces = ((nw / g.C_out + 255) / 256) *
+                           ((g.C_out <= 32 || M > 90) ? (g.C_out + 31) / 32 : (g.C_out + 63) / 64);
     int64_t ns = 1;
-    // >= 4 blocks per CU, >= 16 samples per split and <= 64 MiB of partial
-    // sums; in any case at most kConvMaxSplitSamples samples per split (the
-    // block's live list)
-    while ((tiles * ns < 1024 && n_samp / (ns * 2) >= 16 && ns * 2 * nw * 4 <= (64 << 20)) ||
-           (n_samp + ns - 1) / ns > kConvMaxSplitSamples)
+    const int64_t blocks = static_cast<int64_t>(p.groups) * p.tiles;
+    while ((blocks * ns < 512 || blocks * ns * p.waves < 4096) && ns * 2 <= n_rows &&
+           n_samp / (ns * 2) >= 16 && pieces * ns < 1024 && ns * 2 * nw * 4 <= (64 << 20))
         ns *= 2;
-    p.s_per_split = static_cast<int>(std::max<int64_t>(1, (n_samp + ns - 1) / ns));
-    p.nsplit = static_cast<int>(std::max<int64_t>(1, (n_samp + p.s_per_split - 1) / p.s_per_split));
+    p.rows_per_split = static_cast<int>(std::max<int64_t>(1, (n_rows + ns - 1) / ns));
+    p.nsplit = static_cast<int>(std::max<int64_t>(1, (n_rows + p.rows_per_split - 1) / p.rows_per_split));
+    p.lds = static_cast<size_t>(lds(p.kwt, p.nt));
     return p;
+}
+
+template <int KWT, int NT, int TJ>
+static void launch_back(const LifConst &C, const ConvGeom &g, const ConvBackArgs &a,
+                        const ConvBackPlan &p, int tiles, bool dw, bool dt, hipStream_t st) {
+    const dim3 grid(static_cast<unsigned>(p.groups), static_cast<unsigned>(p.nsplit),
+                    static_cast<unsigned>(tiles));
+    const dim3 block(static_cast<unsigned>(p.waves * kWave));
+    if (dw && dt) hipLaunchKernelGGL((conv_back_kernel<KWT, NT, TJ, true, true>), grid, block, p.lds, st, C, g, a);
+    else if (dw) hipLaunchKernelGGL((conv_back_kernel<KWT, NT, TJ, true, false>), grid, block, p.lds, st, C, g, a);
+    else hipLaunchKernelGGL((conv_back_kernel<KWT, NT, TJ, false, true>), grid, block, p.lds, st, C, g, a);
 }
 
 hipError_t launch_conv_backward(const LifConst &C, const ConvGeom &g, int64_t B, const void *W,
@@ -2013,16 +2035,15 @@ hipError_t launch_conv_backward(const LifConst &C, const ConvGeom &g, int64_t B,
                                 const float *slope, const int *q_idx, const float *grad_t,
                                 ConvBwdWs ws, float *grad_W, float *grad_t_in, const Synfire &sf,
                                 bool reuse, hipStream_t st) {
-    const int R = C.M + 3;
     const int64_t n_in = B * g.Hp * g.Wp * g.PC;
     const int64_t n_pos = B * g.Ho * g.Wo;
     const int64_t nj = static_cast<int64_t>(g.KH) * g.KW * g.C_in;
     const bool dt = grad_t_in && n_in > 0;
     hipError_t e;
     {
-        // cell rows (events; with dt_in the sort), gradient triples +
-        // gradient rows, and the WT layout for dt_in: one launch (with a
-        // kept forward sort only the gradient roles)
+        // cell rows' events, gradient triples + gradient rows, and the WT
+        // layout for dt_in: one launch (after a keeping forward only the
+        // gradient roles)
         const int n_cr = (!reuse && n_in > 0 && (grad_W || dt)) ? static_cast<int>(B * g.Hp) : 0;
         const int n_gr = static_cast<int>((n_pos + kGradPos - 1) / kGradPos) *
                          ((g.C_out + kGradCh - 1) / kGradCh);
@@ -2030,124 +2051,46 @@ hipError_t launch_conv_backward(const LifConst &C, const ConvGeom &g, int64_t B,
         // dead-neuron terms only where dW is written
         const bool dead = sf.on && sf.dq && grad_W;
         const int n_dq = dead ? g.C_out : 0;
-        const CellEv ev{grad_W ? ws.row : nullptr, ws.L, ws.R, ws.crlive};
-        ConvSorted cs = ws.srt;
-        cs.L = cs.R = nullptr;  // the backward sort writes derivatives only
-        if (!dt) cs.key = nullptr;
-        int lds = std::max(kGradLdsBytes, 256 * static_cast<int>(sizeof(int)));
-        if (dt) lds = std::max(lds, conv_sort_lds_bytes(C.M, g));
+        const int lds = std::max({kGradLdsBytes, 256 * static_cast<int>(sizeof(int)),
+                                  n_cr > 0 ? events_stage_floats(g) * static_cast<int>(sizeof(float)) : 0});
         const unsigned blocks = static_cast<unsigned>(n_cr + n_gr + n_dq + n_wt);
         ProfScope prof("conv_bprep", st);
         if (blocks > 0) {
             if (bf16)
                 hipLaunchKernelGGL(conv_bprep_kernel<uint16_t>, dim3(blocks), dim3(256), lds, st, C,
-                                   g, n_cr, n_gr, n_dq, t_in, cs, ev, n_pos, t_out, slope,
-                                   q_idx, grad_t, sf, ws.gam, ws.uq, ws.q, ws.rend,
+                                   g, n_cr, n_gr, n_dq, t_in, ws.ev, n_pos, t_out, slope,
+                                   q_idx, grad_t, sf, ws.tri, ws.rend,
                                    static_cast<const uint16_t *>(W), ws.wt);
             else
                 hipLaunchKernelGGL(conv_bprep_kernel<float>, dim3(blocks), dim3(256), lds, st, C,
-                                   g, n_cr, n_gr, n_dq, t_in, cs, ev, n_pos, t_out, slope,
-                                   q_idx, grad_t, sf, ws.gam, ws.uq, ws.q, ws.rend,
+                                   g, n_cr, n_gr, n_dq, t_in, ws.ev, n_pos, t_out, slope,
+                                   q_idx, grad_t, sf, ws.tri, ws.rend,
                                    static_cast<const float *>(W), ws.wt);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    ConvDwPlan p{};
-    ConvDwArgs da{n_pos, 0, ws.gam, ws.uq, ws.q, ws.rend, ws.crlive, ws.row, ws.L, ws.R,
-                  ws.part, ws.zlive};
-    dim3 dw_grid(1, 1, 1);
-    size_t dw_lds = 0;
-    int nper = 0;
-    if (grad_W) {
-        p = plan_conv_dw(g, B, C.M);
-        da.s_per_split = p.s_per_split;
-        dw_grid = dim3(static_cast<unsigned>((nj + 255) / 256),
-                       static_cast<unsigned>((g.C_out + p.ti - 1) / p.ti),
-                       static_cast<unsigned>(p.nsplit));
-        dw_lds = 2 * static_cast<size_t>(R + 1) * (p.ti + 1) * sizeof(float) +
-                 static_cast<size_t>(p.s_per_split) * sizeof(int);
-        nper = conv_dw_nper(C.M, p.ti);
-    }
+    const ConvBackPlan p = plan_conv_back(g, B, C.M);
     const bool dtl = dt && n_pos > 0;
-    constexpr int kDtWaves = 4;  // dt_in partial blocks: four positions each
-    const int64_t n_dtp = dtl ? (n_pos + kDtWaves - 1) / kDtWaves : 0;
-    const int nt = (g.C_out + kWave - 1) / kWave;
-    const int nt_k = nt == 1 ? 1 : nt == 2 ? 2 : nt <= 4 ? 4 : 8;
-    const int kh_k = g.KH == 1 ? 1 : g.KH <= 3 ? 3 : kConvMaxK;
-    // dW and the dt_in partials in one launch where both run (general
-    // kernel row, the tile shapes instantiated below); else one launch each
-    bool fused = false;
-    if (grad_W && dtl && C.kind == kGeneral) {
-        const int64_t n_dw = static_cast<int64_t>(dw_grid.x) * dw_grid.y * dw_grid.z;
-        if (n_dw + n_dtp < (int64_t{1} << 31)) {
-            const dim3 grid(static_cast<unsigned>(n_dw + n_dtp));
-            const int nbx = static_cast<int>(dw_grid.x), nby = static_cast<int>(dw_grid.y);
-            ProfScope prof("conv_dwdt", st);
-#define DWDT(TIV, NPV, KHV, NTV)                                                                \
-    if (!fused && p.ti == TIV && nper == NPV && kh_k == KHV && nt_k == NTV) {                   \
-        hipLaunchKernelGGL((conv_dwdt_kernel<TIV, NPV, KHV, NTV, kGeneral>), grid, dim3(256),   \
-                           dw_lds, st, C, g, da, nbx, nby, static_cast<int>(n_dw), n_pos, ws.wt, \
-                           ws.srt);                                                             \
-        fused = true;                                                                           \
-    }
-            DWDT(32, 5, 1, 1) DWDT(32, 5, 3, 1)
-            DWDT(64, 5, 1, 1) DWDT(64, 5, 1, 2) DWDT(64, 5, 1, 4)
-            DWDT(64, 5, 3, 1) DWDT(64, 5, 3, 2) DWDT(64, 5, 3, 4)
-            DWDT(64, 9, 1, 1) DWDT(64, 9, 1, 2) DWDT(64, 9, 1, 4)
-            DWDT(64, 9, 3, 1) DWDT(64, 9, 3, 2) DWDT(64, 9, 3, 4)
-#undef DWDT
+    if (grad_W || dtl) {
+        ConvBackArgs a{static_cast<int>(B * g.Ho), p.rows_per_split, p.cpt, p.n_chunk, p.kg, 0, 0, 0,
+                       ws.tri, ws.rend, ws.ev.live, ws.ev.ev, ws.wt, ws.P, ws.part,
+                       ws.zlive};
+        ProfScope prof("conv_back", st);
+        const int step = dtl ? p.tiles_dt : p.tiles;
+        a.n_tile = step;
+        for (int t = 0; t < p.tiles; t += step) {
+            a.tile0 = t;
+            a.add = t > 0;
+            const int nt = std::min(step, p.tiles - t);
+            const bool dw = grad_W != nullptr;
+            if (p.kwt == 3 && p.nt == 2) launch_back<3, 2, 8>(C, g, a, p, nt, dw, dtl, st);
+            else if (p.kwt == 3 && p.tj == 16) launch_back<3, 1, 16>(C, g, a, p, nt, dw, dtl, st);
+            else if (p.kwt == 3) launch_back<3, 1, 8>(C, g, a, p, nt, dw, dtl, st);
+            else if (p.nt == 2) launch_back<1, 2, 16>(C, g, a, p, nt, dw, dtl, st);
+            else if (p.tj == 16) launch_back<1, 1, 16>(C, g, a, p, nt, dw, dtl, st);
+            else launch_back<1, 1, 8>(C, g, a, p, nt, dw, dtl, st);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-    }
-    if (grad_W && !fused) {
-        ProfScope prof("conv_dw", st);
-#define CDW_LAUNCH_K(TIV, NP, KSV) \
-    hipLaunchKernelGGL((conv_dw_kernel<TIV, NP, KSV>), dw_grid, dim3(256), dw_lds, st, C, g, da)
-#define CDW_LAUNCH(TIV, NP)                                               \
-    do {                                                                  \
-        if (C.kind == kGeneral) CDW_LAUNCH_K(TIV, NP, kGeneral);          \
-        else CDW_LAUNCH_K(TIV, NP, kAnyKind);                             \
-    } while (0)
-        if (p.ti == 64) {
-            if (nper == 5) CDW_LAUNCH(64, 5);
-            else if (nper == 9) CDW_LAUNCH(64, 9);
-            else if (nper == 17) CDW_LAUNCH(64, 17);
-            else CDW_LAUNCH(64, 33);
-        } else {
-            if (nper == 5) CDW_LAUNCH(32, 5);
-            else if (nper == 9) CDW_LAUNCH(32, 9);
-            else if (nper == 17) CDW_LAUNCH(32, 17);
-            else CDW_LAUNCH(32, 33);
-        }
-#undef CDW_LAUNCH
-#undef CDW_LAUNCH_K
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (dtl && !fused) {
-        dim3 grid(static_cast<unsigned>(n_dtp));
-        ProfScope prof("conv_dtp", st);
-#define DTP_LAUNCH_K(KHV, NTV, KSV)                                                           \
-    hipLaunchKernelGGL((conv_dtp_kernel<KHV, NTV, KSV>), grid, dim3(kDtWaves * kWave), 0, st,  \
-                       C, g, n_pos, ws.wt, ws.srt, ws.gam, ws.uq, ws.q, ws.rend)
-#define DTP_LAUNCH(KHV, NTV)                                              \
-    do {                                                                  \
-        if (C.kind == kGeneral) DTP_LAUNCH_K(KHV, NTV, kGeneral);         \
-        else DTP_LAUNCH_K(KHV, NTV, kAnyKind);                            \
-    } while (0)
-#define DTP_NT(KHV)                               \
-    do {                                          \
-        if (nt_k == 1) DTP_LAUNCH(KHV, 1);        \
-        else if (nt_k == 2) DTP_LAUNCH(KHV, 2);   \
-        else if (nt_k == 4) DTP_LAUNCH(KHV, 4);   \
-        else DTP_LAUNCH(KHV, 8);                  \
-    } while (0)
-        if (kh_k == 1) DTP_NT(1);
-        else if (kh_k == 3) DTP_NT(3);
-        else DTP_NT(kConvMaxK);
-#undef DTP_NT
-#undef DTP_LAUNCH
-#undef DTP_LAUNCH_K
-        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     {
         // dW split reduction and dt_in gather: one launch
@@ -2162,8 +2105,9 @@ hipError_t launch_conv_backward(const LifConst &C, const ConvGeom &g, int64_t B,
         ProfScope prof("conv_bfin", st);
         if (n_red + n_ga > 0)
             hipLaunchKernelGGL(conv_bfin_kernel, dim3(static_cast<unsigned>(n_red + n_ga)),
-                               dim3(256), 0, st, g, R, n_red, p.nsplit, ws.part, ws.zlive,
-                               (sf.on && sf.dq) ? sf.dq : nullptr, grad_W, nsl, ws.srt, ws.rend,
+                               dim3(256), 0, st, g, n_red, p.nsplit, ws.part, ws.zlive,
+                               (sf.on && sf.dq) ? sf.dq : nullptr, grad_W, nsl,
+                               ConvGatherArgs{ws.ev.live, ws.rend, ws.P, p.kwt, p.kg, p.tiles_dt},
                                grad_t_in);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

@@ -75,6 +75,7 @@ struct ConvGeom {
     float inv_P;
     FastDiv dv_pch, dv_w, dv_cin;  // by Wp * P (raw inputs per channel of a cell row), W, C_in
     FastDiv dv_p, dv_kw, dv_pc;    // by P, KW (receptive-field decode) and PC
+    FastDiv dv_howo, dv_wo;        // by Ho * Wo and Wo (output position decode)
 };
 
 inline FastDiv fast_div(uint32_t d) {
@@ -101,59 +102,51 @@ __host__ __device__ __forceinline__ int conv_off_stride(int R, const ConvGeom &g
 // r] (cr = b*Hp + py, noff = conv_off_stride), so that lanes = event rows
 // read one column contiguously; column px = Wp holds the end of each row r
 // (the start of (r + 1, 0)), and the last entry the row's record count.
-// The forward sort writes the event weights L, R; the backward sort (or a
-// forward that keeps its sort for the backward) writes the record's event
-// row and cell column (px = row << 16 | cell column), its input index in the
-// cell row (src = px * PC + j') and the event derivatives dL, dR. Unused
-// arrays are NULL. P[record][KH*KW] holds the per-tap partial sums of dt_in:
-// the entry of tap k is written by the output position that reads the record
-// through k, and only where that position passes gradient up to the record's
-// event row (rend); the gather reads exactly those entries.
-struct ConvSorted {
-    int *key; float *L; float *R; int *off; int *px; int *src; float *P; float *dL; float *dR;
-};
+struct ConvSorted { int *key; float *L; float *R; int *off; };
 
-// Cell-major events of every input (row -1: no events) for the dW reduction,
-// written only for cell rows where some input has events; live[cr] says which
-// (the dW kernel reads no others). NULL row: not wanted.
-struct CellEv { int *row; float *L, *R; int *live; };
+// Cell-major events of every input for the backward: ev[cell][d][field][ci],
+// fields row (int bits; -1: no events), L, R, dL, dR (values only where the row
+// is >= 0), so the events of neighbouring channels of one raw pixel are five
+// contiguous runs from one address. Written only for cell rows where some input
+// has events; live[cr] says which (nothing is read of the others). NULL ev: not
+// wanted.
+struct CellEv { float *ev; int *live; };
 
 struct ConvBwdWs {
-    int *row;
-    float *L, *R;            // cell-major events (dW), for cell rows with events; L, R
-                             //   hold values only where row >= 0
-    int *crlive;             // [B][Hp]: the cell row has an input with events
-    float *gam, *uq;         // per output neuron, [B][Ho*Wo][C_out]: -g/slope, t - T_q
-    int *q;                  //   and its interval (-1: no gradient flows)
-    int *rend;               // [B][Ho*Wo]: last event row whose records get gradient
+    CellEv ev;               // [B * Hp * Wp][P][5][C_in], live [B][Hp]
+    float *tri;              // gradient triples (grad_triple; q as int bits), per output
+                             //   position: [B][Ho*Wo][3][C_out] (q -1: no gradient flows)
+    int *rend;               // [B][Ho*Wo]: last event row whose inputs get gradient
                              //   there (min(R-2, max q + 1) over channels; -1: none)
+    float *P;                // dt_in partials [cell][entry][PC], entry = (kernel row,
+                             //   tap group, channel tile), see conv_back_kernel
     float *part;             // dW partial sums [nsplit][C_out][KH*KW*C_in]
     int *zlive;              // [nsplit]: 1 if the split has samples that pass
                              //   gradient (its partials are written only then)
     float *wt;               // [KH*KW*C_in][C_out] weights / P (as the forward)
-    ConvSorted srt;          // records sorted as in the forward, with dL, dR
 };
 
-// largest C_out the dt_in kernel handles (channel tiles of 64 per lane)
+// largest C_out for which dt_in is computed
 constexpr int kConvMaxCoutDt = 512;
 
-struct ConvDwPlan { int ti, nsplit, s_per_split; };
-constexpr int kConvMaxSplitSamples = 4096;  // (b, position) samples per dW block
+// Shape of one conv layer's backward contraction: taps and input channels per
+// wave, channels per lane, tap groups per kernel row, channel tiles (and how many
+// of them per dt_in launch), chunks per tap group and in all, blocks over the
+// chunks (groups) of `waves` waves, splits of the output rows, dynamic LDS bytes.
+struct ConvBackPlan {
+    int kwt, nt, tj, kg, tiles, tiles_dt, cpt, n_chunk, groups, waves, nsplit, rows_per_split;
+    size_t lds;
+};
 
-// the dt_in kernel's LDS row stride (words); odd, so rows r and r+1 of one
-// lane fall in different banks
-constexpr int kDtStride = kWave + 1;
-
-ConvDwPlan plan_conv_dw(const ConvGeom &g, int64_t B, int M);
+ConvBackPlan plan_conv_back(const ConvGeom &g, int64_t B, int M);
 int conv_sort_lds_bytes(int M, const ConvGeom &g);
-// keep (cs.dL and ev set): the sort also writes what the backward needs
-// (derivatives, px, src, cell-major events), even where the walk bins its
-// inputs itself.
+// keep (ev set): the set-up also writes the cell-major events the backward
+// needs.
 hipError_t launch_conv_forward(const LifConst &C, const ConvGeom &g, int64_t B, const void *W,
                                bool bf16, float *Wt, ConvSorted cs, CellEv ev, const float *t_in,
                                float *t_out, float *slope, int *q_idx, hipStream_t st);
-// reuse: the workspace holds a kept forward sort (records, events, weight
-// layout) for these inputs and weights: no cell-row or weight-layout work.
+// reuse: the workspace holds a keeping forward's events and weight layout for
+// these inputs and weights: no cell-row or weight-layout work.
 hipError_t launch_conv_backward(const LifConst &C, const ConvGeom &g, int64_t B, const void *W,
                                 bool bf16, const float *t_in, const float *t_out,
                                 const float *slope, const int *q_idx, const float *grad_t,
