@@ -187,17 +187,34 @@ dstd_status check_dims(int64_t B, int64_t N_in, int64_t N_out) {
 }
 
 struct DenseWs {
-    size_t row, L, R, gam, uq, q, part, dq, wt, sj, sr, sL, sR, nvalid, rs, total;
+    size_t ev, tri, P, part, dq, wt, sj, sr, sL, sR, nvalid, rs, total;
     int64_t sstride;
+    int n_buf;
 };
 
 DenseWs dense_ws_layout(int M, int64_t B, int64_t N_in, int64_t N_out, bool backward) {
     DenseWs w{};
     size_t off = 0;
     size_t n = (size_t)(B * N_in);
-    if (!backward && B * N_out == 0) return w;  // the forward enqueues nothing
+    if (backward) {
+        // events, gradient triples, dt_in buffers (as many as the neuron tiles
+        // can use, at most 2 + N_out / B: about the weights' size), dW partials
+        const dstd::BackPlan dp =
+            dstd::plan_back(B, N_in, N_out, 1, M, dstd::back_split_cap(B, N_in, N_out, M));
+        w.ev = off; off += align_up(n * 5 * sizeof(float));
+        w.tri = off; off += align_up((size_t)B * (size_t)N_out * 3 * sizeof(float));
+        w.n_buf = (int)std::max<int64_t>(
+            0, std::min<int64_t>(dp.tiles - 1, 2 + N_out / std::max<int64_t>(B, 1)));
+        w.P = off; off += align_up(n * (size_t)w.n_buf * sizeof(float));
+        w.dq = off; off += align_up((size_t)N_out * sizeof(float));  // dead-neuron term per row
+        w.part = off;
+        if (dp.nsplit > 1) off += align_up((size_t)dp.nsplit * (size_t)N_out * (size_t)N_in * sizeof(float));
+        w.total = off;
+        return w;
+    }
+    if (B * N_out == 0) return w;  // the forward enqueues nothing
     // transposed weights (room for fp32) and the row-sorted event records of
-    // every sample: both passes walk them (the backward for dt_in)
+    // every sample
     w.wt = off; off += align_up((size_t)N_in * (size_t)N_out * sizeof(float));
     // sorted event lists: per sample N_in records; the last sample's list
     // is padded so batched reads past its end stay in the allocation
@@ -209,19 +226,6 @@ DenseWs dense_ws_layout(int M, int64_t B, int64_t N_in, int64_t N_out, bool back
     w.sR = off; off += align_up(ns * sizeof(float));
     w.nvalid = off; off += align_up((size_t)B * sizeof(int));
     w.rs = off; off += align_up((size_t)B * (M + 4) * sizeof(int));
-    if (backward) {
-        // per-input events for the dW reduction, gradient triples, dW partials
-        w.row = off; off += align_up(n * sizeof(int));
-        w.L = off; off += align_up(n * sizeof(float));
-        w.R = off; off += align_up(n * sizeof(float));
-        w.gam = off; off += align_up((size_t)B * (size_t)N_out * sizeof(float));
-        w.uq = off; off += align_up((size_t)B * (size_t)N_out * sizeof(float));
-        w.q = off; off += align_up((size_t)B * (size_t)N_out * sizeof(int));
-        w.dq = off; off += align_up((size_t)N_out * sizeof(float));  // dead-neuron term per row
-        dstd::DwPlan dp = dstd::plan_dw(B, N_in, N_out, M);
-        w.part = off;
-        if (dp.nsplit > 1) off += align_up((size_t)dp.nsplit * (size_t)N_out * (size_t)N_in * sizeof(float));
-    }
     w.total = off;
     return w;
 }
@@ -292,8 +296,6 @@ dstd_status check_conv(const dstd_conv_shape *cs, int64_t B, int M, dstd::ConvGe
     G.dv_p = dstd::fast_div((uint32_t)G.P);
     G.dv_kw = dstd::fast_div((uint32_t)G.KW);
     G.dv_pc = dstd::fast_div((uint32_t)G.PC);
-    G.dv_howo = dstd::fast_div((uint32_t)(G.Ho * G.Wo));
-    G.dv_wo = dstd::fast_div((uint32_t)G.Wo);
     return DSTD_OK;
 }
 
@@ -553,22 +555,15 @@ dstd_status dense_backward(const dstd_lif_params *p, const dstd_synfire_params *
     if ((s = check_ws(ws, ws_bytes, L.total)) != DSTD_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
-    // Empty sizes need no special case: with B == 0 the dW kernel writes
-    // zeros; dt_in is zeroed by the event sort and only inputs with events
-    // are written after that (no memset is used, so the call stays safe to
-    // capture in a graph).
+    // Empty sizes need no special case: with B == 0 the contraction writes zeros
+    // to dW, and without neurons to dt_in (no memset is used, so the call stays
+    // safe to capture in a graph).
     LifConst C = make_const(p);
     dstd::DenseBwdWs bw;
-    bw.row = at<int>(ws, L.row);
-    bw.L = at<float>(ws, L.L);
-    bw.R = at<float>(ws, L.R);
-    bw.srt = dstd::SortedEv{at<int>(ws, L.sj), at<int>(ws, L.sr), at<float>(ws, L.sL),
-                            at<float>(ws, L.sR), L.sstride, at<int>(ws, L.rs)};
-    bw.n_valid = at<int>(ws, L.nvalid);
-    bw.wt = at<void>(ws, L.wt);
-    bw.gam = at<float>(ws, L.gam);
-    bw.uq = at<float>(ws, L.uq);
-    bw.q = at<int>(ws, L.q);
+    bw.ev = at<float>(ws, L.ev);
+    bw.tri = at<float>(ws, L.tri);
+    bw.P = at<float>(ws, L.P);
+    bw.n_buf = L.n_buf;
     bw.part = at<float>(ws, L.part);
     e = dstd::launch_backward(C, B, N_in, N_out, W, w_dtype == DSTD_BF16, t_in, t_out, slope,
                               q_idx, grad_t_out, bw, grad_W, grad_t_in,
@@ -934,24 +929,27 @@ dstd_status check_ms(const dstd_lif_params *p, int64_t B, int64_t N_in, int64_t 
     return DSTD_OK;
 }
 
-struct MsWs { size_t row, L, R, dL, dR, wt, G, part, sj, sr, sL, sR, nvalid, rs, total; };
+struct MsWs {
+    size_t ev, wt, G, P, part, sj, sr, sL, sR, nvalid, rs, total;
+    int n_buf;
+};
 
 // forward: the records of every input spike sorted by event row (as the TTFS
-// forward's lists) and W^T; backward: per-spike events, W^T and G
+// forward's lists) and W^T; backward: per-spike events, G, dW partials and
+// dt_in buffers
 MsWs ms_ws_layout(int M, int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, bool backward) {
     MsWs w{};
     size_t off = 0;
     const size_t n = (size_t)(B * N_in * F_in);
     if (backward) {
-        w.row = off; off += align_up(n * sizeof(int));
-        w.L = off; off += align_up(n * sizeof(float));
-        w.R = off; off += align_up(n * sizeof(float));
-        w.dL = off; off += align_up(n * sizeof(float));
-        w.dR = off; off += align_up(n * sizeof(float));
+        w.ev = off; off += align_up(n * 5 * sizeof(float));
         w.G = off; off += align_up((size_t)B * (size_t)(M + 1) * (size_t)N_out * sizeof(float));
-        const int S = dstd::ms_dw_splits(M, B, N_in, N_out);
+        int64_t n_buf;
+        const dstd::BackPlan mp = dstd::plan_ms_back(B, N_in, F_in, N_out, M, &n_buf);
+        w.n_buf = (int)n_buf;
         w.part = off;
-        if (S > 1) off += align_up((size_t)S * (size_t)N_in * (size_t)N_out * sizeof(float));
+        w.P = off + (mp.nsplit > 1 ? (size_t)mp.nsplit * (size_t)N_in * (size_t)N_out * sizeof(float) : 0);
+        off += align_up(w.P - w.part + n * (size_t)n_buf * sizeof(float));
     } else {
         const size_t ns = n + dstd::kSortPad;
         w.sj = off; off += align_up(ns * sizeof(int));
@@ -960,8 +958,8 @@ MsWs ms_ws_layout(int M, int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, b
         w.sR = off; off += align_up(ns * sizeof(float));
         w.nvalid = off; off += align_up((size_t)B * sizeof(int));
         w.rs = off; off += align_up((size_t)B * (M + 4) * sizeof(int));
+        w.wt = off; off += align_up((size_t)N_in * (size_t)N_out * sizeof(float));
     }
-    w.wt = off; off += align_up((size_t)N_in * (size_t)N_out * sizeof(float));
     w.total = off;
     return w;
 }
@@ -1030,16 +1028,13 @@ dstd_status dstd_lif_multispike_backward(const dstd_lif_params *p, int64_t B, in
     MsWs L = ms_ws_layout(p->M, B, N_in, F_in, N_out, true);
     if ((s = check_ws(ws, ws_bytes, L.total)) != DSTD_OK) return s;
     LifConst C = make_const(p);
-    dstd::MsEvents ev{at<int>(ws, L.row), at<float>(ws, L.L), at<float>(ws, L.R),
-                      at<float>(ws, L.dL), at<float>(ws, L.dR)};
-    // B == 0: the dW kernel still runs and writes zeros; N_out == 0: dt_in
-    // sums nothing and writes zeros
-    hipError_t e = dstd::launch_ms_backward(C, B, N_in, F_in, N_out, F_out, W,
-                                            w_dtype == DSTD_BF16, at<void>(ws, L.wt), ev, t_in,
-                                            t_out, slope, q_idx, cur, grad_t_out,
-                                            at<float>(ws, L.G), at<float>(ws, L.part), grad_W,
-                                            grad_t_in,
-                                            static_cast<hipStream_t>(stream));
+    const dstd::DenseBwdWs bw{at<float>(ws, L.ev), at<float>(ws, L.G), at<float>(ws, L.P),
+                              at<float>(ws, L.part), L.n_buf};
+    // B == 0: the contraction still runs and writes zeros to dW; N_out == 0:
+    // dt_in sums nothing and is zeros
+    hipError_t e = dstd::launch_ms_backward(C, B, N_in, F_in, N_out, F_out, W, w_dtype == DSTD_BF16,
+                                            bw, t_in, t_out, slope, q_idx, cur, grad_t_out, grad_W,
+                                            grad_t_in, static_cast<hipStream_t>(stream));
     return hip_status(e, "multi-spike backward launch");
 }
 

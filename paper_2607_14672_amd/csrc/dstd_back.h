@@ -5,9 +5,11 @@
 // an output position of one) lives in LDS as a table of rows r = m + 1, lanes
 // = neurons. A wave owns some inputs and NT neurons per lane; the dW sums and
 // the weights of those pairs stay in its registers over all samples of the
-// block. An input's event (row, L, R, dL, dR) is the same for every lane:
-// one or two vector loads bring a wave's events, a sample ahead, with lanes =
-// (field, input); an active input's fields then come as scalars by readlane.
+// block. An input's event (row, L, R, dL, dR) is the same for every lane: a
+// few vector loads bring a wave's events, an item ahead, with 16 lanes = inputs
+// of one field; an active input's fields are row_newbcast operands of the
+// instructions that use them (read into scalars first, an input took five more
+// instructions: 5 % of the whole pass at 4096 -> 4096).
 //   - An input without events, or whose row lies past the last spike that
 //     passes gradient, costs one scalar branch (the causal half of the pairs
 //     and the silent inputs are never multiplied);
@@ -114,11 +116,13 @@ __device__ __forceinline__ void settle(float &x) { asm volatile("" : "+v"(x)); }
 
 __device__ __forceinline__ void opaque(unsigned &x) { asm volatile("" : "+s"(x)); }
 
-// A wave's events of one item: with TJ inputs, lane f TJ + k of the registers
-// e[0], e[1], ... holds field f of input k (row as int bits, L, R, dL, dR).
+// A wave's events of one item: lane l of register e[h] holds x = 16 h + l % 16,
+// field x / TJ (row as int bits, L, R, dL, dR) of input x % TJ, so that an
+// input's field reaches every lane as the row_newbcast operand of the
+// instruction that uses it.
 constexpr int kBackGroup = 8;
 constexpr int kEvFields = 5;
-template <int TJ> constexpr int ev_regs() { return (kEvFields * TJ + kWave - 1) / kWave; }
+template <int TJ> constexpr int ev_regs() { return (kEvFields * TJ + 15) / 16; }
 template <int TJ> struct EvRegs { float e[ev_regs<TJ>()]; };
 
 // Offsets (floats) of a lane's events from the first input's row, the fields fs
@@ -129,7 +133,7 @@ template <int TJ> __device__ __forceinline__ EvOffs<TJ> ev_offs(int fs, int nj, 
     EvOffs<TJ> r;
 #pragma unroll
     for (int h = 0; h < ev_regs<TJ>(); ++h) {
-        const int x = h * kWave + lane;
+        const int x = h * 16 + (lane & 15);
         r.o[h] = static_cast<unsigned>(min(x / TJ, kEvFields - 1) * fs + min(x % TJ, nj - 1));
     }
     return r;
@@ -142,12 +146,47 @@ __device__ __forceinline__ EvRegs<TJ> ev_load(const float *p, const EvOffs<TJ> &
     for (int h = 0; h < ev_regs<TJ>(); ++h) r.e[h] = p[o.o[h]];
     return r;
 }
-template <int TJ> __device__ __forceinline__ int ev_bits(const EvRegs<TJ> &r, int f, int k) {
-    const int x = f * TJ + k;  // compile-time
-    return __builtin_amdgcn_readlane(__float_as_int(r.e[x / kWave]), x % kWave);
+// lane N of each 16 lanes, to all of them (every lane active)
+template <int N> __device__ __forceinline__ int row_bcast(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, 0x150 + N, 0xf, 0xf, true);  // row_newbcast:N
 }
-template <int TJ> __device__ __forceinline__ float ev_at(const EvRegs<TJ> &r, int f, int k) {
-    return __int_as_float(ev_bits<TJ>(r, f, k));
+template <int TJ> constexpr int ev_reg(int f, int k) { return (f * TJ + k) / 16; }
+template <int TJ> constexpr int ev_lane(int f, int k) { return (f * TJ + k) % 16; }
+
+// acc[c] += bcast(L) x[c] + bcast(R) y[c] from lanes NL and NR of each 16, the
+// broadcasts being operands of the multiply-adds (the compiler folds a row
+// broadcast into a product but leaves it a move of its own before a
+// multiply-add). s_nop: a register written by the vector ALU may be read as a
+// row broadcast two cycles later at the earliest.
+template <int NL, int NR, int NT>
+__device__ __forceinline__ void fma_bcast(float (&acc)[NT], float L, float R, const float (&x)[NT],
+                                          const float (&y)[NT]) {
+#define FB(d, e, s, n) "v_fmac_f32_dpp " d ", " e ", " s " row_newbcast:" n " row_mask:0xf bank_mask:0xf\n"
+    if constexpr (NT == 4)
+        asm("s_nop 1\n" FB("%0", "%5", "%11", "%15") FB("%1", "%5", "%12", "%15")
+                FB("%2", "%5", "%13", "%15") FB("%3", "%5", "%14", "%15") FB("%0", "%4", "%7", "%6")
+                    FB("%1", "%4", "%8", "%6") FB("%2", "%4", "%9", "%6") FB("%3", "%4", "%10", "%6")
+            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+            : "v"(L), "v"(R), "n"(NL), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(y[0]),
+              "v"(y[1]), "v"(y[2]), "v"(y[3]), "n"(NR));
+    else if constexpr (NT == 2)
+        asm("s_nop 1\n" FB("%0", "%3", "%7", "%9") FB("%1", "%3", "%8", "%9") FB("%0", "%2", "%5", "%4")
+                FB("%1", "%2", "%6", "%4")
+            : "+v"(acc[0]), "+v"(acc[1])
+            : "v"(L), "v"(R), "n"(NL), "v"(x[0]), "v"(x[1]), "v"(y[0]), "v"(y[1]), "n"(NR));
+    else
+        asm("s_nop 1\n" FB("%0", "%2", "%5", "%6") FB("%0", "%1", "%4", "%3")
+            : "+v"(acc[0])
+            : "v"(L), "v"(R), "n"(NL), "v"(x[0]), "v"(y[0]), "n"(NR));
+}
+// bcast(p) a + bcast(q) b
+template <int NP, int NQ>
+__device__ __forceinline__ float dot_bcast(float p, float q, float a, float b) {
+    float v;
+    asm("s_nop 1\nv_mul_f32_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n" FB("%0", "%1", "%3", "%5")
+        : "=&v"(v) : "v"(p), "v"(q), "v"(a), "v"(b), "n"(NP), "n"(NQ));
+#undef FB
+    return v;
 }
 
 // Inputs 8 G .. 8 G + 7 of a wave, act: bit k set where input k's row is in
@@ -162,16 +201,19 @@ __device__ __forceinline__ float back_group(const float *(&gl)[KW], int lane, un
                                             float (&acc)[kBackGroup][KW][NT]) {
     constexpr int kB = (NT * KW == 1) ? 8 : (NT * KW <= 3) ? 4 : 2;
     float v[kBackGroup];
+    // an input's row in the table, in bytes
+    const int row_at = __float_as_int(ev.e[0]) * (NT * kWave * 4);
     static_for<kBackGroup / kB>([&](auto h) {
         float g0[kB][KW][NT], g1[kB][KW][NT];
         opaque(act);  // tested bit by bit where it is used, no masks kept
         static_for<kB>([&](auto j) {
             constexpr int k = G * kBackGroup + h * kB + j;
             if (act & (1u << k)) {
-                const int o = ev_bits<TJ>(ev, 0, k) * (NT * kWave);
+                const int o = row_bcast<k>(row_at);
                 static_for<KW>([&](auto i) {
-                    lds_get<NT>(gl[i] + o, g0[j][i]);
-                    lds_get<NT>(gl[i] + o + NT * kWave, g1[j][i]);
+                    const float *q = reinterpret_cast<const float *>(reinterpret_cast<const char *>(gl[i]) + o);
+                    lds_get<NT>(q, g0[j][i]);
+                    lds_get<NT>(q + NT * kWave, g1[j][i]);
                 });
                 asm volatile("");
             }
@@ -182,22 +224,21 @@ __device__ __forceinline__ float back_group(const float *(&gl)[KW], int lane, un
             v[kl] = 0.f;
             if (act & (1u << k)) {
                 asm volatile("");
-                float a = 0.f, b = 0.f, L = 0.f, R = 0.f;
-                if constexpr (DW) {
-                    L = ev_at<TJ>(ev, 1, k);
-                    R = ev_at<TJ>(ev, 2, k);
-                }
+                float a = 0.f, b = 0.f;
                 static_for<KW>([&](auto i) {
-                    static_for<NT>([&](auto c) {
-                        const float x = g0[j][i][c], y = g1[j][i][c];
-                        if constexpr (DW) acc[kl][i][c] = fmaf(x, L, fmaf(y, R, acc[kl][i][c]));
-                        if constexpr (DT) {
+                    if constexpr (DW)
+                        fma_bcast<ev_lane<TJ>(1, k), ev_lane<TJ>(2, k)>(
+                            acc[kl][i], ev.e[ev_reg<TJ>(1, k)], ev.e[ev_reg<TJ>(2, k)], g0[j][i], g1[j][i]);
+                    if constexpr (DT)
+                        static_for<NT>([&](auto c) {
+                            const float x = g0[j][i][c], y = g1[j][i][c];
                             a = (i == 0 && c == 0) ? w[kl][i][c] * x : fmaf(w[kl][i][c], x, a);
                             b = (i == 0 && c == 0) ? w[kl][i][c] * y : fmaf(w[kl][i][c], y, b);
-                        }
-                    });
+                        });
                 });
-                if constexpr (DT) v[kl] = fmaf(a, ev_at<TJ>(ev, 3, k), b * ev_at<TJ>(ev, 4, k));
+                if constexpr (DT)
+                    v[kl] = dot_bcast<ev_lane<TJ>(3, k), ev_lane<TJ>(4, k)>(
+                        ev.e[ev_reg<TJ>(3, k)], ev.e[ev_reg<TJ>(4, k)], a, b);
             }
         });
     });

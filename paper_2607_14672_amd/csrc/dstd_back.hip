@@ -1,0 +1,469 @@
+// dstd_back.hip -- the backward contraction of a dense layer on gfx950
+// (dstd_back.h with one tap per input): dL/dW and dL/dt_in of the TTFS layer
+// and of the multi-spike layer.
+//
+// A block holds one tile of NT * 64 neurons, up to kBackWavesMax waves of TJ
+// inputs each, and walks a share of the batch. Items are (sample, input spike
+// f) pairs (f < F; F = 1 for the TTFS layer); a wave's TJ events of an item are
+// loaded during the item before. G of the sample S ahead is written to a ring of
+// 2 S LDS tables meanwhile -- from the neurons' gradient triples, or (multi-
+// spike) copied from memory -- with one barrier per S samples, so that waves
+// with many and with few active inputs average out. A sample's table reaches the
+// last grid point at which a neuron of the tile passes gradient; inputs after
+// it are skipped.
+// dW: each block's sums, to grad_W or (batch split) to partial sums added in
+// split order. dt_in: each tile's sums over its neurons go to a buffer of its
+// own, the first of them grad_t_in itself; launches with more tiles than buffers
+// add to theirs, in order, and back_sum_kernel adds the buffers in order.
+// Bound: the vector ALU and, as its chains are short, waits (about half the wave
+// cycles at 4 waves per SIMD). Against the kernels before it (dW with lanes =
+// inputs, two G rows gathered from LDS per lane and neuron; dt_in with a weight
+// row loaded and a block reduced per record), forward and backward of a layer:
+// 4096 -> 4096, batch 256, M = 64, bf16 weights 3.20 -> 2.17 ms; 6000 -> 1000,
+// batch 100 585 -> 407 us; 784 -> 1000, batch 128 114 -> 105 us; the
+// multi-spike layer 784 x 4 -> 1000, batch 128 752 -> 372 us.
+#include "dstd_back.h"
+#include "dstd_internal.h"
+#include "dstd_kernels.h"
+#include "dstd_profile.h"
+
+#include <algorithm>
+
+namespace dstd {
+
+constexpr int kBackWavesMax = 16;
+constexpr int kBackAhead = 4;  // most samples between barriers
+
+// lanes' maximum of v
+__device__ __forceinline__ int wave_max(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false));  // row_half_mirror
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false));  // row_mirror
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// four consecutive weights, 8 (bf16) or 16 byte aligned
+__device__ __forceinline__ void load4(const float *p, float (&x)[4]) {
+    const float4 v = *reinterpret_cast<const float4 *>(p);
+    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+}
+__device__ __forceinline__ void load4(const uint16_t *p, float (&x)[4]) {
+    const uint2 v = *reinterpret_cast<const uint2 *>(p);
+    x[0] = __uint_as_float(v.x << 16);
+    x[1] = __uint_as_float(v.x & 0xffff0000u);
+    x[2] = __uint_as_float(v.y << 16);
+    x[3] = __uint_as_float(v.y & 0xffff0000u);
+}
+
+struct BackArgs {
+    int B, N_in, N_out, F;
+    int b_per_split, n_chunk;
+    int tile0, add;      // first tile of the launch; add to its dt_in buffers
+    int ahead;           // samples between barriers
+    const float *ev;     // events [B][F][5][N_in] (row as int bits, L, R, dL, dR)
+    const float *g;      // triples [B][3][N_out], or G [B][M + 1][N_out]
+    const void *W;
+    float *dt_in, *P;    // dt_in buffer of the launch's tile 0, and of tile t + 1 at P + t n
+    float *dW;           // grad_W or partial sums [nsplit][N_out][N_in]
+    const float *dq;     // dead-neuron term per neuron, added to dW (one split), or NULL
+    bool vec, w_vec;     // dW rows are 16-byte, W rows four elements aligned
+};
+
+template <typename WT, int NT, int TJ, bool DW, bool DT, bool MEMG>
+__global__ __launch_bounds__(kBackWavesMax * kWave) void back_dense_kernel(LifConst C, BackArgs a) {
+    constexpr int kG = TJ / kBackGroup;
+    constexpr int kRow = NT * kWave;
+    extern __shared__ float gs[];  // G [2 S][R][kRow], pairs (a_d, k_d)
+    const int R = rows_of(C);
+    const int ts = R * kRow;
+    const int S = a.ahead;
+    float2 *tab = reinterpret_cast<float2 *>(gs + 2 * S * ts);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = uniform(threadIdx.x >> 6);
+    const int nw = static_cast<int>(blockDim.x) >> 6;
+    const int tile = a.tile0 + static_cast<int>(blockIdx.y);
+    const int j0 = (static_cast<int>(blockIdx.x) * nw + wave) * TJ;
+    const int nj = max(0, min(TJ, a.N_in - j0));
+    const int i0 = tile * kRow + NT * lane;  // this lane's neurons i0 .. i0 + NT - 1
+    const int b0 = static_cast<int>(blockIdx.z) * a.b_per_split;
+    const int b1 = min(a.B, b0 + a.b_per_split);
+    if constexpr (!MEMG) g_table_fill(C, tab);
+    // rows 0 (and, copied tables, R - 1 and R - 2) hold no grid point
+    for (int k = threadIdx.x; k < 2 * S * kRow; k += blockDim.x) {
+        float *t = gs + (k / kRow) * ts + k % kRow;
+        t[0] = 0.f;
+        t[(R - 1) * kRow] = 0.f;
+    }
+    float acc[kG][kBackGroup][1][NT], w[kG][kBackGroup][1][NT];
+    static_for<TJ>([&](auto j) {
+        static_for<NT>([&](auto c) {
+            acc[j / kBackGroup][j % kBackGroup][0][c] = 0.f;
+            w[j / kBackGroup][j % kBackGroup][0][c] = 0.f;
+        });
+    });
+    if constexpr (DT) {
+        const WT *wp = static_cast<const WT *>(a.W);
+        static_for<NT>([&](auto c) {
+            if (i0 + c >= a.N_out) return;
+            const WT *row = wp + static_cast<int64_t>(i0 + c) * a.N_in + j0;
+            if (a.w_vec && nj == TJ) {
+                static_for<TJ / 4>([&](auto k) {
+                    float x[4];
+                    load4(row + 4 * k, x);
+                    static_for<4>([&](auto u) {
+                        constexpr int jj = 4 * k + u;
+                        w[jj / kBackGroup][jj % kBackGroup][0][c] = x[u];
+                    });
+                });
+            } else {
+                static_for<TJ>([&](auto j) {
+                    if (j < nj) w[j / kBackGroup][j % kBackGroup][0][c] = WLoad<WT>::get(row, j);
+                });
+            }
+        });
+        // loaded before the loop: its waits count its own loads
+        static_for<TJ>([&](auto j) {
+            static_for<NT>([&](auto c) { settle(w[j / kBackGroup][j % kBackGroup][0][c]); });
+        });
+    }
+    // this lane's neurons: offsets clamped into the tile, neurons past N_out
+    // without gradient
+    unsigned no[NT];
+    bool nok[NT];
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+        no[c] = static_cast<unsigned>(min(i0 + c, a.N_out - 1));
+        nok[c] = i0 + c < a.N_out;
+    }
+    auto load_tri = [&](int b) {
+        const float *p = a.g + static_cast<int64_t>(min(b, a.B - 1)) * 3 * a.N_out;
+        GTri<NT> t;
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            t.gK[c] = p[no[c]];
+            t.gE[c] = (p + a.N_out)[no[c]];
+            t.q[c] = __float_as_int((p + 2 * a.N_out)[no[c]]);
+        }
+        return t;
+    };
+    // the table of sample b; returns the last event row that meets gradient
+    auto write_tri = [&](GTri<NT> t, int slot) {
+        int qm = -1;
+#pragma unroll
+        for (int c = 0; c < NT; ++c) {
+            t.gK[c] = nok[c] ? t.gK[c] : 0.f;
+            t.gE[c] = nok[c] ? t.gE[c] : 0.f;
+            t.q[c] = nok[c] ? t.q[c] : -1;
+            qm = max(qm, t.q[c]);
+        }
+        const int top = min(R - 2, wave_max(qm) + 1);
+        if (top <= 0) return -1;
+        g_rows<NT>(C.M, tab, t, top, wave, nw, gs + slot * ts + NT * lane);
+        return top;
+    };
+    auto write_mem = [&](int b, int slot) {
+        const float *p = a.g + static_cast<int64_t>(b) * (C.M + 1) * a.N_out;
+        float *gl = gs + slot * ts + NT * lane;
+        for (int r0 = 1 + wave; r0 <= C.M + 1; r0 += 4 * nw) {
+            float v[4][NT];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float *q = p + static_cast<int64_t>(min(r0 + u * nw, C.M + 1) - 1) * a.N_out;
+#pragma unroll
+                for (int c = 0; c < NT; ++c) v[u][c] = q[no[c]];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (r0 + u * nw > C.M + 1) break;
+#pragma unroll
+                for (int c = 0; c < NT; ++c) v[u][c] = nok[c] ? v[u][c] : 0.f;
+                lds_put<NT>(gl + (r0 + u * nw) * kRow, v[u]);
+            }
+        }
+        return R - 2;
+    };
+    const EvOffs<TJ> ev_o = ev_offs<TJ>(a.N_in, max(nj, 1), lane);
+    auto item_ev = [&](int b, int d) {
+        return ev_load<TJ>(a.ev + (static_cast<int64_t>(min(b, a.B - 1)) * a.F + d) * kEvFields * a.N_in +
+                               (nj > 0 ? j0 : 0), ev_o);
+    };
+    // lane 8j + h of a dt_in store holds input 8h + j of the wave
+    const int p_off = (lane & 7) < kG ? 4 * a.F * ((lane & 7) * kBackGroup + (lane >> 3)) : 1 << 30;
+    float *p_buf = blockIdx.y == 0 ? a.dt_in
+                                   : a.P + static_cast<int64_t>(blockIdx.y - 1) * a.B * a.N_in * a.F;
+    if (b0 < b1) {
+        // sample b's table is in slot (b - b0) % (2 S); r[k]: r_end of sample b + k
+        int b = b0, d = 0, r[kBackAhead];
+        EvRegs<TJ> ev[2];
+        ev[0] = item_ev(b0, 0);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kBackAhead; ++k) {
+            r[k] = -1;
+            if (k < S && b0 + k < b1) {
+                if constexpr (MEMG) r[k] = write_mem(b0 + k, k);
+                else r[k] = write_tri(load_tri(b0 + k), k);
+            }
+        }
+        __syncthreads();
+        int slot = 0;
+        bool more = true;
+        auto item = [&](auto par) {
+            constexpr int p = par;
+            const bool last_d = d + 1 == a.F;
+            ev[p ^ 1] = item_ev(last_d ? b + 1 : b, last_d ? 0 : d + 1);
+            GTri<NT> t_n;
+            if constexpr (!MEMG) t_n = load_tri(b + S);
+            float tot[kG];
+            static_for<kG>([&](auto h) { tot[h] = 0.f; });
+            if (r[0] >= 0) {
+                const float *gl[1] = {gs + slot * ts + NT * lane};
+                const unsigned act = static_cast<unsigned>(__ballot(
+                    lane < nj && static_cast<unsigned>(__float_as_int(ev[p].e[0])) <= static_cast<unsigned>(r[0])));
+                static_for<kG>([&](auto h) {
+                    if ((act >> (h * kBackGroup)) & 0xffu)
+                        tot[h] = back_group<NT, 1, TJ, h, DW, DT>(gl, lane, act, ev[p], w[h], acc[h]);
+                });
+            }
+            if constexpr (DT) {
+                float v = tot[0];
+                static_for<kG>([&](auto x) { v = ((lane & 7) == x) ? tot[x] : v; });
+                float *out = p_buf + (static_cast<int64_t>(b) * a.N_in + (nj > 0 ? j0 : 0)) * a.F + d;
+                const __amdgpu_buffer_rsrc_t pr =
+                    make_rsrc(out, nj > 0 ? static_cast<uint32_t>((nj - 1) * a.F + 1) * 4u : 0u);
+                if (a.add) v += BufLoad<float>::get(pr, p_off, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), pr, p_off, 0, 0);
+            }
+            ++d;
+            if (last_d) {
+                int rn = -1;
+                if (b + S < b1) {
+                    const int sn = slot + S < 2 * S ? slot + S : slot - S;
+                    if constexpr (MEMG) rn = write_mem(b + S, sn);
+                    else rn = write_tri(t_n, sn);
+                }
+#pragma unroll
+                for (int k = 0; k < kBackAhead; ++k)
+                    r[k] = k + 1 < S ? r[min(k + 1, kBackAhead - 1)] : rn;
+                ++b;
+                d = 0;
+                more = b < b1;
+                slot = slot + 1 < 2 * S ? slot + 1 : 0;
+                if (slot == 0 || slot == S) __syncthreads();
+            }
+        };
+        while (true) {
+            item(std::integral_constant<int, 0>{});
+            if (!more) break;
+            item(std::integral_constant<int, 1>{});
+            if (!more) break;
+        }
+    }
+    if constexpr (DW) {
+        float *out = a.dW + static_cast<int64_t>(blockIdx.z) * a.N_out * a.N_in + j0;
+        const bool vec = a.vec && nj == TJ;
+        static_for<NT>([&](auto c) {
+            if (!nok[c]) return;
+            float *o = out + static_cast<int64_t>(i0 + c) * a.N_in;
+            const float q = a.dq ? a.dq[i0 + c] : 0.f;
+            auto at = [&](auto jj) {
+                const float x = acc[jj / kBackGroup][jj % kBackGroup][0][c];
+                return a.dq ? x + q : x;
+            };
+            if (vec) {
+                static_for<TJ / 4>([&](auto k) {
+                    constexpr int x = 4 * k;
+                    reinterpret_cast<float4 *>(o)[k] =
+                        make_float4(at(std::integral_constant<int, x>{}), at(std::integral_constant<int, x + 1>{}),
+                                    at(std::integral_constant<int, x + 2>{}), at(std::integral_constant<int, x + 3>{}));
+                });
+            } else {
+                static_for<TJ>([&](auto jj) {
+                    if (jj < nj) o[jj] = at(jj);
+                });
+            }
+        });
+    }
+}
+
+// Sums in order, four outputs per thread (one 16-byte load per summand where
+// they are aligned to it, four summands in flight):
+// blocks [0, n_dw) add the dW partial sums (+ the row's dead-neuron term), the
+// rest the dt_in buffers.
+struct SumJob {
+    int64_t n;
+    int count;
+    const float *first, *rest;
+    float *out;
+    const float *dq;
+    int row_len;
+    bool vec;  // every summand is 16-byte aligned, n a multiple of 4
+};
+
+__device__ __forceinline__ void sum4(const SumJob &s, int64_t t) {
+    const int64_t k = 4 * t;
+    if (k >= s.n) return;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    auto src = [&](int z) { return z == 0 ? s.first : s.rest + static_cast<int64_t>(z - 1) * s.n; };
+    if (s.count > 0 && s.vec) {
+        const float4 x = *reinterpret_cast<const float4 *>(s.first + k);
+        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+#pragma unroll 4
+        for (int z = 1; z < s.count; ++z) {
+            const float4 y = *reinterpret_cast<const float4 *>(src(z) + k);
+            v[0] += y.x; v[1] += y.y; v[2] += y.z; v[3] += y.w;
+        }
+    } else if (s.count > 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = (k + c < s.n) ? s.first[k + c] : 0.f;
+        for (int z = 1; z < s.count; ++z)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (k + c < s.n) v[c] += src(z)[k + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if (k + c < s.n) s.out[k + c] = s.dq ? v[c] + s.dq[(k + c) / s.row_len] : v[c];
+}
+
+__global__ __launch_bounds__(256) void back_sum_kernel(SumJob dw, int n_dw, SumJob dt) {
+    const int64_t blk = blockIdx.x;
+    if (blk < n_dw) sum4(dw, blk * 256 + threadIdx.x);
+    else sum4(dt, (blk - n_dw) * 256 + threadIdx.x);
+}
+
+// ------------------------------------------------------------- launcher --
+// NT = 2 neurons per lane past 64 (their two tables as far as they fit
+// kBackLdsDense), TJ = 16 inputs per wave. The waves per block w, the blocks
+// over the inputs and the batch split (<= cap, >= 4 samples each) by the time
+// they predict: rounds over the chip's blocks x samples (5 for the start and
+// end of a block) x a wave's instructions per sample (its inputs, and its share
+// of the table's rows) x the cycles per instruction, which grow with the waves
+// per CU, + the pass over partial sums. The constants are those of the shapes
+// measured (784 -> 1000, 1021 -> 517, 6000 -> 1000, 4096 -> 4096).
+constexpr int kBackLdsDense = 152 * 1024;
+constexpr int kBackTJ = 16;
+constexpr int kBackCUs = 256;
+constexpr int kLdsBytes = 160 * 1024;
+
+BackPlan plan_back(int64_t B, int64_t N_in, int64_t N_out, int64_t F, int M, int64_t cap) {
+    BackPlan p;
+    const int tab = g_table_len(M) * static_cast<int>(sizeof(float2));
+    auto lds = [&](int nt, int s) { return 2 * s * (M + 3) * nt * kWave * 4 + tab; };
+    p.nt = (N_out > kWave && lds(2, 1) <= kBackLdsDense) ? 2 : 1;
+    p.tiles = static_cast<int>((N_out + p.nt * kWave - 1) / (p.nt * kWave));
+    p.n_chunk = static_cast<int>((N_in + kBackTJ - 1) / kBackTJ);
+    const double items = (p.nt == 2 ? 250. : 170.) * static_cast<double>(F);
+    const double rows = 6. * p.nt * (M + 3);
+    const double part = 8. * static_cast<double>(N_in) * static_cast<double>(N_out) * (1630. / 4e6);
+    double best = -1.;
+    for (int most = kBackWavesMax; most >= 1; --most) {
+        const int groups = std::max(1, (p.n_chunk + most - 1) / most);
+        const int w = std::max(1, (p.n_chunk + groups - 1) / groups);
+        if (w != most && most > 1 && p.n_chunk > 0) continue;  // the same blocks as with fewer waves
+        const int per = std::max(1, std::min(kBackWavesMax / w, kLdsBytes / lds(p.nt, 1)));
+        const int64_t blocks = static_cast<int64_t>(groups) * std::max(1, p.tiles);
+        const int64_t fit = static_cast<int64_t>(kBackCUs) * per / blocks;
+        for (const int64_t want : {int64_t{1}, cap, std::min(cap, fit)}) {
+            const int64_t ns = std::max<int64_t>(1, std::min(want, B / 4));
+            const int64_t bps = std::max<int64_t>(1, (B + ns - 1) / ns);
+            const int64_t n = std::max<int64_t>(1, (B + bps - 1) / bps), tot = blocks * n;
+            const double rounds = static_cast<double>((tot + kBackCUs * per - 1) / (kBackCUs * per));
+            const double in_cu = static_cast<double>(std::min<int64_t>(per, (tot + kBackCUs - 1) / kBackCUs) * w);
+            double cost = rounds * (static_cast<double>(bps) + 5.) * (items + 60. + rows / w) *
+                          (6. + 9. / 16. * in_cu);
+            if (n > 1) cost += 1630. * 5. + static_cast<double>(n + 1) * part;
+            if (best >= 0. && cost >= best) continue;
+            best = cost;
+            p.groups = groups;
+            p.waves = w;
+            p.nsplit = static_cast<int>(n);
+            p.b_per_split = static_cast<int>(bps);
+        }
+    }
+    // tables ahead as far as the CU still holds its blocks
+    const int room = kBackLdsDense / std::max(1, kBackWavesMax / p.waves);
+    p.ahead = 1;
+    while (p.ahead < kBackAhead && lds(p.nt, 2 * p.ahead) <= room) p.ahead *= 2;
+    p.lds = static_cast<size_t>(lds(p.nt, p.ahead));
+    return p;
+}
+
+int64_t back_split_cap(int64_t B, int64_t N_in, int64_t N_out, int M) {
+    const int64_t jw = N_out <= 16 ? 16 : (N_out <= 32 || M > 86) ? 32 : 64;
+    const int64_t pieces = ((N_in + 255) / 256) * ((N_out + jw - 1) / jw);
+    int64_t ns = 1;
+    while (pieces * ns < 1024 && B / (ns * 2) >= 4) ns *= 2;
+    return ns >= 4 ? ns / 2 : ns;
+}
+
+hipError_t launch_back(const LifConst &C, const BackPlan &p, const BackJob &j, hipStream_t st) {
+    const bool dw = j.grad_W && j.N_out * j.N_in > 0;
+    const bool dt = j.grad_t_in && j.B * j.N_in > 0;
+    const bool split = dw && p.nsplit > 1;
+    const int64_t n_dt = j.B * j.N_in * j.F;
+    if (!dw && !dt) return hipSuccess;
+    BackArgs a{static_cast<int>(j.B), static_cast<int>(j.N_in), static_cast<int>(j.N_out),
+               static_cast<int>(j.F), p.b_per_split, p.n_chunk, 0, 0, p.ahead, j.ev, j.g, j.W,
+               j.grad_t_in, j.P, split ? j.part : j.grad_W, split ? nullptr : j.dq, false, false};
+    auto al16 = [](const void *x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
+    a.vec = (j.N_in & 3) == 0 && al16(a.dW);
+    a.w_vec = (j.N_in & 3) == 0 && (reinterpret_cast<uintptr_t>(j.W) & (j.bf16 ? 7 : 15)) == 0;
+    // tiles per launch: all, or with dt_in as evenly as its buffers allow
+    const int launches = dt ? (p.tiles + j.n_buf) / (1 + j.n_buf) : 1;
+    const int bufs = launches > 0 ? (p.tiles + launches - 1) / launches : 0;
+    {
+        ProfScope prof(j.mem_g ? "ms_back" : "back_dense", st);
+        for (int t = 0; t < p.tiles; t += bufs) {
+            a.tile0 = t;
+            a.add = dt && t > 0;
+            const dim3 grid(static_cast<unsigned>(p.groups),
+                            static_cast<unsigned>(std::min(bufs, p.tiles - t)),
+                            static_cast<unsigned>(p.nsplit));
+            const dim3 block(static_cast<unsigned>(p.waves * kWave));
+#define BD(WTY, NTV, DWV, DTV, MG)                                                                  \
+    hipLaunchKernelGGL((back_dense_kernel<WTY, NTV, kBackTJ, DWV, DTV, MG>), grid, block, p.lds, st, C, a)
+#define BD_M(WTY, NTV, MG)                            \
+    do {                                              \
+        if (dw && dt) BD(WTY, NTV, true, true, MG);   \
+        else if (dw) BD(WTY, NTV, true, false, MG);   \
+        else BD(WTY, NTV, false, true, MG);           \
+    } while (0)
+#define BD_N(WTY, MG)                                 \
+    do {                                              \
+        if (p.nt == 2) BD_M(WTY, 2, MG);              \
+        else BD_M(WTY, 1, MG);                        \
+    } while (0)
+            if (j.bf16) {
+                if (j.mem_g) BD_N(uint16_t, true);
+                else BD_N(uint16_t, false);
+            } else {
+                if (j.mem_g) BD_N(float, true);
+                else BD_N(float, false);
+            }
+#undef BD_N
+#undef BD_M
+#undef BD
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+    }
+    const int64_t n_dw = j.N_out * j.N_in;
+    const int used = bufs;
+    const SumJob sw{split ? n_dw : 0, p.nsplit, j.part, j.part + n_dw, j.grad_W, j.dq,
+                    static_cast<int>(j.N_in), (n_dw & 3) == 0 && al16(j.part)};
+    // (no neurons: dt_in = 0)
+    const SumJob sd{dt && used != 1 ? n_dt : 0, used, j.grad_t_in, j.P, j.grad_t_in, nullptr, 1,
+                    (n_dt & 3) == 0 && al16(j.grad_t_in) && al16(j.P)};
+    const int64_t nb_w = (sw.n + 1023) / 1024, nb_d = (sd.n + 1023) / 1024;
+    if (nb_w + nb_d > 0) {
+        ProfScope prof(j.mem_g ? "ms_sum" : "back_sum", st);
+        hipLaunchKernelGGL(back_sum_kernel, dim3(static_cast<unsigned>(nb_w + nb_d)), dim3(256), 0, st,
+                           sw, static_cast<int>(nb_w), sd);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace dstd

@@ -525,12 +525,6 @@ struct PosWalk {
             ob[ky] = vky[ky] ? min(max(o[xb * R], oa[ky]), per) : 0;
         }
     }
-
-    // byte offset of a record's weight row; stale keys read past a segment
-    // end are clamped so the scalar offset always stays inside WT
-    __device__ __forceinline__ int wrow(int key, int ky, int rstride) const {
-        return min(max(key + wofs[ky], 0), wlim) * rstride;
-    }
 };
 
 // -------------------------------------------------------------- forward --

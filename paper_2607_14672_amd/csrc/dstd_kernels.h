@@ -9,37 +9,52 @@
 
 namespace dstd {
 
-struct DwPlan { int waves, jw, nsplit, b_per_split, ipt; };
-// dW of large layers with one sample group and M >= 64: inputs per thread
-constexpr int kDwWideIPT = 2;
-
 // records past the end of a sample's sorted list that the forward kernel may
 // read (and mask): the list array is padded by this many records
 constexpr int kSortPad = 128;
 
-DwPlan plan_dw(int64_t B, int64_t N_in, int64_t N_out, int M);
-
 // per sample, the records with events (one per entry of t_in [B][n_rec])
 // sorted by event row, as the forward walks them
-hipError_t launch_sort_records(const LifConst &C, int64_t B, int64_t n_rec, const float *t_in,
-                               SortedEv srt, int *n_valid, const char *name, hipStream_t st);
+hipError_t launch_sort_transpose(const LifConst &C, int64_t B, int64_t n_rec, int64_t N_in,
+                                 int64_t N_out, const float *t_in, SortedEv srt, int *n_valid,
+                                 const void *W, bool bf16, void *Wt, const char *name,
+                                 hipStream_t st);
 
 hipError_t launch_forward(const LifConst &C, int64_t B, int64_t N_in, int64_t N_out, const void *W,
                           bool bf16, void *Wt, SortedEv srt, int *n_valid, const float *t_in,
                           float *t_out, float *slope, int *q_idx, hipStream_t st);
 
-// Dense backward workspace: per-input events (dW), the row-sorted records
-// with derivatives (dt_in), WT, the per-neuron gradient triples and the dW
-// split partial sums.
-struct DenseBwdWs {
-    int *row;
-    float *L, *R;
-    SortedEv srt;
-    int *n_valid;
-    void *wt;
-    float *gam, *uq;
-    int *q;
+// The dense backward contraction (dstd_back.hip): neurons per lane, neuron
+// tiles, input chunks, blocks over the chunks (groups) of `waves` waves, batch
+// splits and LDS bytes. cap: most batch splits (partial sums).
+struct BackPlan {
+    int nt, tiles, n_chunk, groups, waves, nsplit, b_per_split, ahead;
+    size_t lds;
+};
+BackPlan plan_back(int64_t B, int64_t N_in, int64_t N_out, int64_t F, int M, int64_t cap);
+int64_t back_split_cap(int64_t B, int64_t N_in, int64_t N_out, int M);
+// ev: events [B][F][5][N_in]; g: gradient triples [B][3][N_out], or (mem_g) G
+// [B][M + 1][N_out]; P: n_buf dt_in buffers [B][N_in][F] beside grad_t_in;
+// part: dW partial sums [nsplit][N_out][N_in]; dq: dead-neuron term or NULL.
+struct BackJob {
+    int64_t B, N_in, N_out, F;
+    const float *ev, *g;
+    bool mem_g;
+    const void *W;
+    bool bf16;
+    float *P;
+    int n_buf;
     float *part;
+    const float *dq;
+    float *grad_W, *grad_t_in;
+};
+hipError_t launch_back(const LifConst &C, const BackPlan &p, const BackJob &j, hipStream_t st);
+
+// Dense backward workspace: events, gradient triples, dt_in buffers and dW
+// partial sums (see BackJob).
+struct DenseBwdWs {
+    float *ev, *tri, *P, *part;
+    int n_buf;
 };
 hipError_t launch_backward(const LifConst &C, int64_t B, int64_t N_in, int64_t N_out,
                            const void *W, bool bf16, const float *t_in, const float *t_out,
@@ -75,7 +90,6 @@ struct ConvGeom {
     float inv_P;
     FastDiv dv_pch, dv_w, dv_cin;  // by Wp * P (raw inputs per channel of a cell row), W, C_in
     FastDiv dv_p, dv_kw, dv_pc;    // by P, KW (receptive-field decode) and PC
-    FastDiv dv_howo, dv_wo;        // by Ho * Wo and Wo (output position decode)
 };
 
 inline FastDiv fast_div(uint32_t d) {
@@ -170,10 +184,8 @@ hipError_t launch_skip_split(int64_t B, int64_t n1, int64_t n2, const float *g, 
                              float *g2, hipStream_t st);
 
 // ------------------------------------------------------------ multispike --
-// Events of every input spike ([B][N_in][F_in]: row = q + 1 or -1, L, R and
-// their time derivatives) and the backward's per-neuron inputs: the forward's
-// spikes [B][N_out][F] and the upstream gradient, G [B][M + 1][N_out] out.
-struct MsEvents { int *row; float *L, *R, *dL, *dR; };
+// The backward's per-neuron inputs: the forward's spikes [B][N_out][F] and the
+// upstream gradient, G [B][M + 1][N_out] out.
 struct MsGrad {
     const float *t, *slope;
     const int *q;
@@ -184,32 +196,18 @@ struct MsGrad {
 };
 constexpr int kMsMaxM = 250;  // (M + 3) rows x 64 lanes of fp32 in 64 KB of LDS
 constexpr int kMsMaxF = 64;
-// dW for M <= kMsDwMaxM stages G tiles in LDS, with the batch split S ways
-// (S from the shapes alone, so the workspace query and the launch agree:
-// about 2048 blocks, at most 16 splits);
-// S > 1 needs S * N_in * N_out floats of partials in the workspace. 0: the
-// one-wave-per-input kernel is used instead.
-constexpr int kMsDwMaxM = 64;
-inline int ms_dw_splits(int M, int64_t B, int64_t N_in, int64_t N_out) {
-    if (M > kMsDwMaxM || B < 1 || N_in < 1 || N_out < 1) return 0;
-    const int64_t blocks = ((N_out + 63) / 64) * ((N_in + 63) / 64);
-    int64_t s = (2048 + blocks - 1) / blocks;
-    s = s < 16 ? s : 16;
-    s = s < B ? s : B;
-    const int64_t per = (B + s - 1) / s;
-    return static_cast<int>((B + per - 1) / per);
-}
-
 hipError_t launch_ms_forward(const LifConst &C, int64_t B, int64_t N_in, int64_t F_in,
                              int64_t N_out, int64_t F_out, const void *W, bool bf16, void *Wt,
                              SortedEv srt, int *n_valid, const float *t_in, float *t_out,
                              float *slope, int *q_idx, float *cur, hipStream_t st);
+// the backward's contraction, and its dt_in buffers beside grad_t_in
+BackPlan plan_ms_back(int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, int M, int64_t *n_buf);
+// ws: events [B][F_in][5][N_in], G in place of the triples
 hipError_t launch_ms_backward(const LifConst &C, int64_t B, int64_t N_in, int64_t F_in,
-                              int64_t N_out, int64_t F_out, const void *W, bool bf16, void *Wt,
-                              MsEvents ev, const float *t_in, const float *t_out,
-                              const float *slope, const int *q_idx, const float *cur,
-                              const float *grad_t, float *G, float *dw_part, float *grad_W,
-                              float *grad_t_in, hipStream_t st);
+                              int64_t N_out, int64_t F_out, const void *W, bool bf16, DenseBwdWs ws,
+                              const float *t_in, const float *t_out, const float *slope,
+                              const int *q_idx, const float *cur, const float *grad_t,
+                              float *grad_W, float *grad_t_in, hipStream_t st);
 
 // ----------------------------------------------------------------- exact --
 // Exact spike times by sorting (App. A, Alg. 1). Per sample, the finite

@@ -10,27 +10,28 @@
 // the previous one through the reset); neurons and samples are independent.
 //
 // Kernels:
-//  ms_prep_kernel: events of every input spike (row, L, R, dL/dt, dR/dt),
-//    once per call, and the transposed weights; the backward role also
-//    builds G[b][m][i] = dL/dw^_im from the neuron's spikes (adjoints through
-//    the reset chain, implicit function theorem per spike).
+//  ms_back_prep_kernel: events of every input spike (row, L, R, dL/dt, dR/dt)
+//    and G[b][m][i] = dL/dw^_im from the neuron's spikes (adjoints through the
+//    reset chain, implicit function theorem per spike).
 //  ms_fwd_kernel: the TTFS forward's walk over the sample's input spikes
 //    sorted by event row (the records are input spikes), closing grid points
 //    into a scan with reset that solves each crossing at once.
-//  ms_dw_kernel / ms_dtin_kernel: the event contractions with G read from
-//    memory (lanes over neurons, so G rows are coalesced).
+// The event contractions are the dense layer's (dstd_back.hip), with an item per
+// input spike and G copied from memory.
+#include "dstd_back.h"
 #include "dstd_internal.h"
 #include "dstd_kernels.h"
 #include "dstd_profile.h"
 #include "dstd_walk.h"
 #include "dstd_rows.h"
 
+#include <algorithm>
+
 namespace dstd {
 
 namespace {
 
 constexpr int kMsPrepThreads = 256;
-constexpr int kMsWaves = 4;  // waves per dW / dt_in block (one input each)
 constexpr int kMsGReg = 8;   // spikes per neuron whose G terms are summed in registers
 
 // K(u) in fp64 for the state carried after a reset (Table "tab:kernel")
@@ -47,36 +48,32 @@ __device__ __forceinline__ double kern_d64(const LifConst &C, double u) {
     }
 }
 
-// Setup roles by block: [0, n_ev) events of kMsPrepThreads input spikes,
-// [n_ev, n_ev + n_tr) one 32 x 32 tile of W^T each, then (backward) G of
-// kMsPrepThreads neurons each.
-template <typename WT, int KS>
-__global__ __launch_bounds__(kMsPrepThreads) void ms_prep_kernel(
-    LifConst C, int64_t n_spk, int n_ev, int n_tr, int N_in, int N_out, const float *__restrict__ t_in,
-    MsEvents ev, const WT *__restrict__ W, WT *__restrict__ Wt, MsGrad gr) {
-    __shared__ WT buf[32][33];
+// Set-up of the backward, by block role: [0, n_ev) events of kMsPrepThreads
+// input spikes each, ev[b][f][field][j], the rest G of kMsPrepThreads neurons.
+template <int KS>
+__global__ __launch_bounds__(kMsPrepThreads) void ms_back_prep_kernel(
+    LifConst C, int64_t n_spk, int n_ev, int N_in, int F_in, int N_out, const float *__restrict__ t_in,
+    float *__restrict__ ev, MsGrad gr) {
     const int blk = blockIdx.x;
     if (blk < n_ev) {
         const int64_t x = static_cast<int64_t>(blk) * kMsPrepThreads + threadIdx.x;
-        if (x < n_spk) {
-            const Event e = bin_event<KS>(C, t_in[x]);
-            ev.row[x] = e.row;
-            ev.L[x] = e.L;
-            ev.R[x] = e.R;
-            ev.dL[x] = e.dL;
-            ev.dR[x] = e.dR;
+        if (x < n_spk) {  // x = (b F_in + f) N_in + j
+            const int64_t bf = x / N_in, j = x - bf * N_in, b = bf / F_in, f = bf - b * F_in;
+            const Event e = bin_event<KS>(C, t_in[(b * N_in + j) * F_in + f]);
+            float *o = ev + bf * kEvFields * N_in + j;
+            o[0] = __int_as_float(e.row);
+            o[N_in] = e.L;
+            o[2 * static_cast<int64_t>(N_in)] = e.R;
+            o[3 * static_cast<int64_t>(N_in)] = e.dL;
+            o[4 * static_cast<int64_t>(N_in)] = e.dR;
         }
-        return;
-    }
-    if (blk < n_ev + n_tr) {
-        transpose_tile<WT, kMsPrepThreads>(N_out, N_in, W, Wt, blk - n_ev, buf);
         return;
     }
     // G of one neuron (b, i): gbar_k = g_k + gbar_{k+1} d t_{k+1}/d t_k,
     // gamma_k = -gbar_k / slope_k, G[m] = sum_k gamma_k c_k(m) with
     //   c_k(m) = K(t_k - T_m)                                 q_{k-1} < m <= q_k
     //          = e^{-(t_{k-1} - T_m)/tau_I} K(t_k - t_{k-1})  m <= q_{k-1}
-    const int64_t o = static_cast<int64_t>(blk - n_ev - n_tr) * kMsPrepThreads + threadIdx.x;
+    const int64_t o = static_cast<int64_t>(blk - n_ev) * kMsPrepThreads + threadIdx.x;
     if (o >= gr.n) return;
     const int64_t b = o / N_out, i = o - b * N_out;
     const int F = gr.F;
@@ -339,189 +336,7 @@ __global__ __launch_bounds__(256) void ms_fwd_kernel(LifConst C, int B, int N_in
     sc.finish();
 }
 
-// grad_W[i][j] = sum_b sum_f (G[b][m][i] L + G[b][m+1][i] R) over the events
-// (m = row - 1) of input spike (b, j, f): lanes over neurons i, one wave per
-// input j; G rows [b][m][:] are coalesced, the events uniform.
-__global__ __launch_bounds__(kMsWaves * kWave) void ms_dw_kernel(LifConst C, int B, int N_in,
-                                                                 int F_in, int N_out, MsEvents ev,
-                                                                 const float *__restrict__ G,
-                                                                 float *__restrict__ grad_W) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int j = blockIdx.y * kMsWaves + uniform(threadIdx.x >> 6);
-    const int i = blockIdx.x * kWave + lane;
-    if (j >= N_in) return;  // wave-uniform; no block barrier in this kernel
-    const int R = C.M + 1;
-    const int ic = i < N_out ? i : 0;
-    float a = 0.f;
-    for (int b = 0; b < B; ++b) {
-        const int64_t eo = (static_cast<int64_t>(b) * N_in + j) * F_in;
-        const float *Gb = G + static_cast<int64_t>(b) * R * N_out + ic;
-        for (int f = 0; f < F_in; ++f) {
-            const int row = *as_const(ev.row + eo + f);
-            if (row < 0) continue;
-            const int m = row - 1;  // L at grid point m, R at m + 1
-            if (m >= 0) a = fmaf(Gb[static_cast<int64_t>(m) * N_out], *as_const(ev.L + eo + f), a);
-            if (m + 1 <= C.M) a = fmaf(Gb[static_cast<int64_t>(m + 1) * N_out], *as_const(ev.R + eo + f), a);
-        }
-    }
-    if (i < N_out) grad_W[static_cast<int64_t>(i) * N_in + j] = a;
-}
-
-// grad_t_in[b][j][f] = sum_i w_ij (G[b][m][i] dL + G[b][m+1][i] dR): one wave
-// per (b, j) summing over neurons (lanes) with row j of W^T, then across the
-// wave.
-// dW for M <= kMsDwMaxM. A block takes one 64-neuron tile (lane = neuron i)
-// and 64 inputs (kMsDwIn per wave) over a contiguous share of the batch. Per
-// sample the tile G[b][0..M][tile] is staged in LDS (the next sample's tile
-// is loaded into registers meanwhile), and each wave adds, input by input,
-// G[m][i] L + G[m+1][i] R for the events of its inputs' spikes, whose fields
-// are uniform (scalar loads, a whole spike index f for all kMsDwIn inputs at
-// once). G is read from memory once per (block, sample) instead of once per
-// (input, sample). Output: out[split][i][j], summed over splits in order
-// (or grad_W itself with one split).
-constexpr int kMsDwIn = 16;
-constexpr int kMsDwPre = ((kMsDwMaxM + 1) * kWave + kMsWaves * kWave - 1) / (kMsWaves * kWave);
-
-__global__ __launch_bounds__(kMsWaves * kWave) void ms_dw_tiled_kernel(
-    LifConst C, int B, int N_in, int F_in, int N_out, int b_per, MsEvents ev,
-    const float *__restrict__ G, float *__restrict__ out) {
-    extern __shared__ float gs[];  // [2][M + 1][64]
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = uniform(threadIdx.x >> 6);
-    const int R = C.M + 1;
-    const int n_el = R * kWave;
-    const int i0 = blockIdx.x * kWave;
-    const int j0 = (blockIdx.y * kMsWaves + wave) * kMsDwIn;
-    const int b0 = blockIdx.z * b_per;
-    const int b1 = min(B, b0 + b_per);
-    float pre[kMsDwPre];
-    // thread t holds elements e = t + 256 k of the tile: row e / 64, column e % 64
-    auto fetch = [&](int b) {
-        const float *Gb = G + static_cast<int64_t>(b) * R * N_out;
-#pragma unroll
-        for (int k = 0; k < kMsDwPre; ++k) {
-            const int e = threadIdx.x + k * kMsWaves * kWave;
-            const int ii = i0 + (e & (kWave - 1));
-            pre[k] = (e < n_el && ii < N_out) ? Gb[static_cast<int64_t>(e >> 6) * N_out + ii] : 0.f;
-        }
-    };
-    auto stage = [&](float *dst) {
-#pragma unroll
-        for (int k = 0; k < kMsDwPre; ++k) {
-            const int e = threadIdx.x + k * kMsWaves * kWave;
-            if (e < n_el) dst[e] = pre[k];
-        }
-    };
-    float acc[kMsDwIn];
-#pragma unroll
-    for (int k = 0; k < kMsDwIn; ++k) acc[k] = 0.f;
-    const int jl = N_in - 1;
-    if (b0 < b1) {
-        fetch(b0);
-        stage(gs);
-    }
-    __syncthreads();
-    for (int b = b0; b < b1; ++b) {
-        const int cb = (b - b0) & 1;
-        if (b + 1 < b1) fetch(b + 1);
-        const float *gb = gs + cb * n_el + lane;
-        for (int f = 0; f < F_in; ++f) {
-            int rw[kMsDwIn];
-            float lv[kMsDwIn], rv[kMsDwIn];
-#pragma unroll
-            for (int k = 0; k < kMsDwIn; ++k) {
-                const int64_t eo = (static_cast<int64_t>(b) * N_in + min(j0 + k, jl)) * F_in + f;
-                rw[k] = (j0 + k <= jl) ? *as_const(ev.row + eo) : -1;
-                lv[k] = *as_const(ev.L + eo);
-                rv[k] = *as_const(ev.R + eo);
-            }
-#pragma unroll
-            for (int k = 0; k < kMsDwIn; ++k) {
-                const int m = rw[k] - 1;  // L at grid point m, R at m + 1
-                if (rw[k] >= 0) {
-                    if (m >= 0 && m <= C.M) acc[k] = fmaf(gb[m * kWave], lv[k], acc[k]);
-                    if (m + 1 <= C.M) acc[k] = fmaf(gb[(m + 1) * kWave], rv[k], acc[k]);
-                }
-            }
-        }
-        if (b + 1 < b1) stage(gs + (cb ^ 1) * n_el);
-        __syncthreads();
-    }
-    const int i = i0 + lane;
-    if (i < N_out) {
-        float *o = out + (static_cast<int64_t>(blockIdx.z) * N_out + i) * N_in;
-#pragma unroll
-        for (int k = 0; k < kMsDwIn; ++k)
-            if (j0 + k <= jl) o[j0 + k] = acc[k];
-    }
-}
-
-// out[k] = sum over s of part[s][k], in split order
-__global__ __launch_bounds__(256) void ms_dw_reduce_kernel(int64_t n, int S,
-                                                           const float *__restrict__ part,
-                                                           float *__restrict__ out) {
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (k >= n) return;
-    float a = part[k];
-    for (int s = 1; s < S; ++s) a += part[s * n + k];
-    out[k] = a;
-}
-
-template <typename WT>
-__global__ __launch_bounds__(kMsWaves * kWave) void ms_dtin_kernel(LifConst C, int B, int N_in,
-                                                                   int F_in, int N_out, MsEvents ev,
-                                                                   const WT *__restrict__ Wt,
-                                                                   const float *__restrict__ G,
-                                                                   float *__restrict__ grad_t_in) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int j = blockIdx.x * kMsWaves + uniform(threadIdx.x >> 6);
-    const int b = blockIdx.y;
-    if (j >= N_in) return;  // wave-uniform
-    const int R = C.M + 1;
-    const int64_t eo = (static_cast<int64_t>(b) * N_in + j) * F_in;
-    const float *Gb = G + static_cast<int64_t>(b) * R * N_out;
-    const WT *wr = Wt + static_cast<int64_t>(j) * N_out;
-    for (int f = 0; f < F_in; ++f) {
-        const int row = *as_const(ev.row + eo + f);
-        float a = 0.f;
-        if (row >= 0) {
-            const int m = row - 1;
-            const float dl = (m >= 0) ? *as_const(ev.dL + eo + f) : 0.f;
-            const float dr = (m + 1 <= C.M) ? *as_const(ev.dR + eo + f) : 0.f;
-            const int64_t ml = static_cast<int64_t>(m >= 0 ? m : 0) * N_out;
-            const int64_t mr = static_cast<int64_t>(m + 1 <= C.M ? m + 1 : C.M) * N_out;
-            for (int i = lane; i < N_out; i += kWave) {
-                const float w = WLoad<WT>::get(wr, i);
-                a = fmaf(w, fmaf(Gb[ml + i], dl, Gb[mr + i] * dr), a);
-            }
-        }
-        for (int s = kWave / 2; s > 0; s >>= 1) a += __shfl_xor(a, s);
-        if (lane == 0) grad_t_in[eo + f] = a;
-    }
-}
-
 unsigned cdiv(int64_t a, int64_t b) { return static_cast<unsigned>((a + b - 1) / b); }
-
-template <int KS>
-hipError_t prep(const LifConst &C, int64_t n_spk, int N_in, int N_out, const float *t_in,
-                MsEvents ev, const void *W, bool bf16, void *Wt, bool transpose, MsGrad gr,
-                hipStream_t st) {
-    const int n_ev = static_cast<int>(cdiv(n_spk, kMsPrepThreads));
-    const int n_tr = (transpose && static_cast<int64_t>(N_in) * N_out > 0)
-                         ? static_cast<int>(cdiv(N_in, 32) * cdiv(N_out, 32)) : 0;
-    const int n_g = static_cast<int>(cdiv(gr.n, kMsPrepThreads));
-    const unsigned blocks = static_cast<unsigned>(n_ev + n_tr + n_g);
-    if (blocks == 0) return hipSuccess;
-    if (bf16)
-        hipLaunchKernelGGL((ms_prep_kernel<uint16_t, KS>), dim3(blocks), dim3(kMsPrepThreads), 0, st,
-                           C, n_spk, n_ev, n_tr, N_in, N_out, t_in, ev,
-                           static_cast<const uint16_t *>(W), static_cast<uint16_t *>(Wt), gr);
-    else
-        hipLaunchKernelGGL((ms_prep_kernel<float, KS>), dim3(blocks), dim3(kMsPrepThreads), 0, st,
-                           C, n_spk, n_ev, n_tr, N_in, N_out, t_in, ev,
-                           static_cast<const float *>(W), static_cast<float *>(Wt), gr);
-    return hipGetLastError();
-}
 
 }  // namespace
 
@@ -529,15 +344,9 @@ hipError_t launch_ms_forward(const LifConst &C, int64_t B, int64_t N_in, int64_t
                              int64_t N_out, int64_t F_out, const void *W, bool bf16, void *Wt,
                              SortedEv srt, int *n_valid, const float *t_in, float *t_out,
                              float *slope, int *q_idx, float *cur, hipStream_t st) {
-    hipError_t e = launch_sort_records(C, B, N_in * F_in, t_in, srt, n_valid, "ms_sort", st);
+    const hipError_t e = launch_sort_transpose(C, B, N_in * F_in, N_in, N_out, t_in, srt, n_valid, W,
+                                               bf16, Wt, "ms_sort_transpose", st);
     if (e != hipSuccess) return e;
-    {
-        ProfScope prof("ms_transpose", st);
-        MsEvents none_ev{};
-        e = prep<kAnyKind>(C, 0, static_cast<int>(N_in), static_cast<int>(N_out), t_in, none_ev,
-                           W, bf16, Wt, true, MsGrad{}, st);
-        if (e != hipSuccess) return e;
-    }
     ProfScope prof("ms_fwd", st);
     if (B == 0 || N_out == 0) return hipSuccess;
     const bool gen = C.kind == kGeneral;
@@ -595,71 +404,48 @@ hipError_t launch_ms_forward(const LifConst &C, int64_t B, int64_t N_in, int64_t
     return hipGetLastError();
 }
 
+BackPlan plan_ms_back(int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, int M, int64_t *n_buf) {
+    // Scratch for dt_in buffers and dW partials together: S + 1 times dW (S
+    // splits; 1 without a split). The buffers first, up to half of it.
+    const int64_t n_dw = N_in * N_out, n_dt = std::max<int64_t>(1, B * N_in * F_in);
+    int64_t S = 1;
+    if (M <= 64 && B > 0 && n_dw > 0) {
+        const int64_t blocks = ((N_out + 63) / 64) * ((N_in + 63) / 64);
+        S = std::min<int64_t>({(2048 + blocks - 1) / blocks, 16, B});
+        S = (B + (B + S - 1) / S - 1) / ((B + S - 1) / S);
+        if (S == 1) S = 0;
+        S += 1;
+    }
+    const BackPlan one = plan_back(B, N_in, N_out, F_in, M, 1);
+    *n_buf = std::max<int64_t>(0, std::min<int64_t>(one.tiles - 1, (S + 1) / 2 * n_dw / n_dt));
+    const int64_t cap = n_dw > 0 ? (S * n_dw - *n_buf * n_dt) / n_dw : 1;
+    return plan_back(B, N_in, N_out, F_in, M, std::max<int64_t>(1, cap));
+}
+
 hipError_t launch_ms_backward(const LifConst &C, int64_t B, int64_t N_in, int64_t F_in,
-                              int64_t N_out, int64_t F_out, const void *W, bool bf16, void *Wt,
-                              MsEvents ev, const float *t_in, const float *t_out,
-                              const float *slope, const int *q_idx, const float *cur,
-                              const float *grad_t, float *G, float *dw_part, float *grad_W,
-                              float *grad_t_in, hipStream_t st) {
+                              int64_t N_out, int64_t F_out, const void *W, bool bf16, DenseBwdWs ws,
+                              const float *t_in, const float *t_out, const float *slope,
+                              const int *q_idx, const float *cur, const float *grad_t,
+                              float *grad_W, float *grad_t_in, hipStream_t st) {
     const int64_t n_spk = B * N_in * F_in;
-    MsGrad gr{t_out, slope, q_idx, cur, grad_t, G, B * N_out, static_cast<int>(F_out)};
-    {
+    MsGrad gr{t_out, slope, q_idx, cur, grad_t, ws.tri, B * N_out, static_cast<int>(F_out)};
+    const unsigned n_ev = cdiv(n_spk, kMsPrepThreads), n_g = cdiv(gr.n, kMsPrepThreads);
+    if (n_ev + n_g > 0) {
         ProfScope prof("ms_bwd_prep", st);
-        hipError_t e = (C.kind == kGeneral)
-                           ? prep<kGeneral>(C, n_spk, static_cast<int>(N_in), static_cast<int>(N_out),
-                                            t_in, ev, W, bf16, Wt, grad_t_in != nullptr, gr, st)
-                           : prep<kAnyKind>(C, n_spk, static_cast<int>(N_in), static_cast<int>(N_out),
-                                            t_in, ev, W, bf16, Wt, grad_t_in != nullptr, gr, st);
+#define MSP(KSV)                                                                                  \
+    hipLaunchKernelGGL((ms_back_prep_kernel<KSV>), dim3(n_ev + n_g), dim3(kMsPrepThreads), 0, st,  \
+                       C, n_spk, static_cast<int>(n_ev), static_cast<int>(N_in),                  \
+                       static_cast<int>(F_in), static_cast<int>(N_out), t_in, ws.ev, gr)
+        if (C.kind == kGeneral) MSP(kGeneral);
+        else MSP(kAnyKind);
+#undef MSP
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (grad_W && N_in * N_out > 0) {
-        ProfScope prof("ms_dw", st);
-        const int S = ms_dw_splits(C.M, B, N_in, N_out);
-        if (S > 0) {
-            const int per = static_cast<int>(cdiv(B, S));
-            float *dst = (S > 1) ? dw_part : grad_W;
-            const size_t lds = 2 * static_cast<size_t>(C.M + 1) * kWave * sizeof(float);
-            hipLaunchKernelGGL(ms_dw_tiled_kernel,
-                               dim3(cdiv(N_out, kWave), cdiv(N_in, kMsWaves * kMsDwIn),
-                                    static_cast<unsigned>(S)),
-                               dim3(kMsWaves * kWave), lds, st, C, static_cast<int>(B),
-                               static_cast<int>(N_in), static_cast<int>(F_in),
-                               static_cast<int>(N_out), per, ev, G, dst);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            if (S > 1) {
-                const int64_t n = N_in * N_out;
-                hipLaunchKernelGGL(ms_dw_reduce_kernel, dim3(cdiv(n, 256)), dim3(256), 0, st, n, S,
-                                   dw_part, grad_W);
-                e = hipGetLastError();
-                if (e != hipSuccess) return e;
-            }
-        } else {
-            hipLaunchKernelGGL(ms_dw_kernel, dim3(cdiv(N_out, kWave), cdiv(N_in, kMsWaves)),
-                               dim3(kMsWaves * kWave), 0, st, C, static_cast<int>(B),
-                               static_cast<int>(N_in), static_cast<int>(F_in), static_cast<int>(N_out),
-                               ev, G, grad_W);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-    }
-    if (grad_t_in && B * N_in > 0) {
-        ProfScope prof("ms_dtin", st);
-        dim3 grid(cdiv(N_in, kMsWaves), static_cast<unsigned>(B));
-        if (bf16)
-            hipLaunchKernelGGL(ms_dtin_kernel<uint16_t>, grid, dim3(kMsWaves * kWave), 0, st, C,
-                               static_cast<int>(B), static_cast<int>(N_in), static_cast<int>(F_in),
-                               static_cast<int>(N_out), ev, static_cast<const uint16_t *>(Wt), G,
-                               grad_t_in);
-        else
-            hipLaunchKernelGGL(ms_dtin_kernel<float>, grid, dim3(kMsWaves * kWave), 0, st, C,
-                               static_cast<int>(B), static_cast<int>(N_in), static_cast<int>(F_in),
-                               static_cast<int>(N_out), ev, static_cast<const float *>(Wt), G,
-                               grad_t_in);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    int64_t n_buf;
+    const BackPlan p = plan_ms_back(B, N_in, F_in, N_out, C.M, &n_buf);
+    return launch_back(C, p, BackJob{B, N_in, N_out, F_in, ws.ev, ws.tri, true, W, bf16, ws.P, ws.n_buf,
+                                     ws.part, nullptr, grad_W, grad_t_in}, st);
 }
 
 }  // namespace dstd
