@@ -209,7 +209,14 @@ DenseWs dense_ws_layout(int M, int64_t B, int64_t N_in, int64_t N_out, bool back
         w.dq = off; off += align_up((size_t)N_out * sizeof(float));  // dead-neuron term per row
         w.part = off;
         if (dp.nsplit > 1) off += align_up((size_t)dp.nsplit * (size_t)N_out * (size_t)N_in * sizeof(float));
-        w.total = off;
+        // more than the layer's forward takes, so that one buffer serves both
+        // (up to the most partials that a plan may take)
+        const size_t nt = align_up((size_t)B * (size_t)N_out * sizeof(float));
+        const int64_t cap = dstd::back_split_cap(B, N_in, N_out, M), bps = (std::max<int64_t>(B, 1) + cap - 1) / cap;
+        const int64_t S = (B + bps - 1) / bps;
+        const size_t part = S > 1 ? align_up((size_t)S * (size_t)N_out * (size_t)N_in * sizeof(float)) : 0;
+        w.total = std::max(off, dense_ws_layout(M, B, N_in, N_out, false).total +
+                                    3 * (align_up(n * sizeof(float)) + nt) + (w.part - w.dq) + part);
         return w;
     }
     if (B * N_out == 0) return w;  // the forward enqueues nothing
@@ -944,12 +951,18 @@ MsWs ms_ws_layout(int M, int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, b
     if (backward) {
         w.ev = off; off += align_up(n * 5 * sizeof(float));
         w.G = off; off += align_up((size_t)B * (size_t)(M + 1) * (size_t)N_out * sizeof(float));
-        int64_t n_buf;
-        const dstd::BackPlan mp = dstd::plan_ms_back(B, N_in, F_in, N_out, M, &n_buf);
+        int64_t n_buf, room;
+        const dstd::BackPlan mp = dstd::plan_ms_back(B, N_in, F_in, N_out, M, &n_buf, &room);
         w.n_buf = (int)n_buf;
         w.part = off;
         w.P = off + (mp.nsplit > 1 ? (size_t)mp.nsplit * (size_t)N_in * (size_t)N_out * sizeof(float) : 0);
+        const size_t dw = (size_t)N_in * (size_t)N_out * sizeof(float);
+        const size_t most = 5 * align_up(n * sizeof(float)) + (w.part - w.G) +
+                            align_up((size_t)room * sizeof(float) - dw) + align_up(dw);
         off += align_up(w.P - w.part + n * (size_t)n_buf * sizeof(float));
+        // as much as the layer's forward takes, within the room
+        const size_t fwd = B * N_out == 0 ? 0 : ms_ws_layout(M, B, N_in, F_in, N_out, false).total;
+        off = std::max(off, std::min(most, fwd));
     } else {
         const size_t ns = n + dstd::kSortPad;
         w.sj = off; off += align_up(ns * sizeof(int));

@@ -200,8 +200,10 @@ hipError_t launch_ms_forward(const LifConst &C, int64_t B, int64_t N_in, int64_t
                              int64_t N_out, int64_t F_out, const void *W, bool bf16, void *Wt,
                              SortedEv srt, int *n_valid, const float *t_in, float *t_out,
                              float *slope, int *q_idx, float *cur, hipStream_t st);
-// the backward's contraction, and its dt_in buffers beside grad_t_in
-BackPlan plan_ms_back(int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, int M, int64_t *n_buf);
+// the backward's contraction, its dt_in buffers beside grad_t_in, and the floats
+// that those and the dW partials may take
+BackPlan plan_ms_back(int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, int M, int64_t *n_buf,
+                      int64_t *room);
 // ws: events [B][F_in][5][N_in], G in place of the triples
 hipError_t launch_ms_backward(const LifConst &C, int64_t B, int64_t N_in, int64_t F_in,
                               int64_t N_out, int64_t F_out, const void *W, bool bf16, DenseBwdWs ws,
