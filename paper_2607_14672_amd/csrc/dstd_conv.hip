@@ -537,8 +537,8 @@ struct PosWalk {
 // record, and loads the record's fields with one vector load each; the
 // decoded entries (weight-row offset, row, L, R) go to a small LDS area of
 // the wave. The entries are then summed in batches of up to 8 entries of one
-// event row (each entry read back as one 16-byte LDS broadcast, the batch's
-// weight rows loaded together), and rows close into the interval scan as the
+// event row (a batch's entries read back with one LDS read, its weight rows
+// loaded together), and rows close into the interval scan as the
 // row changes. Sums and their order are those of a row-by-row walk.
 struct FwdEntry { int wb, row; float L, R; };
 // kDirect (receptive fields of at most 64 raw inputs, at most 64 event rows,
@@ -559,6 +559,47 @@ struct FwdEntry { int wb, row; float L, R; };
 // (At most 72 VGPRs, seven waves per SIMD, where that needs no spill: conv9
 // 0.819 -> 0.795 ms against six; else at most 80. Eight would spill.)
 constexpr int kFwdWaves = 4;
+// Sums of up to kCBatch list entries: lane l holds entry l % 8 of the batch (one
+// LDS read of the lanes' entries instead of a broadcast read of each), and an
+// entry's fields are row_newbcast operands: of the add that makes its weight's
+// offset and of its two multiply-adds. What bounds the walk is the vector ALU:
+// 64 -> 64 channels, 32 x 32, 3,873 -> 3,068 vector, 898 -> 143 LDS and (the second
+// half of a batch not loaded where the row ends before it) 453 -> 393 vector
+// memory instructions per wave; forward and backward of that layer 1321 -> 1281 us,
+// the forward of 64 -> 128, 28 x 28, stride 2 220 -> 199 us. Offsets read into
+// scalars instead cost a wait each (forward 15 % slower), and groups of 8 loaded
+// ahead across rows more scalar branches than the unused loads they save (28 %).
+// s_nop: a register written by the vector ALU may be read as a row broadcast two
+// cycles later at the earliest.
+#define FWD_FMA(q, w)                                                                   \
+    "v_fmac_f32_dpp %0, %2, " w " row_newbcast:" q " row_mask:0xf bank_mask:0xf\n" \
+    "v_fmac_f32_dpp %1, %3, " w " row_newbcast:" q " row_mask:0xf bank_mask:0xf\n"
+template <int Q>
+__device__ __forceinline__ void sum_entry(float &aL, float &aR, float L, float R, float w) {
+    asm("s_nop 1\n" FWD_FMA("%5", "%4") : "+v"(aL), "+v"(aR) : "v"(L), "v"(R), "v"(w), "n"(Q));
+}
+__device__ __forceinline__ void sum_entries4(float &aL, float &aR, float L, float R,
+                                             const float *w) {
+    asm("s_nop 1\n" FWD_FMA("0", "%4") FWD_FMA("1", "%5") FWD_FMA("2", "%6") FWD_FMA("3", "%7")
+        : "+v"(aL), "+v"(aR)
+        : "v"(L), "v"(R), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
+}
+__device__ __forceinline__ void sum_entries8(float &aL, float &aR, float L, float R,
+                                             const float (&w)[kCBatch]) {
+    static_assert(kCBatch == 8, "one asm operand per entry");
+    asm("s_nop 1\n" FWD_FMA("0", "%4") FWD_FMA("1", "%5") FWD_FMA("2", "%6") FWD_FMA("3", "%7")
+            FWD_FMA("4", "%8") FWD_FMA("5", "%9") FWD_FMA("6", "%10") FWD_FMA("7", "%11")
+        : "+v"(aL), "+v"(aR)
+        : "v"(L), "v"(R), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]),
+          "v"(w[6]), "v"(w[7]));
+}
+#undef FWD_FMA
+// the weights of entries Q .. Q + 3 of a batch, their byte offsets row broadcasts of wb
+template <int Q>
+__device__ __forceinline__ void load_entries(__amdgpu_buffer_rsrc_t wr, int voff, int wb,
+                                             float (&w)[kCBatch]) {
+    static_for<kCBatch / 2>([&](auto q) { w[Q + q] = BufLoad<float>::get(wr, voff + row_bcast<Q + q>(wb), 0); });
+}
 template <int KHT, int KS, bool kDirect>
 constexpr int fwd_min_waves() {
     return (KHT <= 3 && (kDirect || KS != kAnyKind)) ? 7 : 6;
@@ -821,19 +862,17 @@ __global__ __launch_bounds__(kFwdWaves * kWave) __attribute__((amdgpu_waves_per_
             __builtin_amdgcn_wave_barrier();
             const int nc = min(kWave, total - c0);
             // batches never cross a row: up to kCBatch entries of the head
-            // entry's row, summed without per-entry row tests; a batch's
-            // entries past its row are read (and their weights loaded) but
-            // not summed
+            // entry's row, summed without per-entry row tests; entries past
+            // the row are read (and, in the batch's first half, and in its
+            // second where it has entries, their weights loaded) but not summed
             for (int s0 = 0; s0 < nc;) {
-                FwdEntry e[kCBatch];
+                const FwdEntry e = my[s0 + (lane & (kCBatch - 1))];
                 float w[kCBatch];
-#pragma unroll
-                for (int q = 0; q < kCBatch; ++q) e[q] = my[s0 + q];  // LDS broadcasts
-#pragma unroll
-                for (int q = 0; q < kCBatch; ++q) w[q] = BufLoad<float>::get(wr, voff + e[q].wb, 0);
-                const int hd = uniform(e[0].row);
+                load_entries<0>(wr, voff, e.wb, w);
+                const int hd = uniform(e.row);
                 const int ra = hd & 0xffff;
                 const int nk = max(1, min(min(kCBatch, hd >> 16), nc - s0));  // always advances
+                if (nk > kCBatch / 2) load_entries<kCBatch / 2>(wr, voff, e.wb, w);
                 if (ra != cur) {
                     close_to_mid(ra);
                     if (__all(sc.found() || !row_ok)) {
@@ -842,19 +881,16 @@ __global__ __launch_bounds__(kFwdWaves * kWave) __attribute__((amdgpu_waves_per_
                     }
                 }
                 if (nk == kCBatch) {
-#pragma unroll
-                    for (int q = 0; q < kCBatch; ++q) {
-                        aL = fmaf(w[q], e[q].L, aL);
-                        aR = fmaf(w[q], e[q].R, aR);
-                    }
+                    sum_entries8(aL, aR, e.L, e.R, w);
+                } else if (nk >= kCBatch / 2) {
+                    sum_entries4(aL, aR, e.L, e.R, w);
+                    if (nk > 4) sum_entry<4>(aL, aR, e.L, e.R, w[4]);
+                    if (nk > 5) sum_entry<5>(aL, aR, e.L, e.R, w[5]);
+                    if (nk > 6) sum_entry<6>(aL, aR, e.L, e.R, w[6]);
                 } else {
-#pragma unroll
-                    for (int q = 0; q < kCBatch - 1; ++q) {
-                        if (q < nk) {
-                            aL = fmaf(w[q], e[q].L, aL);
-                            aR = fmaf(w[q], e[q].R, aR);
-                        }
-                    }
+                    sum_entry<0>(aL, aR, e.L, e.R, w[0]);
+                    if (nk > 1) sum_entry<1>(aL, aR, e.L, e.R, w[1]);
+                    if (nk > 2) sum_entry<2>(aL, aR, e.L, e.R, w[2]);
                 }
                 s0 += nk;
             }
@@ -913,24 +949,17 @@ __host__ __device__ __forceinline__ int list_wave_ints(int ne) {
 template <int K, bool kFull = false>
 __device__ __forceinline__ void list_batch(const uint16_t *erow, const float2 *eLR, int idx,
                                            int left, __amdgpu_buffer_rsrc_t wr, int voff,
-                                           int rstride, float &aL, float &aR) {
-    int wb[K];
-    float Lq[K], Rq[K], w[K];
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-        const bool ok = kFull || q < left;
-        wb[q] = ok ? static_cast<int>(__umul24(erow[idx + q], rstride)) : 0;  // both < 2^24
-        const float2 lr = ok ? eLR[idx + q] : make_float2(0.f, 0.f);
-        Lq[q] = lr.x;
-        Rq[q] = lr.y;
-    }
-#pragma unroll
-    for (int q = 0; q < K; ++q) w[q] = BufLoad<float>::get(wr, voff + wb[q], 0);
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-        aL = fmaf(w[q], Lq[q], aL);
-        aR = fmaf(w[q], Rq[q], aR);
-    }
+                                           int rstride, int l8, float &aL, float &aR) {
+    // l8 = lane % 8: lanes l and l + 8 of each 16 hold record l of the lane's position
+    // (32 -> 32 channels, 28 x 28, batch 128: the layer's pass 1340 -> 1297 us)
+    const bool ok = (K == 8 || l8 < K) && (kFull || l8 < left);
+    const int wb = ok ? static_cast<int>(__umul24(erow[idx + l8], rstride)) : 0;  // both < 2^24
+    const float2 lr = ok ? eLR[idx + l8] : make_float2(0.f, 0.f);
+    float w[K];
+    static_for<K>([&](auto q) { w[q] = BufLoad<float>::get(wr, voff + row_bcast<q>(wb), 0); });
+    if constexpr (K == 8) sum_entries8(aL, aR, lr.x, lr.y, w);
+    else if constexpr (K == 4) sum_entries4(aL, aR, lr.x, lr.y, w);
+    else static_for<K>([&](auto q) { sum_entry<q>(aL, aR, lr.x, lr.y, w[q]); });
 }
 
 // kDirect (E <= LP): as in the chunked walk, no cell-row sort: lane li of a
@@ -1198,14 +1227,14 @@ __global__ __launch_bounds__(256) void conv_fwd_list_kernel(LifConst C, ConvGeom
             // count
             int i0 = 0;
             for (; i0 + 8 <= nmin; i0 += 8)
-                list_batch<8, true>(erow, eLR, my_s + i0, my_n - i0, wr, voff, rstride, aL, aR);
+                list_batch<8, true>(erow, eLR, my_s + i0, my_n - i0, wr, voff, rstride, li & 7, aL, aR);
             for (; i0 + 8 <= n; i0 += 8)
-                list_batch<8>(erow, eLR, my_s + i0, my_n - i0, wr, voff, rstride, aL, aR);
+                list_batch<8>(erow, eLR, my_s + i0, my_n - i0, wr, voff, rstride, li & 7, aL, aR);
             if (i0 + 4 <= n) {
-                list_batch<4>(erow, eLR, my_s + i0, my_n - i0, wr, voff, rstride, aL, aR);
+                list_batch<4>(erow, eLR, my_s + i0, my_n - i0, wr, voff, rstride, li & 7, aL, aR);
                 i0 += 4;
             }
-            for (; i0 < n; ++i0) list_batch<1>(erow, eLR, my_s + i0, my_n - i0, wr, voff, rstride, aL, aR);
+            for (; i0 < n; ++i0) list_batch<1>(erow, eLR, my_s + i0, my_n - i0, wr, voff, rstride, li & 7, aL, aR);
         } else if (r == r_last + 2) {
             // every record is in: grid points r-1 .. M see no input, the rest
             // of the window is one free-decay segment
