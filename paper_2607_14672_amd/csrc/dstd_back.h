@@ -14,8 +14,11 @@
 //     passes gradient, costs one scalar branch (the causal half of the pairs
 //     and the silent inputs are never multiplied);
 //   - its two G rows are one conflict-free two-address LDS read;
-//   - dW takes 2 and dt_in 2 multiply-adds per lane, neuron and tap from those
-//     reads, and no weight is loaded again;
+//   - dW takes 2 and dt_in 3 multiply-adds per lane, neuron and tap from those
+//     reads, and no weight is loaded again. (dt_in's dL G[r-1] + dR G[r] nearly
+//     cancels where dt is small: formed per neuron, before the weight. Summing
+//     w G[r-1] and w G[r] apart over a lane's pairs, one multiply-add less for
+//     three taps, rounds two to three times as often at that size.)
 //   - dt_in's sum over the lanes is taken once per input, for all its taps.
 // What bounds it is the vector ALU.
 #pragma once
@@ -179,14 +182,29 @@ __device__ __forceinline__ void fma_bcast(float (&acc)[NT], float L, float R, co
             : "+v"(acc[0])
             : "v"(L), "v"(R), "n"(NL), "v"(x[0]), "v"(y[0]), "n"(NR));
 }
-// bcast(p) a + bcast(q) b
-template <int NP, int NQ>
-__device__ __forceinline__ float dot_bcast(float p, float q, float a, float b) {
-    float v;
-    asm("s_nop 1\nv_mul_f32_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n" FB("%0", "%1", "%3", "%5")
-        : "=&v"(v) : "v"(p), "v"(q), "v"(a), "v"(b), "n"(NP), "n"(NQ));
+// v[c] = bcast(p) a[c] + bcast(q) b[c]
+template <int NP, int NQ, int NT>
+__device__ __forceinline__ void dot_bcast(float (&v)[NT], float p, float q, const float (&a)[NT],
+                                          const float (&b)[NT]) {
+#define MB(d, e, s, n) "v_mul_f32_dpp " d ", " e ", " s " row_newbcast:" n " row_mask:0xf bank_mask:0xf\n"
+    if constexpr (NT == 4)
+        asm("s_nop 1\n" MB("%0", "%5", "%10", "%15") MB("%1", "%5", "%11", "%15")
+                MB("%2", "%5", "%12", "%15") MB("%3", "%5", "%13", "%15") FB("%0", "%4", "%6", "%14")
+                    FB("%1", "%4", "%7", "%14") FB("%2", "%4", "%8", "%14") FB("%3", "%4", "%9", "%14")
+            : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+            : "v"(p), "v"(q), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]),
+              "v"(b[2]), "v"(b[3]), "n"(NP), "n"(NQ));
+    else if constexpr (NT == 2)
+        asm("s_nop 1\n" MB("%0", "%3", "%6", "%9") MB("%1", "%3", "%7", "%9") FB("%0", "%2", "%4", "%8")
+                FB("%1", "%2", "%5", "%8")
+            : "=&v"(v[0]), "=&v"(v[1])
+            : "v"(p), "v"(q), "v"(a[0]), "v"(a[1]), "v"(b[0]), "v"(b[1]), "n"(NP), "n"(NQ));
+    else
+        asm("s_nop 1\n" MB("%0", "%2", "%4", "%6") FB("%0", "%1", "%3", "%5")
+            : "=&v"(v[0])
+            : "v"(p), "v"(q), "v"(a[0]), "v"(b[0]), "n"(NP), "n"(NQ));
+#undef MB
 #undef FB
-    return v;
 }
 
 // Inputs 8 G .. 8 G + 7 of a wave, act: bit k set where input k's row is in
@@ -224,21 +242,19 @@ __device__ __forceinline__ float back_group(const float *(&gl)[KW], int lane, un
             v[kl] = 0.f;
             if (act & (1u << k)) {
                 asm volatile("");
-                float a = 0.f, b = 0.f;
                 static_for<KW>([&](auto i) {
                     if constexpr (DW)
                         fma_bcast<ev_lane<TJ>(1, k), ev_lane<TJ>(2, k)>(
                             acc[kl][i], ev.e[ev_reg<TJ>(1, k)], ev.e[ev_reg<TJ>(2, k)], g0[j][i], g1[j][i]);
-                    if constexpr (DT)
+                    if constexpr (DT) {
+                        float d[NT];
+                        dot_bcast<ev_lane<TJ>(3, k), ev_lane<TJ>(4, k)>(
+                            d, ev.e[ev_reg<TJ>(3, k)], ev.e[ev_reg<TJ>(4, k)], g0[j][i], g1[j][i]);
                         static_for<NT>([&](auto c) {
-                            const float x = g0[j][i][c], y = g1[j][i][c];
-                            a = (i == 0 && c == 0) ? w[kl][i][c] * x : fmaf(w[kl][i][c], x, a);
-                            b = (i == 0 && c == 0) ? w[kl][i][c] * y : fmaf(w[kl][i][c], y, b);
+                            v[kl] = (i == 0 && c == 0) ? w[kl][i][c] * d[c] : fmaf(w[kl][i][c], d[c], v[kl]);
                         });
+                    }
                 });
-                if constexpr (DT)
-                    v[kl] = dot_bcast<ev_lane<TJ>(3, k), ev_lane<TJ>(4, k)>(
-                        ev.e[ev_reg<TJ>(3, k)], ev.e[ev_reg<TJ>(4, k)], a, b);
             }
         });
     });
