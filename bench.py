@@ -309,28 +309,20 @@ def layer_desc(lay):
     return f"{lay.n_in}->{lay.n_out} M={lay.M}"
 
 
-def kernel_algorithmic_flops(net, act, with_scan=True, fused_dwdt=False):
+def kernel_algorithmic_flops(net, act, with_scan=True):
     """Algorithmic flops of one step, per kernel name (2-sparse events:
     FLOPS_PER_UPDATE per (sample, input with events, neuron)); the forward
     kernels, which run the interval scan of their neurons too, also count
-    FLOPS_PER_SCAN_STEP per (neuron, grid point) when with_scan. With
-    fused_dwdt, the conv layers that compute dt_in ran dW and the dt_in
-    partials in one launch (conv_dwdt)."""
-    fl = {k: 0.0 for k in ("fwd_dense", "dw_dense", "dtin_rows", "conv_fwd", "conv_dw",
-                           "conv_dtp", "conv_dwdt", "fwd_mfma")}
+    FLOPS_PER_SCAN_STEP per (neuron, grid point) when with_scan. A layer's dW
+    and dt_in come from one launch (back_dense, conv_back)."""
+    fl = {k: 0.0 for k in ("fwd_dense", "back_dense", "conv_fwd", "conv_back", "fwd_mfma")}
     for l, (e, a) in enumerate(zip(net.L, act)):
         upd = a["updates"]
-        conv = e["cs"] is not None
-        fwd, dw, dt = (("conv_fwd", "conv_dw", "conv_dtp") if conv else
-                       ("fwd_dense", "dw_dense", "dtin_rows"))
-        if conv and fused_dwdt and l > 0:
-            dw = dt = "conv_dwdt"
+        fwd, back = ("conv_fwd", "conv_back") if e["cs"] is not None else ("fwd_dense", "back_dense")
         fl[fwd] += FLOPS_PER_UPDATE * upd
         if with_scan:
             fl[fwd] += FLOPS_PER_SCAN_STEP * e["t_out"].numel() * (e["lay"].M + 1)
-        fl[dw] += FLOPS_PER_UPDATE * upd
-        if l > 0:
-            fl[dt] += FLOPS_PER_UPDATE * upd
+        fl[back] += FLOPS_PER_UPDATE * upd * (2 if l > 0 else 1)
     return fl
 
 
@@ -750,14 +742,8 @@ def measure(torch, dstd, wl, dev, steps, warmup, profile_steps, eager, contract=
     prof = dstd.profile_table()
     per_step = {k: v[1] / profile_steps for k, v in prof.items()}
     launches = {k: v[0] / profile_steps for k, v in prof.items()}
-    # the library runs a conv layer's dW and dt_in partials in one launch
-    # where it has that launch for the layer's shapes (every bench layer)
-    fused = "conv_dwdt" in per_step
-    if fused and "conv_dtp" in per_step:
-        raise RuntimeError("conv layers ran both fused and separate dW / dt_in launches; "
-                           "the per-kernel flop attribution assumes one form")
-    flops = kernel_algorithmic_flops(net, act, fused_dwdt=fused)
-    contraction = kernel_algorithmic_flops(net, act, with_scan=False, fused_dwdt=fused)
+    flops = kernel_algorithmic_flops(net, act)
+    contraction = kernel_algorithmic_flops(net, act, with_scan=False)
     if "fwd_mfma" in per_step and "fwd_dense" not in per_step:
         # the MFMA kernel only contracts; its scan runs in mfma_scan
         flops["fwd_mfma"] = contraction.pop("fwd_dense")
