@@ -37,12 +37,17 @@ namespace dstd {
 // d < 0, once per block.
 __host__ __device__ __forceinline__ int g_table_len(int M) { return 2 * M + 4; }
 
+// Every thread of the block calls it: the entries are shared out over the
+// threads and any wave reads all of them, so it ends with the block barrier
+// that stands between (what was written to LDS before the call is seen after it
+// too).
 __device__ __forceinline__ void g_table_fill(const LifConst &C, float2 *tab) {
     for (int k = threadIdx.x; k < g_table_len(C.M); k += blockDim.x) {
         const int d = k - (C.M + 2);
         const float u = static_cast<float>(d) * C.dt;
         tab[k] = (d >= 0) ? make_float2(expf(-u * C.inv_tv), kern(C, u)) : make_float2(0.f, 0.f);
     }
+    __syncthreads();
 }
 
 struct GradTriple { float gK, gE; int q; };

@@ -89,13 +89,15 @@ __global__ __launch_bounds__(kBackWavesMax * kWave) void back_dense_kernel(LifCo
     const int i0 = tile * kRow + NT * lane;  // this lane's neurons i0 .. i0 + NT - 1
     const int b0 = static_cast<int>(blockIdx.z) * a.b_per_split;
     const int b1 = min(a.B, b0 + a.b_per_split);
-    if constexpr (!MEMG) g_table_fill(C, tab);
-    // rows 0 (and, copied tables, R - 1 and R - 2) hold no grid point
+    // rows 0 and R - 1 hold no grid point (R - 1 is also a triple's table's last
+    // row: written after a barrier)
     for (int k = threadIdx.x; k < 2 * S * kRow; k += blockDim.x) {
         float *t = gs + (k / kRow) * ts + k % kRow;
         t[0] = 0.f;
         t[(R - 1) * kRow] = 0.f;
     }
+    if constexpr (MEMG) __syncthreads();
+    else g_table_fill(C, tab);
     float acc[kG][kBackGroup][1][NT], w[kG][kBackGroup][1][NT];
     static_for<TJ>([&](auto j) {
         static_for<NT>([&](auto c) {
@@ -198,7 +200,6 @@ __global__ __launch_bounds__(kBackWavesMax * kWave) void back_dense_kernel(LifCo
         int b = b0, d = 0, r[kBackAhead];
         EvRegs<TJ> ev[2];
         ev[0] = item_ev(b0, 0);
-        __syncthreads();
 #pragma unroll
         for (int k = 0; k < kBackAhead; ++k) {
             r[k] = -1;

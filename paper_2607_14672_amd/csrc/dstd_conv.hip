@@ -1562,8 +1562,8 @@ __global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst 
     const int nj = mine ? min(TJ, g.C_in - ci0) : 0;
     const int ky = tg / a.kg, kx0 = (tg - ky * a.kg) * KWT;
     const int co = tile * kRow + NT * lane;  // this lane's channels co .. co + NT - 1
-    g_table_fill(C, tab);
     for (int k = threadIdx.x; k < kRing * kRow; k += blockDim.x) gs[(k / kRow) * ts + k % kRow] = 0.f;
+    g_table_fill(C, tab);
     // channels past C_out: weight 0 and no gradient
     float acc[kG][kBackGroup][KWT][NT], w[kG][kBackGroup][KWT][NT];
     static_for<kG>([&](auto h) {
