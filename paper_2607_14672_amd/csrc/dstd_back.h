@@ -52,9 +52,11 @@ __device__ __forceinline__ void g_table_fill(const LifConst &C, float2 *tab) {
 
 struct GradTriple { float gK, gE; int q; };
 
+// q <= M also where the caller's interval index is not (the table has no entry
+// past it): such a neuron is taken to fire after the last grid point.
 __device__ __forceinline__ GradTriple grad_triple(const LifConst &C, float t, float slope, int q,
                                                   float g) {
-    const GradPrep p = grad_prep(C, t, slope, q, g);
+    const GradPrep p = grad_prep(C, t, slope, min(q, C.M), g);
     if (p.q < 0) return GradTriple{0.f, 0.f, -1};
     return GradTriple{p.gam * kern(C, p.uq), p.gam * expf(-p.uq * C.inv_ti), p.q};
 }

@@ -1316,7 +1316,7 @@ __device__ void grad_block(const LifConst &C, const ConvGeom &g, int64_t n_pos, 
                         const int64_t o = obase + static_cast<int64_t>(c4 + u * cstep) * HoWo;
                         float gt = grad_t[o];
                         if (sf.on) gt += synfire_dt(sf, t_out[o]);
-                        if (gt != 0.f) atomicMax(&sl[pl], q[u]);
+                        if (gt != 0.f) atomicMax(&sl[pl], min(q[u], C.M));
                     }
                 }
             }

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kBackPrep) void back_prep_kernel(LifConst C, int B,
                 // the spike time only where it is used (no gradient: no load)
                 const float t = (sf.on || g != 0.f) ? t_out[k] : 0.f;
                 if (sf.on) g += synfire_dt(sf, t);
-                if (g != 0.f) gp = grad_triple(C, t, slope[k], min(q, C.M), g);
+                if (g != 0.f) gp = grad_triple(C, t, slope[k], q, g);
             }
             float *o = tri + static_cast<int64_t>(b) * 3 * N_out + i;
             o[0] = gp.gK;

@@ -45,3 +45,19 @@ def test_conv_backward_shapes(dev, case):  # noqa: F811
     assert none is None and np.array_equal(only_W, gW)
     none, only_x = _gpu_backward(dev, h, g, need_W=False)
     assert none is None and np.array_equal(only_x, gx)
+
+
+@pytest.mark.parametrize("c_out", [20, 70])
+def test_conv_backward_interval_index_past_the_grid(dev, c_out):  # noqa: F811
+    """Interval indices past M are taken as M: same gradients, no entry past the table."""
+    import torch
+    cs = _cs(6, 5, 7, c_out)
+    p, t, W = _conv_case(79, 2, cs, 10, 1.0, 0.3, k=7.0)
+    gpu, (prm, c, tt, Wt, to, sl, q) = _gpu_forward(dev, p, cs, t, W)
+    g = np.random.default_rng(80).standard_normal(gpu["t_out"].shape).astype(np.float32)
+    last = torch.where(q >= 0, torch.full_like(q, p["M"]), q)
+    past = torch.where((q >= 0) & (q % 2 == 0), q + p["M"] + 1000, last)
+    a = _gpu_backward(dev, (prm, c, tt, Wt, to, sl, last), g)
+    b = _gpu_backward(dev, (prm, c, tt, Wt, to, sl, past), g)
+    assert all(np.isfinite(x).all() and x.any() for x in a)
+    assert all(np.array_equal(x, y) for x, y in zip(a, b))
