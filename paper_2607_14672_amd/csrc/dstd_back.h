@@ -167,7 +167,9 @@ template <int TJ> constexpr int ev_lane(int f, int k) { return (f * TJ + k) % 16
 // broadcasts being operands of the multiply-adds (the compiler folds a row
 // broadcast into a product but leaves it a move of its own before a
 // multiply-add). s_nop: a register written by the vector ALU may be read as a
-// row broadcast two cycles later at the earliest.
+// row broadcast two cycles later at the earliest. (&: the sums are written
+// before the last operand is read; without it an operand that starts out equal
+// to a sum is given the sum's own register.)
 template <int NL, int NR, int NT>
 __device__ __forceinline__ void fma_bcast(float (&acc)[NT], float L, float R, const float (&x)[NT],
                                           const float (&y)[NT]) {
@@ -176,17 +178,17 @@ __device__ __forceinline__ void fma_bcast(float (&acc)[NT], float L, float R, co
         asm("s_nop 1\n" FB("%0", "%5", "%11", "%15") FB("%1", "%5", "%12", "%15")
                 FB("%2", "%5", "%13", "%15") FB("%3", "%5", "%14", "%15") FB("%0", "%4", "%7", "%6")
                     FB("%1", "%4", "%8", "%6") FB("%2", "%4", "%9", "%6") FB("%3", "%4", "%10", "%6")
-            : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+            : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3])
             : "v"(L), "v"(R), "n"(NL), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(y[0]),
               "v"(y[1]), "v"(y[2]), "v"(y[3]), "n"(NR));
     else if constexpr (NT == 2)
         asm("s_nop 1\n" FB("%0", "%3", "%7", "%9") FB("%1", "%3", "%8", "%9") FB("%0", "%2", "%5", "%4")
                 FB("%1", "%2", "%6", "%4")
-            : "+v"(acc[0]), "+v"(acc[1])
+            : "+&v"(acc[0]), "+&v"(acc[1])
             : "v"(L), "v"(R), "n"(NL), "v"(x[0]), "v"(x[1]), "v"(y[0]), "v"(y[1]), "n"(NR));
     else
         asm("s_nop 1\n" FB("%0", "%2", "%5", "%6") FB("%0", "%1", "%4", "%3")
-            : "+v"(acc[0])
+            : "+&v"(acc[0])
             : "v"(L), "v"(R), "n"(NL), "v"(x[0]), "v"(y[0]), "n"(NR));
 }
 // v[c] = bcast(p) a[c] + bcast(q) b[c]

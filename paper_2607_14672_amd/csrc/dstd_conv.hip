@@ -576,12 +576,12 @@ constexpr int kFwdWaves = 4;
     "v_fmac_f32_dpp %1, %3, " w " row_newbcast:" q " row_mask:0xf bank_mask:0xf\n"
 template <int Q>
 __device__ __forceinline__ void sum_entry(float &aL, float &aR, float L, float R, float w) {
-    asm("s_nop 1\n" FWD_FMA("%5", "%4") : "+v"(aL), "+v"(aR) : "v"(L), "v"(R), "v"(w), "n"(Q));
+    asm("s_nop 1\n" FWD_FMA("%5", "%4") : "+&v"(aL), "+&v"(aR) : "v"(L), "v"(R), "v"(w), "n"(Q));
 }
 __device__ __forceinline__ void sum_entries4(float &aL, float &aR, float L, float R,
                                              const float *w) {
     asm("s_nop 1\n" FWD_FMA("0", "%4") FWD_FMA("1", "%5") FWD_FMA("2", "%6") FWD_FMA("3", "%7")
-        : "+v"(aL), "+v"(aR)
+        : "+&v"(aL), "+&v"(aR)
         : "v"(L), "v"(R), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
 }
 __device__ __forceinline__ void sum_entries8(float &aL, float &aR, float L, float R,
@@ -589,7 +589,7 @@ __device__ __forceinline__ void sum_entries8(float &aL, float &aR, float L, floa
     static_assert(kCBatch == 8, "one asm operand per entry");
     asm("s_nop 1\n" FWD_FMA("0", "%4") FWD_FMA("1", "%5") FWD_FMA("2", "%6") FWD_FMA("3", "%7")
             FWD_FMA("4", "%8") FWD_FMA("5", "%9") FWD_FMA("6", "%10") FWD_FMA("7", "%11")
-        : "+v"(aL), "+v"(aR)
+        : "+&v"(aL), "+&v"(aR)
         : "v"(L), "v"(R), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]),
           "v"(w[6]), "v"(w[7]));
 }
