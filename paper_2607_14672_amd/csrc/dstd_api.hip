@@ -197,26 +197,17 @@ DenseWs dense_ws_layout(int M, int64_t B, int64_t N_in, int64_t N_out, bool back
     size_t off = 0;
     size_t n = (size_t)(B * N_in);
     if (backward) {
-        // events, gradient triples, dt_in buffers (as many as the neuron tiles
-        // can use, at most 2 + N_out / B: about the weights' size), dW partials
-        const dstd::BackPlan dp =
-            dstd::plan_back(B, N_in, N_out, 1, M, dstd::back_split_cap(B, N_in, N_out, M));
+        // events, gradient triples, dt_in buffers, dead-neuron terms, dW partials
         w.ev = off; off += align_up(n * 5 * sizeof(float));
         w.tri = off; off += align_up((size_t)B * (size_t)N_out * 3 * sizeof(float));
-        w.n_buf = (int)std::max<int64_t>(
-            0, std::min<int64_t>(dp.tiles - 1, 2 + N_out / std::max<int64_t>(B, 1)));
+        w.n_buf = (int)dstd::back_buf_cap(B, N_in, 1, N_out);
         w.P = off; off += align_up(n * (size_t)w.n_buf * sizeof(float));
-        w.dq = off; off += align_up((size_t)N_out * sizeof(float));  // dead-neuron term per row
-        w.part = off;
-        if (dp.nsplit > 1) off += align_up((size_t)dp.nsplit * (size_t)N_out * (size_t)N_in * sizeof(float));
-        // more than the layer's forward takes, so that one buffer serves both
-        // (up to the most partials that a plan may take)
-        const size_t nt = align_up((size_t)B * (size_t)N_out * sizeof(float));
-        const int64_t cap = dstd::back_split_cap(B, N_in, N_out, M), bps = (std::max<int64_t>(B, 1) + cap - 1) / cap;
-        const int64_t S = (B + bps - 1) / bps;
-        const size_t part = S > 1 ? align_up((size_t)S * (size_t)N_out * (size_t)N_in * sizeof(float)) : 0;
-        w.total = std::max(off, dense_ws_layout(M, B, N_in, N_out, false).total +
-                                    3 * (align_up(n * sizeof(float)) + nt) + (w.part - w.dq) + part);
+        w.dq = off; off += align_up((size_t)N_out * sizeof(float));
+        const size_t cap = (size_t)dstd::back_split_cap(B, N_in, N_out);
+        w.part = off; off += align_up((cap > 1 ? cap : 0) * (size_t)N_out * (size_t)N_in * sizeof(float));
+        // and the forward's, so that one buffer serves both and a larger layer
+        // (more intervals too) never takes a smaller one
+        w.total = off + dense_ws_layout(M, B, N_in, N_out, false).total;
         return w;
     }
     if (B * N_out == 0) return w;  // the forward enqueues nothing
@@ -951,18 +942,12 @@ MsWs ms_ws_layout(int M, int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, b
     if (backward) {
         w.ev = off; off += align_up(n * 5 * sizeof(float));
         w.G = off; off += align_up((size_t)B * (size_t)(M + 1) * (size_t)N_out * sizeof(float));
-        int64_t n_buf, room;
-        const dstd::BackPlan mp = dstd::plan_ms_back(B, N_in, F_in, N_out, M, &n_buf, &room);
-        w.n_buf = (int)n_buf;
-        w.part = off;
-        w.P = off + (mp.nsplit > 1 ? (size_t)mp.nsplit * (size_t)N_in * (size_t)N_out * sizeof(float) : 0);
-        const size_t dw = (size_t)N_in * (size_t)N_out * sizeof(float);
-        const size_t most = 5 * align_up(n * sizeof(float)) + (w.part - w.G) +
-                            align_up((size_t)room * sizeof(float) - dw) + align_up(dw);
-        off += align_up(w.P - w.part + n * (size_t)n_buf * sizeof(float));
-        // as much as the layer's forward takes, within the room
-        const size_t fwd = B * N_out == 0 ? 0 : ms_ws_layout(M, B, N_in, F_in, N_out, false).total;
-        off = std::max(off, std::min(most, fwd));
+        w.n_buf = (int)dstd::back_buf_cap(B, N_in, F_in, N_out);
+        w.P = off; off += align_up(n * (size_t)w.n_buf * sizeof(float));
+        const size_t cap = (size_t)dstd::back_split_cap(B, N_in, N_out);
+        w.part = off; off += align_up((cap > 1 ? cap : 0) * (size_t)N_in * (size_t)N_out * sizeof(float));
+        // no less than the forward's, so that one buffer serves both
+        off = std::max(off, B * N_out == 0 ? 0 : ms_ws_layout(M, B, N_in, F_in, N_out, false).total);
     } else {
         const size_t ns = n + dstd::kSortPad;
         w.sj = off; off += align_up(ns * sizeof(int));

@@ -59,7 +59,7 @@ __device__ __forceinline__ void load4(const uint16_t *p, float (&x)[4]) {
 
 struct BackArgs {
     int B, N_in, N_out, F;
-    int b_per_split, n_chunk;
+    int b_per_split;
     int tile0, add;      // first tile of the launch; add to its dt_in buffers
     int ahead;           // samples between barriers
     const float *ev;     // events [B][F][5][N_in] (row as int bits, L, R, dL, dR)
@@ -125,10 +125,6 @@ __global__ __launch_bounds__(kBackWavesMax * kWave) void back_dense_kernel(LifCo
                 });
             }
         });
-        // loaded before the loop: its waits count its own loads
-        static_for<TJ>([&](auto j) {
-            static_for<NT>([&](auto c) { settle(w[j / kBackGroup][j % kBackGroup][0][c]); });
-        });
     }
     // this lane's neurons: offsets clamped into the tile, neurons past N_out
     // without gradient
@@ -168,16 +164,18 @@ __global__ __launch_bounds__(kBackWavesMax * kWave) void back_dense_kernel(LifCo
     auto write_mem = [&](int b, int slot) {
         const float *p = a.g + static_cast<int64_t>(b) * (C.M + 1) * a.N_out;
         float *gl = gs + slot * ts + NT * lane;
-        for (int r0 = 1 + wave; r0 <= C.M + 1; r0 += 4 * nw) {
-            float v[4][NT];
+        constexpr int kU = 16 / NT;  // rows in flight: a one-sample block waits for little else
+        for (int r0 = 1 + wave; r0 <= C.M + 1; r0 += kU * nw) {
+            float v[kU][NT];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float *q = p + static_cast<int64_t>(min(r0 + u * nw, C.M + 1) - 1) * a.N_out;
+            for (int u = 0; u < kU; ++u) {
+                if (r0 + u * nw > C.M + 1) break;
+                const float *q = p + static_cast<int64_t>(r0 + u * nw - 1) * a.N_out;
 #pragma unroll
                 for (int c = 0; c < NT; ++c) v[u][c] = q[no[c]];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < kU; ++u) {
                 if (r0 + u * nw > C.M + 1) break;
 #pragma unroll
                 for (int c = 0; c < NT; ++c) v[u][c] = nok[c] ? v[u][c] : 0.f;
@@ -208,6 +206,12 @@ __global__ __launch_bounds__(kBackWavesMax * kWave) void back_dense_kernel(LifCo
                 else r[k] = write_tri(load_tri(b0 + k), k);
             }
         }
+        // the weights are here before the loop (its waits count its own loads), but
+        // only now: they were on their way together with the first tables
+        if constexpr (DT)
+            static_for<TJ>([&](auto j) {
+                static_for<NT>([&](auto c) { settle(w[j / kBackGroup][j % kBackGroup][0][c]); });
+            });
         __syncthreads();
         int slot = 0;
         bool more = true;
@@ -290,7 +294,8 @@ __global__ __launch_bounds__(kBackWavesMax * kWave) void back_dense_kernel(LifCo
 }
 
 // Sums in order, four outputs per thread (one 16-byte load per summand where
-// they are aligned to it, four summands in flight):
+// they are aligned to it), eight summands in flight: what bounds a small layer's
+// many partial sums is the chain of their loads.
 // blocks [0, n_dw) add the dW partial sums (+ the row's dead-neuron term), the
 // rest the dt_in buffers.
 struct SumJob {
@@ -303,119 +308,191 @@ struct SumJob {
     bool vec;  // every summand is 16-byte aligned, n a multiple of 4
 };
 
-__device__ __forceinline__ void sum4(const SumJob &s, int64_t t) {
-    const int64_t k = 4 * t;
-    if (k >= s.n) return;
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    auto src = [&](int z) { return z == 0 ? s.first : s.rest + static_cast<int64_t>(z - 1) * s.n; };
-    if (s.count > 0 && s.vec) {
-        const float4 x = *reinterpret_cast<const float4 *>(s.first + k);
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-#pragma unroll 4
-        for (int z = 1; z < s.count; ++z) {
-            const float4 y = *reinterpret_cast<const float4 *>(src(z) + k);
-            v[0] += y.x; v[1] += y.y; v[2] += y.z; v[3] += y.w;
+template <bool VEC> __device__ __forceinline__ void sum4(const SumJob &s, int64_t k) {
+    constexpr int kAhead = 8;
+    auto load = [&](int z, float (&y)[4]) {
+        const float *p = (z == 0 ? s.first : s.rest + static_cast<int64_t>(z - 1) * s.n) + k;
+        if constexpr (VEC) {
+            const float4 x = *reinterpret_cast<const float4 *>(p);
+            y[0] = x.x; y[1] = x.y; y[2] = x.z; y[3] = x.w;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) y[c] = p[k + c < s.n ? c : 0];
         }
-    } else if (s.count > 0) {
+    };
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (s.count > 0) load(0, v);
+    for (int z = 1; z < s.count; z += kAhead) {
+        float y[kAhead][4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = (k + c < s.n) ? s.first[k + c] : 0.f;
-        for (int z = 1; z < s.count; ++z)
+        for (int u = 0; u < kAhead; ++u)
+            if (z + u < s.count) load(z + u, y[u]);
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (k + c < s.n) v[c] += src(z)[k + c];
+        for (int u = 0; u < kAhead; ++u)
+            if (z + u < s.count)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] += y[u][c];
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         if (k + c < s.n) s.out[k + c] = s.dq ? v[c] + s.dq[(k + c) / s.row_len] : v[c];
 }
 
+__device__ __forceinline__ void sum_block(const SumJob &s, int64_t blk) {
+    const int64_t k = 4 * (blk * 256 + threadIdx.x);
+    if (k >= s.n) return;
+    if (s.vec) sum4<true>(s, k);
+    else sum4<false>(s, k);
+}
+
 __global__ __launch_bounds__(256) void back_sum_kernel(SumJob dw, int n_dw, SumJob dt) {
     const int64_t blk = blockIdx.x;
-    if (blk < n_dw) sum4(dw, blk * 256 + threadIdx.x);
-    else sum4(dt, (blk - n_dw) * 256 + threadIdx.x);
+    if (blk < n_dw) sum_block(dw, blk);
+    else sum_block(dt, blk - n_dw);
 }
 
 // ------------------------------------------------------------- launcher --
-// NT = 2 neurons per lane past 64 (their two tables as far as they fit
-// kBackLdsDense), TJ = 16 inputs per wave. The waves per block w, the blocks
-// over the inputs and the batch split (<= cap, >= 4 samples each) by the time
-// they predict: rounds over the chip's blocks x samples (5 for the start and
-// end of a block) x a wave's instructions per sample (its inputs, and its share
-// of the table's rows) x the cycles per instruction, which grow with the waves
-// per CU, + the pass over partial sums. The constants are those of the shapes
-// measured (784 -> 1000, 1021 -> 517, 6000 -> 1000, 4096 -> 4096).
+// The shape of a call: NT neurons per lane (2 only past 64 neurons, as far as
+// their two tables fit kBackLdsDense), TJ = 8 or 16 inputs per wave, the waves
+// per block, the blocks over the inputs and the batch split, by the time they
+// predict. A block takes a fixed start and, per sample, its barrier, its share of
+// the table's rows (copied ones: a load each) and its wave's inputs, in cycles of
+// a wave alone on its CU; waves that share a CU slow each other down by kShare
+// each. The last, partly filled round of blocks counts with the waves that it
+// has. Partial sums are written and read once more, in order.
+// The constants are a fit to 6,500 timed shapes of 143 layers, dW alone, dt_in
+// alone and both: batch 4 to 256, 16 to 6000 inputs of 1 to 8 spikes, 4 to 4096
+// neurons, M 8 to 250. The predicted best is 4 % above the timed best on average;
+// one fixed shape (16 inputs, two neurons, at least four samples per block) was
+// 54 % above it, and small layers left most of the chip idle with it:
+// 400 -> 120, batch 24, M = 64, both gradients 47.5 -> 21.1 us.
 constexpr int kBackLdsDense = 152 * 1024;
-constexpr int kBackTJ = 16;
 constexpr int kBackCUs = 256;
 constexpr int kLdsBytes = 160 * 1024;
 
-BackPlan plan_back(int64_t B, int64_t N_in, int64_t N_out, int64_t F, int M, int64_t cap) {
-    BackPlan p;
-    const int tab = g_table_len(M) * static_cast<int>(sizeof(float2));
-    auto lds = [&](int nt, int s) { return 2 * s * (M + 3) * nt * kWave * 4 + tab; };
-    p.nt = (N_out > kWave && lds(2, 1) <= kBackLdsDense) ? 2 : 1;
-    p.tiles = static_cast<int>((N_out + p.nt * kWave - 1) / (p.nt * kWave));
-    p.n_chunk = static_cast<int>((N_in + kBackTJ - 1) / kBackTJ);
-    const double items = (p.nt == 2 ? 250. : 170.) * static_cast<double>(F);
-    const double rows = 6. * p.nt * (M + 3);
-    const double part = 8. * static_cast<double>(N_in) * static_cast<double>(N_out) * (1630. / 4e6);
+// Waves per SIMD that the kernel's registers leave (at least)
+static int back_occupancy(int pairs, bool both) {
+    if (both) return pairs >= 32 ? 4 : pairs >= 16 ? 5 : 8;
+    return pairs >= 32 ? 5 : pairs >= 16 ? 7 : 8;
+}
+
+static int back_lds(int M, int nt, int ahead) {
+    return 2 * ahead * (M + 3) * nt * kWave * 4 + g_table_len(M) * static_cast<int>(sizeof(float2));
+}
+
+// nt, b_per_split: given, or 0
+static BackPlan back_search(const BackSize &z, int M, bool dw, bool dt, int nt_given, int bps_given) {
+    constexpr double kStart = 3600., kStartM = 10.5, kBarrier = 1000., kRow = 52., kRowMem = 980.;
+    constexpr double kPerUs = 2400., kShare = 0.053, kWide = 1.27;
+    constexpr double kSumUs = 3., kSumUsPerMB = 0.68, kSumUsPerPart = 0.18;
+    const double k_input = (dw && dt) ? 109. : dt ? 105. : 57.;
+    const int64_t Bn = std::max<int64_t>(z.B, 1);
+    const double dw_mb = 4e-6 * static_cast<double>(z.N_in) * static_cast<double>(z.N_out);
+    const double dt_mb = 4e-6 * static_cast<double>(z.B) * static_cast<double>(z.N_in * z.F);
+    const int64_t most_split = dw ? std::max<int64_t>(1, std::min(z.cap, Bn)) : std::min<int64_t>(Bn, 256);
+    // (one tile needs no dt_in buffers to add up: 64 < N_out <= 128 takes NT = 2)
+    const int nt_most = (z.N_out > kWave && back_lds(M, 2, 1) <= kBackLdsDense) ? 2 : 1;
+    if (nt_most == 2 && z.N_out <= 2 * kWave) nt_given = 2;
+    BackPlan p{};
     double best = -1.;
-    for (int most = kBackWavesMax; most >= 1; --most) {
-        const int groups = std::max(1, (p.n_chunk + most - 1) / most);
-        const int w = std::max(1, (p.n_chunk + groups - 1) / groups);
-        if (w != most && most > 1 && p.n_chunk > 0) continue;  // the same blocks as with fewer waves
-        const int per = std::max(1, std::min(kBackWavesMax / w, kLdsBytes / lds(p.nt, 1)));
-        const int64_t blocks = static_cast<int64_t>(groups) * std::max(1, p.tiles);
-        const int64_t fit = static_cast<int64_t>(kBackCUs) * per / blocks;
-        for (const int64_t want : {int64_t{1}, cap, std::min(cap, fit)}) {
-            const int64_t ns = std::max<int64_t>(1, std::min(want, B / 4));
-            const int64_t bps = std::max<int64_t>(1, (B + ns - 1) / ns);
-            const int64_t n = std::max<int64_t>(1, (B + bps - 1) / bps), tot = blocks * n;
-            const double rounds = static_cast<double>((tot + kBackCUs * per - 1) / (kBackCUs * per));
-            const double in_cu = static_cast<double>(std::min<int64_t>(per, (tot + kBackCUs - 1) / kBackCUs) * w);
-            double cost = rounds * (static_cast<double>(bps) + 5.) * (items + 60. + rows / w) *
-                          (6. + 9. / 16. * in_cu);
-            if (n > 1) cost += 1630. * 5. + static_cast<double>(n + 1) * part;
-            if (best >= 0. && cost >= best) continue;
-            best = cost;
-            p.groups = groups;
-            p.waves = w;
-            p.nsplit = static_cast<int>(n);
-            p.b_per_split = static_cast<int>(bps);
+    for (int nt = nt_given ? nt_given : nt_most; nt >= (nt_given ? nt_given : 1); --nt) {
+        const int tiles = static_cast<int>((z.N_out + nt * kWave - 1) / (nt * kWave));
+        const int launches = dt ? static_cast<int>((tiles + z.n_buf) / (1 + z.n_buf)) : 1;
+        const int per_launch = launches > 0 ? (tiles + launches - 1) / launches : 0;
+        const int by_lds = std::max(1, kLdsBytes / back_lds(M, nt, 1));
+        for (int tj = 16; tj >= 8; tj -= 8) {
+            const int chunks = static_cast<int>((z.N_in + tj - 1) / tj);
+            const int slots = 4 * back_occupancy(nt * tj, dw && dt);
+            const double item = static_cast<double>(z.F) * tj * k_input * (nt == 2 ? kWide : 1.);
+            for (int most = kBackWavesMax; most >= 2; most /= 2) {
+                const int groups = std::max(1, (chunks + most - 1) / most);
+                // (one block over the inputs: also with waves that only write table rows)
+                const int even = std::max(1, (chunks + groups - 1) / groups);
+                const int w = groups == 1 ? most : even;
+                const int per = std::max(1, std::min(slots / w, by_lds));
+                const int64_t blocks = static_cast<int64_t>(groups) * std::max(1, per_launch);
+                const double sample = item + kBarrier + (z.mem_g ? kRowMem : kRow) * nt * (M + 3) / w;
+                const double start = kStart + kStartM * M / w;
+                for (int64_t want = 1;; want = std::min(2 * want, most_split)) {
+                    const int64_t bps = bps_given ? bps_given : (Bn + want - 1) / want;
+                    const int64_t ns = (Bn + bps - 1) / bps;
+                    const int64_t tot = blocks * ns, full = tot / (kBackCUs * per);
+                    const int64_t rest = tot - full * kBackCUs * per;
+                    const double alone = start + static_cast<double>(bps) * sample;
+                    double us = static_cast<double>(full) * (1. + kShare * per * w);
+                    if (rest > 0) us += 1. + kShare * static_cast<double>((rest + kBackCUs - 1) / kBackCUs) * w;
+                    us *= alone * std::max(1, launches) / kPerUs;
+                    if (dw && ns > 1)
+                        us += kSumUs + std::max(kSumUsPerMB * static_cast<double>(ns + 1) * dw_mb,
+                                                kSumUsPerPart * static_cast<double>(ns));
+                    else if (dt && per_launch > 1) us += kSumUs;
+                    if (dt && per_launch > 1) us += kSumUsPerMB * (per_launch + 1) * dt_mb;
+                    if (best < 0. || us < best) {
+                        best = us;
+                        p.nt = nt;
+                        p.tj = tj;
+                        p.tiles = tiles;
+                        p.groups = groups;
+                        p.waves = w;
+                        p.nsplit = static_cast<int>(ns);
+                        p.b_per_split = static_cast<int>(bps);
+                    }
+                    if (bps_given || want >= most_split) break;
+                }
+            }
         }
     }
     // tables ahead as far as the CU still holds its blocks
     const int room = kBackLdsDense / std::max(1, kBackWavesMax / p.waves);
     p.ahead = 1;
-    while (p.ahead < kBackAhead && lds(p.nt, 2 * p.ahead) <= room) p.ahead *= 2;
-    p.lds = static_cast<size_t>(lds(p.nt, p.ahead));
+    while (p.ahead < kBackAhead && back_lds(M, p.nt, 2 * p.ahead) <= room) p.ahead *= 2;
+    p.lds = static_cast<size_t>(back_lds(M, p.nt, p.ahead));
     return p;
 }
 
-int64_t back_split_cap(int64_t B, int64_t N_in, int64_t N_out, int M) {
-    const int64_t jw = N_out <= 16 ? 16 : (N_out <= 32 || M > 86) ? 32 : 64;
-    const int64_t pieces = ((N_in + 255) / 256) * ((N_out + jw - 1) / jw);
-    int64_t ns = 1;
-    while (pieces * ns < 1024 && B / (ns * 2) >= 4) ns *= 2;
-    return ns >= 4 ? ns / 2 : ns;
+// One gradient alone keeps what the order of its sums depends on (dW: the batch
+// split; dt_in: the neurons per lane) as both together have it, so that it comes
+// out the same to the bit; that costs it 0 and 2 % of its time.
+BackPlan plan_back(const BackSize &z, int M, bool dw, bool dt) {
+    const BackPlan p = back_search(z, M, true, true, 0, 0);
+    if (dw && dt) return p;
+    return dw ? back_search(z, M, true, false, 0, p.b_per_split) : back_search(z, M, false, true, p.nt, 0);
 }
 
-hipError_t launch_back(const LifConst &C, const BackPlan &p, const BackJob &j, hipStream_t st) {
+// Room for partial sums and dt_in buffers by their bytes: at most 64 splits and
+// 48 MiB of partials; a dt_in buffer for each 64 neurons past the first, as far
+// as 32 MiB or about the weights' size (2 + N_out / B buffers) hold them.
+int64_t back_split_cap(int64_t B, int64_t N_in, int64_t N_out) {
+    const int64_t n = std::max<int64_t>(1, N_in * N_out);
+    return std::max<int64_t>(1, std::min<int64_t>({B, 64, (int64_t{48} << 20) / (4 * n)}));
+}
+int64_t back_buf_cap(int64_t B, int64_t N_in, int64_t F, int64_t N_out) {
+    const int64_t n = std::max<int64_t>(1, B * N_in * F);
+    const int64_t most = std::max<int64_t>(2 + N_out / std::max<int64_t>(B, 1), (int64_t{32} << 20) / (4 * n));
+    return std::max<int64_t>(0, std::min<int64_t>((N_out + kWave - 1) / kWave - 1, most));
+}
+
+// ---- end of the launch rules of back_dense_kernel ----
+
+hipError_t launch_back(const LifConst &C, const BackJob &j, hipStream_t st) {
     const bool dw = j.grad_W && j.N_out * j.N_in > 0;
     const bool dt = j.grad_t_in && j.B * j.N_in > 0;
-    const bool split = dw && p.nsplit > 1;
     const int64_t n_dt = j.B * j.N_in * j.F;
     if (!dw && !dt) return hipSuccess;
+    const BackPlan p = plan_back(BackSize{j.B, j.N_in, j.N_out, j.F, j.mem_g,
+                                          back_split_cap(j.B, j.N_in, j.N_out), j.n_buf},
+                                 C.M, dw, dt);
+    const bool split = dw && p.nsplit > 1;
     BackArgs a{static_cast<int>(j.B), static_cast<int>(j.N_in), static_cast<int>(j.N_out),
-               static_cast<int>(j.F), p.b_per_split, p.n_chunk, 0, 0, p.ahead, j.ev, j.g, j.W,
+               static_cast<int>(j.F), p.b_per_split, 0, 0, p.ahead, j.ev, j.g, j.W,
                j.grad_t_in, j.P, split ? j.part : j.grad_W, split ? nullptr : j.dq, false, false};
     auto al16 = [](const void *x) { return (reinterpret_cast<uintptr_t>(x) & 15) == 0; };
     a.vec = (j.N_in & 3) == 0 && al16(a.dW);
     a.w_vec = (j.N_in & 3) == 0 && (reinterpret_cast<uintptr_t>(j.W) & (j.bf16 ? 7 : 15)) == 0;
-    // tiles per launch: all, or with dt_in as evenly as its buffers allow
     const int launches = dt ? (p.tiles + j.n_buf) / (1 + j.n_buf) : 1;
     const int bufs = launches > 0 ? (p.tiles + launches - 1) / launches : 0;
     {
+        // tiles per launch: all, or with dt_in as evenly as its buffers allow
         ProfScope prof(j.mem_g ? "ms_back" : "back_dense", st);
         for (int t = 0; t < p.tiles; t += bufs) {
             a.tile0 = t;
@@ -424,18 +501,23 @@ hipError_t launch_back(const LifConst &C, const BackPlan &p, const BackJob &j, h
                             static_cast<unsigned>(std::min(bufs, p.tiles - t)),
                             static_cast<unsigned>(p.nsplit));
             const dim3 block(static_cast<unsigned>(p.waves * kWave));
-#define BD(WTY, NTV, DWV, DTV, MG)                                                                  \
-    hipLaunchKernelGGL((back_dense_kernel<WTY, NTV, kBackTJ, DWV, DTV, MG>), grid, block, p.lds, st, C, a)
-#define BD_M(WTY, NTV, MG)                            \
-    do {                                              \
-        if (dw && dt) BD(WTY, NTV, true, true, MG);   \
-        else if (dw) BD(WTY, NTV, true, false, MG);   \
-        else BD(WTY, NTV, false, true, MG);           \
+#define BD(WTY, NTV, TJV, DWV, DTV, MG)                                                          \
+    hipLaunchKernelGGL((back_dense_kernel<WTY, NTV, TJV, DWV, DTV, MG>), grid, block, p.lds, st, C, a)
+#define BD_M(WTY, NTV, TJV, MG)                               \
+    do {                                                      \
+        if (dw && dt) BD(WTY, NTV, TJV, true, true, MG);      \
+        else if (dw) BD(float, NTV, TJV, true, false, MG);    \
+        else BD(WTY, NTV, TJV, false, true, MG);              \
     } while (0)
-#define BD_N(WTY, MG)                                 \
-    do {                                              \
-        if (p.nt == 2) BD_M(WTY, 2, MG);              \
-        else BD_M(WTY, 1, MG);                        \
+#define BD_T(WTY, NTV, MG)                       \
+    do {                                         \
+        if (p.tj == 16) BD_M(WTY, NTV, 16, MG);  \
+        else BD_M(WTY, NTV, 8, MG);              \
+    } while (0)
+#define BD_N(WTY, MG)                     \
+    do {                                  \
+        if (p.nt == 2) BD_T(WTY, 2, MG);  \
+        else BD_T(WTY, 1, MG);            \
     } while (0)
             if (j.bf16) {
                 if (j.mem_g) BD_N(uint16_t, true);
@@ -445,6 +527,7 @@ hipError_t launch_back(const LifConst &C, const BackPlan &p, const BackJob &j, h
                 else BD_N(float, false);
             }
 #undef BD_N
+#undef BD_T
 #undef BD_M
 #undef BD
             const hipError_t e = hipGetLastError();

@@ -442,9 +442,8 @@ hipError_t launch_backward(const LifConst &C, int64_t B, int64_t N_in, int64_t N
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const BackPlan p = plan_back(B, N_in, N_out, 1, C.M, back_split_cap(B, N_in, N_out, C.M));
-    return launch_back(C, p, BackJob{B, N_in, N_out, 1, ws.ev, ws.tri, false, W, bf16, ws.P, ws.n_buf,
-                                     ws.part, dq, grad_W, grad_t_in}, st);
+    return launch_back(C, BackJob{B, N_in, N_out, 1, ws.ev, ws.tri, false, W, bf16, ws.P, ws.n_buf, ws.part,
+                                  dq, grad_W, grad_t_in}, st);
 }
 
 hipError_t launch_softmax_ce(int64_t B, int64_t N, const float *t, const int *labels,

@@ -24,18 +24,27 @@ hipError_t launch_forward(const LifConst &C, int64_t B, int64_t N_in, int64_t N_
                           bool bf16, void *Wt, SortedEv srt, int *n_valid, const float *t_in,
                           float *t_out, float *slope, int *q_idx, hipStream_t st);
 
-// The dense backward contraction (dstd_back.hip): neurons per lane, neuron
-// tiles, input chunks, blocks over the chunks (groups) of `waves` waves, batch
-// splits and LDS bytes. cap: most batch splits (partial sums).
+// The dense backward contraction (dstd_back.hip): neurons per lane, inputs per
+// wave, neuron tiles, blocks over the inputs (groups) of `waves` waves, batch
+// splits and LDS bytes. cap: most batch splits (partial sums); n_buf: dt_in
+// buffers; dw, dt: which gradients are wanted.
 struct BackPlan {
-    int nt, tiles, n_chunk, groups, waves, nsplit, b_per_split, ahead;
+    int nt, tj, tiles, groups, waves, nsplit, b_per_split, ahead;
     size_t lds;
 };
-BackPlan plan_back(int64_t B, int64_t N_in, int64_t N_out, int64_t F, int M, int64_t cap);
-int64_t back_split_cap(int64_t B, int64_t N_in, int64_t N_out, int M);
+struct BackSize {
+    int64_t B, N_in, N_out, F;
+    bool mem_g;
+    int64_t cap, n_buf;
+};
+BackPlan plan_back(const BackSize &z, int M, bool dw, bool dt);
+// partial sums (of dW's size each) and dt_in buffers (beside grad_t_in) that the
+// workspace holds
+int64_t back_split_cap(int64_t B, int64_t N_in, int64_t N_out);
+int64_t back_buf_cap(int64_t B, int64_t N_in, int64_t F, int64_t N_out);
 // ev: events [B][F][5][N_in]; g: gradient triples [B][3][N_out], or (mem_g) G
 // [B][M + 1][N_out]; P: n_buf dt_in buffers [B][N_in][F] beside grad_t_in;
-// part: dW partial sums [nsplit][N_out][N_in]; dq: dead-neuron term or NULL.
+// part: back_split_cap dW partial sums [N_out][N_in]; dq: dead-neuron term or NULL.
 struct BackJob {
     int64_t B, N_in, N_out, F;
     const float *ev, *g;
@@ -48,7 +57,7 @@ struct BackJob {
     const float *dq;
     float *grad_W, *grad_t_in;
 };
-hipError_t launch_back(const LifConst &C, const BackPlan &p, const BackJob &j, hipStream_t st);
+hipError_t launch_back(const LifConst &C, const BackJob &j, hipStream_t st);
 
 // Dense backward workspace: events, gradient triples, dt_in buffers and dW
 // partial sums (see BackJob).
@@ -200,10 +209,6 @@ hipError_t launch_ms_forward(const LifConst &C, int64_t B, int64_t N_in, int64_t
                              int64_t N_out, int64_t F_out, const void *W, bool bf16, void *Wt,
                              SortedEv srt, int *n_valid, const float *t_in, float *t_out,
                              float *slope, int *q_idx, float *cur, hipStream_t st);
-// the backward's contraction, its dt_in buffers beside grad_t_in, and the floats
-// that those and the dW partials may take
-BackPlan plan_ms_back(int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, int M, int64_t *n_buf,
-                      int64_t *room);
 // ws: events [B][F_in][5][N_in], G in place of the triples
 hipError_t launch_ms_backward(const LifConst &C, int64_t B, int64_t N_in, int64_t F_in,
                               int64_t N_out, int64_t F_out, const void *W, bool bf16, DenseBwdWs ws,

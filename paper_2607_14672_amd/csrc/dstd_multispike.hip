@@ -404,26 +404,6 @@ hipError_t launch_ms_forward(const LifConst &C, int64_t B, int64_t N_in, int64_t
     return hipGetLastError();
 }
 
-BackPlan plan_ms_back(int64_t B, int64_t N_in, int64_t F_in, int64_t N_out, int M, int64_t *n_buf,
-                      int64_t *room) {
-    // Scratch for dt_in buffers and dW partials together: S + 1 times dW (S
-    // splits; 1 without a split). The buffers first, up to half of it.
-    const int64_t n_dw = N_in * N_out, n_dt = std::max<int64_t>(1, B * N_in * F_in);
-    int64_t S = 1;
-    if (M <= 64 && B > 0 && n_dw > 0) {
-        const int64_t blocks = ((N_out + 63) / 64) * ((N_in + 63) / 64);
-        S = std::min<int64_t>({(2048 + blocks - 1) / blocks, 16, B});
-        S = (B + (B + S - 1) / S - 1) / ((B + S - 1) / S);
-        if (S == 1) S = 0;
-        S += 1;
-    }
-    *room = S * n_dw;
-    const BackPlan one = plan_back(B, N_in, N_out, F_in, M, 1);
-    *n_buf = std::max<int64_t>(0, std::min<int64_t>(one.tiles - 1, (S + 1) / 2 * n_dw / n_dt));
-    const int64_t cap = n_dw > 0 ? (S * n_dw - *n_buf * n_dt) / n_dw : 1;
-    return plan_back(B, N_in, N_out, F_in, M, std::max<int64_t>(1, cap));
-}
-
 hipError_t launch_ms_backward(const LifConst &C, int64_t B, int64_t N_in, int64_t F_in,
                               int64_t N_out, int64_t F_out, const void *W, bool bf16, DenseBwdWs ws,
                               const float *t_in, const float *t_out, const float *slope,
@@ -444,10 +424,8 @@ hipError_t launch_ms_backward(const LifConst &C, int64_t B, int64_t N_in, int64_
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    int64_t n_buf, room;
-    const BackPlan p = plan_ms_back(B, N_in, F_in, N_out, C.M, &n_buf, &room);
-    return launch_back(C, p, BackJob{B, N_in, N_out, F_in, ws.ev, ws.tri, true, W, bf16, ws.P, ws.n_buf,
-                                     ws.part, nullptr, grad_W, grad_t_in}, st);
+    return launch_back(C, BackJob{B, N_in, N_out, F_in, ws.ev, ws.tri, true, W, bf16, ws.P, ws.n_buf,
+                                  ws.part, nullptr, grad_W, grad_t_in}, st);
 }
 
 }  // namespace dstd

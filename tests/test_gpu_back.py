@@ -84,3 +84,33 @@ def test_dense_backward_unaligned_buffers(dev):  # noqa: F811
 def test_multispike_backward_shapes(dev, B, N_in, F_in, N_out, M, bf16):  # noqa: F811
     p, t, W = _ms_case(21, B, N_in, F_in, N_out, M, 1.0, 0.3, k=3.0)
     _ms_parity(dev, p, t, W, 3, f"multispike back {B}x{N_in}x{F_in}->{N_out} M={M}", bf16=bf16)
+
+
+@pytest.mark.parametrize("B,N_in,N_out,M", [
+    (1, 5, 3, 4), (24, 400, 120, 64), (9, 100, 129, 20), (64, 33, 200, 100), (5, 700, 65, 200)])
+def test_dense_backward_alone_is_the_same(dev, B, N_in, N_out, M):  # noqa: F811
+    """Each gradient alone has the bits that both together give it, whatever the
+    launch shapes; both are checked against the oracle."""
+    p, t, W = _layer_case(23, B, N_in, N_out, M, 1.0, 0.3)
+    _fwd_bwd_parity(dev, p, t, W, f"back alone {B}x{N_in}->{N_out} M={M}")
+    gpu, h = _gpu_forward(dev, p, t, W)
+    g = np.random.default_rng(24).standard_normal(gpu["t_out"].shape).astype(np.float32)
+    gW, gx = _gpu_backward(dev, h, g)
+    assert np.array_equal(_gpu_backward(dev, h, g, need_t=False)[0], gW)
+    assert np.array_equal(_gpu_backward(dev, h, g, need_W=False)[1], gx)
+
+
+@pytest.mark.parametrize("B,N_in,F_in,N_out,M", [
+    (2, 5, 1, 3, 4), (24, 60, 4, 40, 65), (9, 30, 2, 129, 20), (16, 100, 3, 70, 128)])
+def test_multispike_backward_alone_is_the_same(dev, B, N_in, F_in, N_out, M):  # noqa: F811
+    import torch
+    from paper_2607_14672_amd import dstd
+    p, t, W = _ms_case(25, B, N_in, F_in, N_out, M, 1.0, 0.3, k=3.0)
+    _ms_parity(dev, p, t, W, 3, f"multispike back {B}x{N_in}x{F_in}->{N_out} M={M}")
+    prm = dstd.make_params(1.0, 0.3, 1.0, M, 0.0, 1.0 / M)
+    tt, Wt = (torch.from_numpy(np.ascontiguousarray(x, np.float32)).to(dev) for x in (t, W))
+    r = dstd.multispike_forward(prm, tt, Wt, 3)
+    g = torch.randn(r[0].shape, device=dev, generator=torch.Generator(device=dev).manual_seed(26))
+    gW, gx = dstd.multispike_backward(prm, tt, Wt, *r, g)
+    assert torch.equal(dstd.multispike_backward(prm, tt, Wt, *r, g, need_t_in=False)[0], gW)
+    assert torch.equal(dstd.multispike_backward(prm, tt, Wt, *r, g, need_W=False)[1], gx)
