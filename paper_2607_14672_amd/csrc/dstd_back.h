@@ -83,8 +83,8 @@ template <int NT> __device__ __forceinline__ void lds_put(float *p, const float 
 
 // rows 1 .. r_end + 1 of one sample's G (row 0 is zero for good), wave w of nw
 // taking rows 1 + w, 1 + w + nw, ..., four at a time (their table reads in
-// flight together); gl = the table + NT * lane
-template <int NT>
+// flight together); gl = the table + NT * lane, its rows kRow floats apart
+template <int NT, int kRow = NT * kWave>
 __device__ __forceinline__ void g_rows(int M, const float2 *tab, const GTri<NT> &t, int r_end,
                                        int w, int nw, float *gl) {
     for (int r0 = 1 + w; r0 <= r_end + 1; r0 += 4 * nw) {
@@ -105,7 +105,7 @@ __device__ __forceinline__ void g_rows(int M, const float2 *tab, const GTri<NT> 
                 const float x = fmaf(t.gK[c], e[u][c].x, t.gE[c] * e[u][c].y);
                 v[c] = (t.q[c] >= r - 1) ? x : 0.f;
             }
-            lds_put<NT>(gl + r * (NT * kWave), v);
+            lds_put<NT>(gl + r * kRow, v);
         }
     }
 }

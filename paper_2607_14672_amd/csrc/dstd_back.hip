@@ -293,6 +293,117 @@ __global__ __launch_bounds__(kBackWavesMax * kWave) void back_dense_kernel(LifCo
     }
 }
 
+// dW alone with lanes = inputs: a block takes 256 * IPT inputs and 64 neurons,
+// a thread IPT inputs and all the tile's sums. Against the kernel above, whose
+// two LDS reads per input and lane are covered by the dt_in products only if
+// there are any: a thread reads four neurons of a row at a time, and lanes whose
+// inputs have the same event row read the same words at once (few intervals:
+// most of them). G of the next sample goes to the other of two tables meanwhile.
+// Same sums in the same order. Bound: LDS reads.
+constexpr int kDwIn = 256;
+constexpr int kDwRow = kWave + 4;  // a row's floats: 16-byte reads, neighbouring rows 4 banks apart
+template <int IPT>
+__global__ __launch_bounds__(kDwIn) void back_dw_kernel(LifConst C, BackArgs a) {
+    extern __shared__ float gs[];  // G [2][R + 1][kDwRow], pairs (a_d, k_d)
+    const int R = rows_of(C);
+    const int ts = (R + 1) * kDwRow;
+    float2 *tab = reinterpret_cast<float2 *>(gs + 2 * ts);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = uniform(threadIdx.x >> 6);
+    const int jb = static_cast<int>(blockIdx.x) * kDwIn * IPT + static_cast<int>(threadIdx.x);
+    const int i0 = static_cast<int>(blockIdx.y) * kWave;
+    const int b0 = static_cast<int>(blockIdx.z) * a.b_per_split;
+    const int b1 = min(a.B, b0 + a.b_per_split);
+    // row 0 holds no grid point; rows R - 1 and R are zero for inputs without
+    // events (or past the last spike)
+    for (int k = threadIdx.x; k < 2 * kDwRow; k += kDwIn) {
+        float *t = gs + (k / kDwRow) * ts + k % kDwRow;
+        t[0] = 0.f;
+        t[(R - 1) * kDwRow] = 0.f;
+        t[R * kDwRow] = 0.f;
+    }
+    g_table_fill(C, tab);
+    float acc[IPT][kWave];
+#pragma unroll
+    for (int k = 0; k < IPT; ++k)
+#pragma unroll
+        for (int i = 0; i < kWave; ++i) acc[k][i] = 0.f;
+    const unsigned no = static_cast<unsigned>(min(i0 + lane, a.N_out - 1));
+    const bool nok = i0 + lane < a.N_out;
+    auto load_tri = [&](int b) {
+        const float *p = a.g + static_cast<int64_t>(min(b, a.B - 1)) * 3 * a.N_out;
+        GTri<1> t;
+        t.gK[0] = p[no];
+        t.gE[0] = (p + a.N_out)[no];
+        t.q[0] = __float_as_int((p + 2 * a.N_out)[no]);
+        return t;
+    };
+    auto write_tri = [&](GTri<1> t, int slot) {
+        t.gK[0] = nok ? t.gK[0] : 0.f;
+        t.gE[0] = nok ? t.gE[0] : 0.f;
+        t.q[0] = nok ? t.q[0] : -1;
+        const int top = min(R - 2, wave_max(t.q[0]) + 1);
+        if (top <= 0) return -1;
+        g_rows<1, kDwRow>(C.M, tab, t, top, wave, kDwIn / kWave, gs + slot * ts + lane);
+        return top;
+    };
+    struct Ev { int row[IPT]; float L[IPT], R[IPT]; };
+    auto load_ev = [&](int b) {
+        const float *p = a.ev + static_cast<int64_t>(min(b, a.B - 1)) * kEvFields * a.N_in;
+        Ev e;
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+            const unsigned j = static_cast<unsigned>(min(jb + k * kDwIn, a.N_in - 1));
+            e.row[k] = __float_as_int(p[j]);
+            e.L[k] = (p + a.N_in)[j];
+            e.R[k] = (p + 2 * static_cast<int64_t>(a.N_in))[j];
+        }
+        return e;
+    };
+    if (b0 < b1) {
+        Ev ev = load_ev(b0);
+        int top = write_tri(load_tri(b0), 0);
+        GTri<1> tri = load_tri(b0 + 1);
+        __syncthreads();
+        for (int b = b0; b < b1; ++b) {
+            const Ev next = load_ev(b + 1);
+            const int cur = (b - b0) & 1;
+            int top_n = -1;
+            if (b + 1 < b1) top_n = write_tri(tri, cur ^ 1);
+            tri = load_tri(b + 2);
+            if (top >= 0) {
+#pragma unroll
+                for (int k = 0; k < IPT; ++k) {
+                    const bool on = static_cast<unsigned>(ev.row[k]) <= static_cast<unsigned>(top);
+                    const float L = on ? ev.L[k] : 0.f, Rv = on ? ev.R[k] : 0.f;
+                    const float4 *p = reinterpret_cast<const float4 *>(gs + cur * ts + (on ? ev.row[k] : R - 1) * kDwRow);
+#pragma unroll
+                    for (int i = 0; i < kWave; i += 4) {
+                        const float4 x = p[i / 4], y = p[(i + kDwRow) / 4];
+                        acc[k][i] = fmaf(L, x.x, fmaf(Rv, y.x, acc[k][i]));
+                        acc[k][i + 1] = fmaf(L, x.y, fmaf(Rv, y.y, acc[k][i + 1]));
+                        acc[k][i + 2] = fmaf(L, x.z, fmaf(Rv, y.z, acc[k][i + 2]));
+                        acc[k][i + 3] = fmaf(L, x.w, fmaf(Rv, y.w, acc[k][i + 3]));
+                    }
+                }
+            }
+            ev = next;
+            top = top_n;
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+        const int j = jb + k * kDwIn;
+        if (j >= a.N_in) continue;
+        float *o = a.dW + (static_cast<int64_t>(blockIdx.z) * a.N_out + i0) * a.N_in + j;
+#pragma unroll
+        for (int i = 0; i < kWave; ++i)
+            if (i0 + i < a.N_out)
+                o[static_cast<int64_t>(i) * a.N_in] = a.dq ? acc[k][i] + a.dq[i0 + i] : acc[k][i];
+    }
+}
+
 // Sums in order, four outputs per thread (one 16-byte load per summand where
 // they are aligned to it), eight summands in flight: what bounds a small layer's
 // many partial sums is the chain of their loads.
@@ -474,6 +585,27 @@ int64_t back_buf_cap(int64_t B, int64_t N_in, int64_t F, int64_t N_out) {
 
 // ---- end of the launch rules of back_dense_kernel ----
 
+// dW alone (TTFS layer): inputs or neurons along the lanes? back_dw_kernel from
+// 2.5 million pairs over the batch, 96 inputs, and as far as a CU holds two of its
+// blocks (M <= 128); two inputs per thread where that still leaves two blocks per
+// CU, and the table's rows are many enough to be worth sharing. back_dense_kernel
+// -> back_dw_kernel, prep and sums with it:
+//   4096 -> 4096, batch 256, M = 8, 32, 64, 128   891, 1010, 1105, 1418 -> 427, 593, 713, 918 us
+//     (one input per thread                       427, 618, 767, 1337)
+//   6000 -> 1000, batch 100 203 -> 131; 784 -> 1000, batch 128 63 -> 49 (two inputs: 55)
+//   below the line: 24 x 400 -> 120 19.9 -> 21.0, 8 x 784 -> 100 18.0 -> 18.8
+static size_t dw_lds(int M) {
+    return 2 * static_cast<size_t>(M + 4) * kDwRow * sizeof(float) +
+           static_cast<size_t>(g_table_len(M)) * sizeof(float2);
+}
+static bool dw_by_input(const BackJob &j, int M) {
+    return !j.mem_g && M <= 128 && j.N_in >= 96 && j.B * j.N_in * j.N_out >= 2500000;
+}
+static int dw_ipt(const BackJob &j, int M, int nsplit) {
+    const int64_t blocks = ((j.N_in + 2 * kDwIn - 1) / (2 * kDwIn)) * ((j.N_out + kWave - 1) / kWave) * nsplit;
+    return (M >= 16 && blocks >= 2 * kBackCUs) ? 2 : 1;
+}
+
 hipError_t launch_back(const LifConst &C, const BackJob &j, hipStream_t st) {
     const bool dw = j.grad_W && j.N_out * j.N_in > 0;
     const bool dt = j.grad_t_in && j.B * j.N_in > 0;
@@ -491,7 +623,17 @@ hipError_t launch_back(const LifConst &C, const BackJob &j, hipStream_t st) {
     a.w_vec = (j.N_in & 3) == 0 && (reinterpret_cast<uintptr_t>(j.W) & (j.bf16 ? 7 : 15)) == 0;
     const int launches = dt ? (p.tiles + j.n_buf) / (1 + j.n_buf) : 1;
     const int bufs = launches > 0 ? (p.tiles + launches - 1) / launches : 0;
-    {
+    if (dw && !dt && dw_by_input(j, C.M)) {
+        ProfScope prof("back_dw", st);
+        const int ipt = dw_ipt(j, C.M, p.nsplit);
+        const dim3 grid(static_cast<unsigned>((j.N_in + kDwIn * ipt - 1) / (kDwIn * ipt)),
+                        static_cast<unsigned>((j.N_out + kWave - 1) / kWave),
+                        static_cast<unsigned>(p.nsplit));
+        if (ipt == 2) hipLaunchKernelGGL((back_dw_kernel<2>), grid, dim3(kDwIn), dw_lds(C.M), st, C, a);
+        else hipLaunchKernelGGL((back_dw_kernel<1>), grid, dim3(kDwIn), dw_lds(C.M), st, C, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    } else {
         // tiles per launch: all, or with dt_in as evenly as its buffers allow
         ProfScope prof(j.mem_g ? "ms_back" : "back_dense", st);
         for (int t = 0; t < p.tiles; t += bufs) {
