@@ -198,3 +198,23 @@ def test_multispike_bench_size_sampled(dev, F_in, F_out):
                kappa=MS_KAPPA)
     others = np.setdiff1d(np.arange(B), rows)
     assert not gxs[others].any()
+
+
+@pytest.mark.parametrize("M,F_out,k", [(1, 2, 3.0), (4, 2, 3.0), (5, 12, 9.0), (33, 12, 6.0), (131, 3, 3.0)])
+def test_multispike_set_up_row_shares(dev, M, F_out, k):
+    """A small layer shares a neuron's rows of G out over threads, a batch of
+    134,000 neurons does not: the same samples get the same bits (fewer rows than
+    a share, one row more, neurons of more than eight spikes, a ragged last share)."""
+    import torch
+    from paper_2607_14672_amd import dstd
+    p, t, W = _case(9, 3, 20, 2, 67, M, 1.0, 0.3, k=k)
+    prm = dstd.make_params(p["tau_m"], p["tau_s"], p["threshold"], p["M"], p["t0"], p["dt"])
+    tt, Wt = torch.from_numpy(t).to(dev), torch.from_numpy(W).to(dev)
+    big = tt.repeat(667, 1, 1)[:2000].contiguous()
+    r, rb = dstd.multispike_forward(prm, tt, Wt, F_out), dstd.multispike_forward(prm, big, Wt, F_out)
+    assert all(torch.equal(a, b[:3]) for a, b in zip(r, rb))
+    gen = torch.Generator(device=dev).manual_seed(10)
+    g = torch.randn(rb[0].shape, device=dev, generator=gen)
+    gx = dstd.multispike_backward(prm, tt, Wt, *r, g[:3].contiguous(), need_W=False)[1]
+    gb = dstd.multispike_backward(prm, big, Wt, *rb, g, need_W=False)[1]
+    assert bool(gx.any()) and torch.equal(gx, gb[:3])
