@@ -320,9 +320,7 @@ ConvWs conv_ws_layout(int M, const dstd::ConvGeom &g, int64_t B, bool backward) 
     w.R = off; off += align_up(nr * sizeof(float));
     w.off = off; off += align_up((size_t)B * g.Hp * (size_t)dstd::conv_off_stride(R, g) * sizeof(int));
     if (backward) {
-        // (scalar loads of an input group may run a few slots past the events,
-        // into the arrays after them)
-        const dstd::ConvBackPlan dp = dstd::plan_conv_back(g, B, M);
+        const dstd::ConvBackPlan dp = dstd::plan_conv_back(g, B, M, true, true);
         w.ev = off; off += align_up(n * 5 * sizeof(float));
         w.P = off; off += align_up(n * (size_t)(g.KH * dp.kg * dp.tiles_dt) * sizeof(float));
         w.crlive = off; off += align_up((size_t)B * g.Hp * sizeof(int));

@@ -1996,51 +1996,114 @@ hipError_t launch_conv_forward(const LifConst &C, const ConvGeom &g, int64_t B, 
     return hipGetLastError();
 }
 
-// The shape of the backward contraction. KWT = 3 taps per wave for kernels
-// wider than 1 at stride 1 (a 5- or 7-wide kernel row takes 2 or 3 such groups),
-// as far as its four G tables of 64 channels fit kBackLds; else 1.
-// NT = 2 channels per lane for layers of more than 64, where those fit too.
-// KWT NT TJ = 48 pairs per lane (32 with one tap): their sums and weights take
-// two thirds of the 168 registers that three waves per SIMD leave; 8 inputs per
-// wave where a tap has no more. Blocks of up to 12 waves, evenly filled (the
-// more inputs share a position's table the better), and splits of the output
-// rows for two blocks and 16 waves per CU, with >= 16 positions per split and bounded
-// partial sums: 64 MiB, and 1024 pieces of 256 (tap, input) rows x 64 channels
-// (32 for narrow layers and long grids).
+// The shape of the backward contraction: KWT = 3 taps per wave (kernels wider
+// than 1 at stride 1; a 5- or 7-wide kernel row takes 2 or 3 such groups) or 1,
+// NT = 1 or 2 channels per lane (2 only past 64), each as far as their G tables fit
+// kBackLds, TJ = 8 or 16 inputs per wave (KWT NT TJ <= 48 pairs per lane: their
+// sums and weights are two thirds of the 168 registers that three waves per SIMD
+// leave), up to 12 or 4 waves per block, evenly filled, and splits of the output
+// rows (at most 4096, 64 MiB of partial sums), by the time they predict. A block
+// takes a fixed start and its weights, and per position its barrier, its share of
+// the table's rows, and per raw pixel a fixed part and its wave's inputs, in cycles
+// of a wave alone on its CU; waves that share a CU slow each other down by kShare
+// each, and a block of w waves needs ceil(w / 4) on every SIMD (blocks of three to
+// six waves fill a CU less than their waves would). Partial sums and dt_in entries
+// are written and read once more.
+// The constants are a fit to 2,700 timed shapes of 98 layers: batch 4 to 128, 1 to
+// 256 channels in, 8 to 256 out, maps of 4 to 32, kernels 1, 3 and 5, strides,
+// pooling, M 8 to 128, dW alone, dt_in alone and both. The predicted best is 2 %
+// above the timed best on average; one fixed shape per layer with at least 16
+// positions per split was 66 % above it: 16 -> 32, 8 x 8, batch 16, both gradients
+// 71.9 -> 39 us, 53 -> 101, 10 x 10 pooled, 1 x 1, batch 4 177 -> 42,
+// 32 -> 32, 28 x 28, batch 128 1007 -> 743.
 constexpr int kBackLds = 152 * 1024;
+constexpr int kConvCUs = 256;
+constexpr int kConvMaxSplit = 4096;
 
-ConvBackPlan plan_conv_back(const ConvGeom &g, int64_t B, int M) {
-    ConvBackPlan p;
-    const int tab = g_table_len(M) * static_cast<int>(sizeof(float2));
-    auto lds = [&](int kwt, int nt) {
-        return back_ring(kwt) * (M + 3) * nt * kWave * 4 + tab;
-    };
-    p.kwt = (g.KW > 1 && g.stride == 1 && lds(3, 1) <= kBackLds) ? 3 : 1;
-    p.nt = (g.C_out > kWave && lds(p.kwt, 2) <= kBackLds) ? 2 : 1;
-    p.tj = (g.C_in <= 8 || (p.kwt == 3 && p.nt == 2)) ? 8 : 16;
-    if (p.kwt == 1 && p.nt == 2) p.tj = 16;
-    p.kg = (g.KW + p.kwt - 1) / p.kwt;
-    p.tiles = (g.C_out + p.nt * kWave - 1) / (p.nt * kWave);
-    // dt_in entries per input: at most KH * KW + 1 at a time
-    p.tiles_dt = std::min(p.tiles, (g.KH * g.KW + 1) / (g.KH * p.kg));
-    p.cpt = (g.C_in + p.tj - 1) / p.tj;
-    p.n_chunk = p.cpt * g.KH * p.kg;
-    p.groups = (p.n_chunk + kBackWaves - 1) / kBackWaves;
-    p.waves = (p.n_chunk + p.groups - 1) / p.groups;
+static int conv_back_lds(int M, int kwt, int nt) {
+    return back_ring(kwt) * (M + 3) * nt * kWave * 4 + g_table_len(M) * static_cast<int>(sizeof(float2));
+}
+
+// waves per SIMD that the kernel's registers leave
+static int conv_back_occupancy(int kwt, int pairs, bool dw, bool dt) {
+    if (dw && dt) return pairs > 24 ? 3 : pairs > 8 ? 4 : 6;
+    if (dw) return pairs > 32 ? 4 : pairs > 16 ? 5 : 7;
+    return pairs > 32 ? 3 : pairs > 16 ? 4 : kwt == 1 && pairs <= 8 ? 7 : 6;
+}
+
+// kwt and nt, rows_per_split: given, or 0
+static ConvBackPlan conv_back_search(const ConvGeom &g, int64_t B, int M, bool dw, bool dt, int kwt_given,
+                                     int nt_given, int rows_given) {
+    constexpr double kStart = 2720., kStartPair = 294., kStep = 750., kRow = 79., kItem = 831., kInput = 49.5;
+    constexpr double kPerUs = 2400., kShare = 0.0346, kPartUsPerMB = 1.92, kPartUsPerSplit = 0.0134, kEntryUsPerMB = 0.76;
+    const double k_pair = (dw && dt) ? 38. : dt ? 33.7 : 10.1;
     const int64_t nw = static_cast<int64_t>(g.KH) * g.KW * g.C_in * g.C_out;
-    const int64_t n_rows = B * g.Ho, n_samp = n_rows * g.Wo;
-    const int64_t pieces = ((nw / g.C_out + 255) / 256) *
-                           ((g.C_out <= 32 || M > 90) ? (g.C_out + 31) / 32 : (g.C_out + 63) / 64);
-    int64_t ns = 1;
-    const int64_t blocks = static_cast<int64_t>(p.groups) * p.tiles;
-    while ((blocks * ns < 512 || blocks * ns * p.waves < 4096) && ns * 2 <= n_rows &&
-           n_samp / (ns * 2) >= 16 && pieces * ns < 1024 && ns * 2 * nw * 4 <= (64 << 20))
-        ns *= 2;
-    p.rows_per_split = static_cast<int>(std::max<int64_t>(1, (n_rows + ns - 1) / ns));
-    p.nsplit = static_cast<int>(std::max<int64_t>(1, (n_rows + p.rows_per_split - 1) / p.rows_per_split));
-    p.lds = static_cast<size_t>(lds(p.kwt, p.nt));
+    const int64_t rows = std::max<int64_t>(1, B * g.Ho);
+    const double dw_mb = 4e-6 * static_cast<double>(nw);
+    const double in_mb = 4e-6 * static_cast<double>(B * g.Hp) * g.Wp * g.PC;
+    int64_t most_split = std::min<int64_t>(rows, kConvMaxSplit);
+    if (dw) most_split = std::max<int64_t>(1, std::min(most_split, (int64_t{64} << 20) / (4 * std::max<int64_t>(nw, 1))));
+    ConvBackPlan p{};
+    double best = -1.;
+    for (int kwt = 3; kwt >= 1; kwt -= 2) {
+        if (kwt_given ? kwt != kwt_given : (kwt == 3 && (g.KW == 1 || g.stride != 1))) continue;
+        if (conv_back_lds(M, kwt, 1) > kBackLds) continue;
+        for (int nt = 2; nt >= 1; --nt) {
+            if (nt_given ? nt != nt_given : (nt == 2 && (g.C_out <= kWave || conv_back_lds(M, kwt, 2) > kBackLds))) continue;
+            const int kg = (g.KW + kwt - 1) / kwt;
+            const int tiles = (g.C_out + nt * kWave - 1) / (nt * kWave);
+            // dt_in entries per input: at most KH * KW + 1 at a time
+            const int tiles_dt = std::max(1, std::min(tiles, (g.KH * g.KW + 1) / (g.KH * kg)));
+            const int launches = dt ? (tiles + tiles_dt - 1) / tiles_dt : 1;
+            const int by_lds = std::max(1, (160 * 1024) / (conv_back_lds(M, kwt, nt) + 1024));
+            const double steps = g.Wo + kwt - 1;
+            for (int tj = 16; tj >= 8; tj -= 8) {
+                if (kwt * nt * tj > 48) continue;
+                const int cpt = (g.C_in + tj - 1) / tj, chunks = cpt * g.KH * kg;
+                const int occ = conv_back_occupancy(kwt, kwt * nt * tj, dw, dt);
+                const double item = kItem + static_cast<double>(g.C_in) / cpt * (kwt * nt * k_pair + kInput);
+                const double start = kStart + kStartPair * kwt * nt * tj;
+                for (int most = kBackWaves; most >= 4; most -= 8) {
+                    const int groups = (chunks + most - 1) / most;
+                    const int w = (chunks + groups - 1) / groups;
+                    const int per = std::max(1, std::min(w <= 2 ? 4 * occ / w : occ / ((w + 3) / 4), by_lds));
+                    const double step = g.P * item + kStep + kRow * nt * (M + 3) / w;
+                    const int64_t blocks = static_cast<int64_t>(groups) * ((tiles + launches - 1) / launches);
+                    for (int64_t want = 1;; want = std::min(2 * want, most_split)) {
+                        const int64_t rps = rows_given ? rows_given : (rows + want - 1) / want;
+                        const int64_t ns = (rows + rps - 1) / rps, tot = blocks * ns;
+                        const int64_t full = tot / (kConvCUs * per), rest = tot - full * kConvCUs * per;
+                        double us = static_cast<double>(full) * (1. + kShare * per * w);
+                        if (rest > 0) us += 1. + kShare * static_cast<double>((rest + kConvCUs - 1) / kConvCUs) * w;
+                        us *= launches * (start + static_cast<double>(rps) * steps * step) / kPerUs;
+                        if (dw) us += std::max(kPartUsPerMB * static_cast<double>(ns) * dw_mb,
+                                               kPartUsPerSplit * static_cast<double>(ns));
+                        if (dt) us += kEntryUsPerMB * g.KH * kg * tiles * in_mb;
+                        if (best < 0. || us < best) {
+                            best = us;
+                            p = ConvBackPlan{kwt, nt, tj, kg, tiles, tiles_dt, cpt, chunks, groups, w,
+                                             static_cast<int>(ns), static_cast<int>(rps),
+                                             static_cast<size_t>(conv_back_lds(M, kwt, nt))};
+                        }
+                        if (rows_given || want >= most_split) break;
+                    }
+                }
+            }
+        }
+    }
     return p;
 }
+
+// One gradient alone keeps what the order of its sums depends on (dW: the splits;
+// dt_in: taps and channels per lane) as both together have it, so that it comes out
+// the same to the bit; the workspace is laid out for both.
+ConvBackPlan plan_conv_back(const ConvGeom &g, int64_t B, int M, bool dw, bool dt) {
+    const ConvBackPlan p = conv_back_search(g, B, M, true, true, 0, 0, 0);
+    if (dw == dt) return p;
+    return dw ? conv_back_search(g, B, M, true, false, 0, 0, p.rows_per_split)
+              : conv_back_search(g, B, M, false, true, p.kwt, p.nt, 0);
+}
+// ---- end of the launch rules of conv_back_kernel ----
 
 template <int KWT, int NT, int TJ>
 static void launch_back(const LifConst &C, const ConvGeom &g, const ConvBackArgs &a,
@@ -2092,8 +2155,8 @@ hipError_t launch_conv_backward(const LifConst &C, const ConvGeom &g, int64_t B,
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const ConvBackPlan p = plan_conv_back(g, B, C.M);
     const bool dtl = dt && n_pos > 0;
+    const ConvBackPlan p = plan_conv_back(g, B, C.M, grad_W != nullptr, dtl);
     if (grad_W || dtl) {
         ConvBackArgs a{static_cast<int>(B * g.Ho), p.rows_per_split, p.cpt, p.n_chunk, p.kg, 0, 0, 0,
                        ws.tri, ws.rend, ws.ev.live, ws.ev.ev, ws.wt, ws.P, ws.part,
@@ -2109,7 +2172,8 @@ hipError_t launch_conv_backward(const LifConst &C, const ConvGeom &g, int64_t B,
             if (p.kwt == 3 && p.nt == 2) launch_back<3, 2, 8>(C, g, a, p, nt, dw, dtl, st);
             else if (p.kwt == 3 && p.tj == 16) launch_back<3, 1, 16>(C, g, a, p, nt, dw, dtl, st);
             else if (p.kwt == 3) launch_back<3, 1, 8>(C, g, a, p, nt, dw, dtl, st);
-            else if (p.nt == 2) launch_back<1, 2, 16>(C, g, a, p, nt, dw, dtl, st);
+            else if (p.nt == 2 && p.tj == 16) launch_back<1, 2, 16>(C, g, a, p, nt, dw, dtl, st);
+            else if (p.nt == 2) launch_back<1, 2, 8>(C, g, a, p, nt, dw, dtl, st);
             else if (p.tj == 16) launch_back<1, 1, 16>(C, g, a, p, nt, dw, dtl, st);
             else launch_back<1, 1, 8>(C, g, a, p, nt, dw, dtl, st);
             if ((e = hipGetLastError()) != hipSuccess) return e;

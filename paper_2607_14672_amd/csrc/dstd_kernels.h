@@ -161,7 +161,7 @@ struct ConvBackPlan {
     size_t lds;
 };
 
-ConvBackPlan plan_conv_back(const ConvGeom &g, int64_t B, int M);
+ConvBackPlan plan_conv_back(const ConvGeom &g, int64_t B, int M, bool dw, bool dt);
 int conv_sort_lds_bytes(int M, const ConvGeom &g);
 // keep (ev set): the set-up also writes the cell-major events the backward
 // needs.
