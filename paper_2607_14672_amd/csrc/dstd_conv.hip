@@ -1748,6 +1748,144 @@ __global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst 
     }
 }
 
+// dW alone with lanes = (tap, input) pairs: a block takes 256 of a layer's pairs
+// and TI channels, whose sums stay in registers over its output rows, position by
+// position. The contraction above gives an input a wave and its taps a table read
+// each; where a kernel row has few inputs (a first layer's one to three) a wave
+// spends its position on one of them, and without dt_in nothing covers the reads.
+// Here lanes whose inputs have the same event row read the same words of it at
+// once. Positions without gradient are skipped 64 at a time; the next position's
+// table goes to the other of two meanwhile, its triples and the next events are on
+// their way. Same sums in the same order.
+constexpr int kDwPairs = 256;
+
+template <int TI>
+__global__ __launch_bounds__(kDwPairs) void conv_dw_kernel(LifConst C, ConvGeom g, ConvBackArgs a) {
+    constexpr int kRow = TI + 4;            // a row's floats: 16-byte reads
+    constexpr int kParts = kWave / TI;      // rows that a wave writes at a time
+    extern __shared__ float gs[];  // G [2][R + 1][kRow], pairs (a_d, k_d)
+    const int R = rows_of(C);
+    const int ts = (R + 1) * kRow;
+    float2 *tab = reinterpret_cast<float2 *>(gs + 2 * ts);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = uniform(threadIdx.x >> 6);
+    const int z = blockIdx.y;
+    const int s_lo = z * a.rows_per_split * g.Wo;
+    const int s_hi = min(a.n_rows, (z + 1) * a.rows_per_split) * g.Wo;
+    // the split's positions that pass gradient, in order (-1: none left), and the
+    // last event row that meets it there
+    int base = s_lo - kWave, er = -1;
+    uint64_t mask = 0;
+    auto next = [&](int &top) {
+        while (mask == 0) {
+            if (s_hi - base <= kWave) return -1;
+            base += kWave;
+            er = base + lane < s_hi ? a.rend[base + lane] : -1;
+            mask = __ballot(er >= 0);
+        }
+        const int bit = __builtin_ctzll(mask);
+        mask &= mask - 1;
+        top = __builtin_amdgcn_readlane(er, bit);
+        return base + bit;
+    };
+    int top0 = -1, top1 = -1, top2 = -1;
+    int s0 = next(top0);
+    // (a split without any writes no partials: the reduction skips it)
+    if (threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.z == 0) a.zlive[z] = s0 >= 0;
+    if (s0 < 0) return;  // block-uniform
+    int s1 = next(top1);
+    const int NJ = g.KH * g.KW * g.C_in;
+    const int jj = static_cast<int>(blockIdx.x) * kDwPairs + static_cast<int>(threadIdx.x);
+    const bool j_ok = jj < NJ;
+    const int k = (j_ok ? jj : 0) / g.C_in, ci = (j_ok ? jj : 0) - k * g.C_in;
+    const int ky = k / g.KW, kx = k - ky * g.KW;
+    const int c0 = static_cast<int>(blockIdx.z) * TI;
+    // row 0 holds no grid point; rows R - 1 and R are zero for inputs without
+    // events (or past the last spike)
+    for (int t = threadIdx.x; t < 2 * kRow; t += kDwPairs) {
+        float *q = gs + (t / kRow) * ts + t % kRow;
+        q[0] = 0.f;
+        q[(R - 1) * kRow] = 0.f;
+        q[R * kRow] = 0.f;
+    }
+    g_table_fill(C, tab);
+    float acc[TI];
+#pragma unroll
+    for (int i = 0; i < TI; ++i) acc[i] = 0.f;
+    const int cl = lane % TI, part = lane / TI;
+    const unsigned co = static_cast<unsigned>(min(c0 + cl, g.C_out - 1));
+    const bool c_ok = c0 + cl < g.C_out;
+    auto load_tri = [&](int s) {
+        const float *p = a.tri + static_cast<int64_t>(s) * 3 * g.C_out;
+        GTri<1> t;
+        t.gK[0] = p[co];
+        t.gE[0] = (p + g.C_out)[co];
+        t.q[0] = __float_as_int((p + 2 * g.C_out)[co]);
+        return t;
+    };
+    auto write_tri = [&](GTri<1> t, int top, int slot) {
+        t.gK[0] = c_ok ? t.gK[0] : 0.f;
+        t.gE[0] = c_ok ? t.gE[0] : 0.f;
+        t.q[0] = c_ok ? t.q[0] : -1;
+        g_rows<1, kRow>(C.M, tab, t, top, wave * kParts + part, kDwPairs / TI, gs + slot * ts + cl);
+    };
+    // this lane's cell at position s (-1: outside, or no events in its cell row)
+    struct Ev { int row; float L, R; };
+    const int HoWo = g.Ho * g.Wo;
+    auto cell_at = [&](int s, int &live) {
+        const int b = s / HoWo, p = s - b * HoWo, oy = p / g.Wo, ox = p - oy * g.Wo;
+        const int py = oy * g.stride - g.pad + ky, px = ox * g.stride - g.pad + kx;
+        const bool in = j_ok && py >= 0 && py < g.Hp && px >= 0 && px < g.Wp;
+        const int cr = in ? b * g.Hp + py : 0;
+        live = in ? a.cr_live[cr] : 0;
+        return static_cast<int64_t>(cr) * g.Wp + (in ? px : 0);
+    };
+    auto load_ev = [&](int64_t cell, int d) {
+        const float *p = a.ev + (cell * g.P + d) * kEvFields * g.C_in + ci;
+        return Ev{__float_as_int(p[0]), p[g.C_in], p[2 * g.C_in]};
+    };
+    int live0 = 0, live1 = 0;
+    int64_t cell0 = cell_at(s0, live0), cell1 = cell0;
+    Ev ev = load_ev(cell0, 0);
+    write_tri(load_tri(s0), top0, 0);
+    GTri<1> tri = load_tri(s1 >= 0 ? s1 : s0);
+    __syncthreads();
+    for (int cur = 0;; cur ^= 1) {
+        const int s2 = s1 >= 0 ? next(top2) : -1;
+        if (s1 >= 0) {
+            cell1 = cell_at(s1, live1);
+            write_tri(tri, top1, cur ^ 1);
+            tri = load_tri(s2 >= 0 ? s2 : s1);
+        }
+        for (int d = 0; d < g.P; ++d) {
+            const Ev n = d + 1 < g.P ? load_ev(cell0, d + 1) : load_ev(cell1, 0);
+            const bool on = live0 != 0 && static_cast<unsigned>(ev.row) <= static_cast<unsigned>(top0);
+            if (__any(on)) {
+                const float L = on ? ev.L : 0.f, Rv = on ? ev.R : 0.f;
+                const float4 *p = reinterpret_cast<const float4 *>(gs + cur * ts + (on ? ev.row : R - 1) * kRow);
+#pragma unroll
+                for (int i = 0; i < TI; i += 4) {
+                    const float4 x = p[i / 4], y = p[(i + kRow) / 4];
+                    acc[i] = fmaf(L, x.x, fmaf(Rv, y.x, acc[i]));
+                    acc[i + 1] = fmaf(L, x.y, fmaf(Rv, y.y, acc[i + 1]));
+                    acc[i + 2] = fmaf(L, x.z, fmaf(Rv, y.z, acc[i + 2]));
+                    acc[i + 3] = fmaf(L, x.w, fmaf(Rv, y.w, acc[i + 3]));
+                }
+            }
+            ev = n;
+        }
+        if (s1 < 0) break;
+        s0 = s1; top0 = top1; cell0 = cell1; live0 = live1;
+        s1 = s2; top1 = top2;
+        __syncthreads();
+    }
+    if (!j_ok) return;
+    float *out = a.part + (static_cast<int64_t>(z) * g.C_out + c0) * NJ + jj;
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+        if (c0 + i < g.C_out) out[static_cast<int64_t>(i) * NJ] = acc[i];
+}
+
 // dW[co, ci, ky, kx] = (1/P) sum_z part[z][co][k * C_in + ci]. Threads follow
 // the partial-sum layout (coalesced reads); a block takes groups of 256 / G
 // consecutive entries x G split groups (G from red_groups: more groups where
@@ -2001,7 +2139,7 @@ hipError_t launch_conv_forward(const LifConst &C, const ConvGeom &g, int64_t B, 
 // NT = 1 or 2 channels per lane (2 only past 64), each as far as their G tables fit
 // kBackLds, TJ = 8 or 16 inputs per wave (KWT NT TJ <= 48 pairs per lane: their
 // sums and weights are two thirds of the 168 registers that three waves per SIMD
-// leave), up to 12 or 4 waves per block, evenly filled, and splits of the output
+// leave), up to 12 or 4 waves per block, and splits of the output
 // rows (at most 4096, 64 MiB of partial sums), by the time they predict. A block
 // takes a fixed start and its weights, and per position its barrier, its share of
 // the table's rows, and per raw pixel a fixed part and its wave's inputs, in cycles
@@ -2043,6 +2181,12 @@ static ConvBackPlan conv_back_search(const ConvGeom &g, int64_t B, int M, bool d
     const double in_mb = 4e-6 * static_cast<double>(B * g.Hp) * g.Wp * g.PC;
     int64_t most_split = std::min<int64_t>(rows, kConvMaxSplit);
     if (dw) most_split = std::max<int64_t>(1, std::min(most_split, (int64_t{64} << 20) / (4 * std::max<int64_t>(nw, 1))));
+    // (dW alone of a layer whose pairs are one block of conv_dw_kernel needs 1024
+    // splits, of 16 positions at least, to fill the chip: 1 -> 32, 5 x 5, 28 x 28, batch 64 250 -> 122 us, both
+    // gradients 324 -> 360)
+    const int64_t least_split =
+        (dw && g.KH * g.KW * g.C_in <= kDwPairs && g.C_out <= kWave)
+            ? std::max<int64_t>(1, std::min<int64_t>({1024, most_split, rows * g.Wo / 16})) : 1;
     ConvBackPlan p{};
     double best = -1.;
     for (int kwt = 3; kwt >= 1; kwt -= 2) {
@@ -2065,27 +2209,32 @@ static ConvBackPlan conv_back_search(const ConvGeom &g, int64_t B, int M, bool d
                 const double start = kStart + kStartPair * kwt * nt * tj;
                 for (int most = kBackWaves; most >= 4; most -= 8) {
                     const int groups = (chunks + most - 1) / most;
-                    const int w = (chunks + groups - 1) / groups;
-                    const int per = std::max(1, std::min(w <= 2 ? 4 * occ / w : occ / ((w + 3) / 4), by_lds));
-                    const double step = g.P * item + kStep + kRow * nt * (M + 3) / w;
-                    const int64_t blocks = static_cast<int64_t>(groups) * ((tiles + launches - 1) / launches);
-                    for (int64_t want = 1;; want = std::min(2 * want, most_split)) {
-                        const int64_t rps = rows_given ? rows_given : (rows + want - 1) / want;
-                        const int64_t ns = (rows + rps - 1) / rps, tot = blocks * ns;
-                        const int64_t full = tot / (kConvCUs * per), rest = tot - full * kConvCUs * per;
-                        double us = static_cast<double>(full) * (1. + kShare * per * w);
-                        if (rest > 0) us += 1. + kShare * static_cast<double>((rest + kConvCUs - 1) / kConvCUs) * w;
-                        us *= launches * (start + static_cast<double>(rps) * steps * step) / kPerUs;
-                        if (dw) us += std::max(kPartUsPerMB * static_cast<double>(ns) * dw_mb,
-                                               kPartUsPerSplit * static_cast<double>(ns));
-                        if (dt) us += kEntryUsPerMB * g.KH * kg * tiles * in_mb;
-                        if (best < 0. || us < best) {
-                            best = us;
-                            p = ConvBackPlan{kwt, nt, tj, kg, tiles, tiles_dt, cpt, chunks, groups, w,
-                                             static_cast<int>(ns), static_cast<int>(rps),
-                                             static_cast<size_t>(conv_back_lds(M, kwt, nt))};
+                    const int even = (chunks + groups - 1) / groups;
+                    // (one block over the chunks: also with waves that only write table
+                    // rows; 1 -> 22, 1 x 1, 24 x 24, batch 7, M = 66 112 -> 51 us)
+                    for (const int w : {even, most}) {
+                        if (w != even && groups > 1) continue;
+                        const int per = std::max(1, std::min(w <= 2 ? 4 * occ / w : occ / ((w + 3) / 4), by_lds));
+                        const double step = g.P * item + kStep + kRow * nt * (M + 3) / w;
+                        const int64_t blocks = static_cast<int64_t>(groups) * ((tiles + launches - 1) / launches);
+                        for (int64_t want = least_split;; want = std::min(2 * want, most_split)) {
+                            const int64_t rps = rows_given ? rows_given : (rows + want - 1) / want;
+                            const int64_t ns = (rows + rps - 1) / rps, tot = blocks * ns;
+                            const int64_t full = tot / (kConvCUs * per), rest = tot - full * kConvCUs * per;
+                            double us = static_cast<double>(full) * (1. + kShare * per * w);
+                            if (rest > 0) us += 1. + kShare * static_cast<double>((rest + kConvCUs - 1) / kConvCUs) * w;
+                            us *= launches * (start + static_cast<double>(rps) * steps * step) / kPerUs;
+                            if (dw) us += std::max(kPartUsPerMB * static_cast<double>(ns) * dw_mb,
+                                                   kPartUsPerSplit * static_cast<double>(ns));
+                            if (dt) us += kEntryUsPerMB * g.KH * kg * tiles * in_mb;
+                            if (best < 0. || us < best) {
+                                best = us;
+                                p = ConvBackPlan{kwt, nt, tj, kg, tiles, tiles_dt, cpt, chunks, groups, w,
+                                                 static_cast<int>(ns), static_cast<int>(rps),
+                                                 static_cast<size_t>(conv_back_lds(M, kwt, nt))};
+                            }
+                            if (rows_given || want >= most_split) break;
                         }
-                        if (rows_given || want >= most_split) break;
                     }
                 }
             }
@@ -2104,6 +2253,24 @@ ConvBackPlan plan_conv_back(const ConvGeom &g, int64_t B, int M, bool dw, bool d
               : conv_back_search(g, B, M, false, true, p.kwt, p.nt, 0);
 }
 // ---- end of the launch rules of conv_back_kernel ----
+
+// dW alone: pairs along the lanes (conv_dw_kernel) where a position has enough of
+// them for the lanes, 64 (tap, input) pairs times raw pixels, or 18 with at most 64
+// channels out (below: 3 -> 64, 1 x 1, 32 x 32, batch 64 149 us, 171 with pairs
+// along the lanes; 1 -> 38, 18 x 18, batch 11 44 and 53). 32 channels per block past
+// M = 88, where two tables of 64 would leave two blocks per CU or less.
+// conv_back_kernel -> conv_dw_kernel, set-up and sums with it: 64 -> 64, 32 x 32,
+// batch 64 656 -> 589 us; 128 -> 128, 16 x 16, stride 2, batch 64 341 -> 263;
+// 17 -> 140, 26 x 26, stride 2, batch 20 146 -> 79; 1 -> 32, 5 x 5, 28 x 28,
+// batch 64 285 -> 122.
+static bool conv_dw_by_pair(const ConvGeom &g) {
+    return static_cast<int64_t>(g.KH) * g.KW * g.C_in * g.P >= (g.C_out <= kWave ? 18 : 64);
+}
+static int conv_dw_ti(const ConvGeom &g, int M) { return (g.C_out <= 32 || M > 88) ? 32 : 64; }
+static size_t conv_dw_lds(int M, int ti) {
+    return 2 * static_cast<size_t>(M + 4) * (ti + 4) * sizeof(float) +
+           static_cast<size_t>(g_table_len(M)) * sizeof(float2);
+}
 
 template <int KWT, int NT, int TJ>
 static void launch_back(const LifConst &C, const ConvGeom &g, const ConvBackArgs &a,
@@ -2161,22 +2328,32 @@ hipError_t launch_conv_backward(const LifConst &C, const ConvGeom &g, int64_t B,
         ConvBackArgs a{static_cast<int>(B * g.Ho), p.rows_per_split, p.cpt, p.n_chunk, p.kg, 0, 0, 0,
                        ws.tri, ws.rend, ws.ev.live, ws.ev.ev, ws.wt, ws.P, ws.part,
                        ws.zlive};
-        ProfScope prof("conv_back", st);
-        const int step = dtl ? p.tiles_dt : p.tiles;
-        a.n_tile = step;
-        for (int t = 0; t < p.tiles; t += step) {
-            a.tile0 = t;
-            a.add = t > 0;
-            const int nt = std::min(step, p.tiles - t);
-            const bool dw = grad_W != nullptr;
-            if (p.kwt == 3 && p.nt == 2) launch_back<3, 2, 8>(C, g, a, p, nt, dw, dtl, st);
-            else if (p.kwt == 3 && p.tj == 16) launch_back<3, 1, 16>(C, g, a, p, nt, dw, dtl, st);
-            else if (p.kwt == 3) launch_back<3, 1, 8>(C, g, a, p, nt, dw, dtl, st);
-            else if (p.nt == 2 && p.tj == 16) launch_back<1, 2, 16>(C, g, a, p, nt, dw, dtl, st);
-            else if (p.nt == 2) launch_back<1, 2, 8>(C, g, a, p, nt, dw, dtl, st);
-            else if (p.tj == 16) launch_back<1, 1, 16>(C, g, a, p, nt, dw, dtl, st);
-            else launch_back<1, 1, 8>(C, g, a, p, nt, dw, dtl, st);
+        if (grad_W && !dtl && conv_dw_by_pair(g)) {
+            ProfScope prof("conv_dw", st);
+            const int ti = conv_dw_ti(g, C.M);
+            const dim3 grid(static_cast<unsigned>((nj + kDwPairs - 1) / kDwPairs), static_cast<unsigned>(p.nsplit),
+                            static_cast<unsigned>((g.C_out + ti - 1) / ti));
+            if (ti == 64) hipLaunchKernelGGL((conv_dw_kernel<64>), grid, dim3(kDwPairs), conv_dw_lds(C.M, 64), st, C, g, a);
+            else hipLaunchKernelGGL((conv_dw_kernel<32>), grid, dim3(kDwPairs), conv_dw_lds(C.M, 32), st, C, g, a);
             if ((e = hipGetLastError()) != hipSuccess) return e;
+        } else {
+            ProfScope prof("conv_back", st);
+            const int step = dtl ? p.tiles_dt : p.tiles;
+            a.n_tile = step;
+            for (int t = 0; t < p.tiles; t += step) {
+                a.tile0 = t;
+                a.add = t > 0;
+                const int nt = std::min(step, p.tiles - t);
+                const bool dw = grad_W != nullptr;
+                if (p.kwt == 3 && p.nt == 2) launch_back<3, 2, 8>(C, g, a, p, nt, dw, dtl, st);
+                else if (p.kwt == 3 && p.tj == 16) launch_back<3, 1, 16>(C, g, a, p, nt, dw, dtl, st);
+                else if (p.kwt == 3) launch_back<3, 1, 8>(C, g, a, p, nt, dw, dtl, st);
+                else if (p.nt == 2 && p.tj == 16) launch_back<1, 2, 16>(C, g, a, p, nt, dw, dtl, st);
+                else if (p.nt == 2) launch_back<1, 2, 8>(C, g, a, p, nt, dw, dtl, st);
+                else if (p.tj == 16) launch_back<1, 1, 16>(C, g, a, p, nt, dw, dtl, st);
+                else launch_back<1, 1, 8>(C, g, a, p, nt, dw, dtl, st);
+                if ((e = hipGetLastError()) != hipSuccess) return e;
+            }
         }
     }
     {

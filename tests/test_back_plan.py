@@ -108,3 +108,97 @@ def test_multispike_splits_do_not_end_at_64_intervals(plan, N_out):
     assert b["groups"] * b["waves"] * b["nsplit"] * b["tiles"] >= \
         0.9 * a["groups"] * a["waves"] * a["nsplit"] * a["tiles"]
     assert b["n_buf"] >= b["tiles"] - 1
+
+
+CONV_HARNESS = r"""
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#define __device__
+#define __host__
+#define __forceinline__ inline
+struct float2 { float x, y; };
+constexpr int kWave = 64;
+struct ConvGeom { int C_in, C_out, KH, KW, stride, Hp, Wp, Ho, Wo, P, PC; };
+@CODE@
+int main() {
+    long v[11];  // B, C_in, C_out, KH, KW, stride, map, output map, P, M, which gradients
+    while (scanf("%ld %ld %ld %ld %ld %ld %ld %ld %ld %ld %ld", v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6,
+                 v + 7, v + 8, v + 9, v + 10) == 11) {
+        auto n = [&](int k) { return static_cast<int>(v[k]); };
+        const ConvGeom g{n(1), n(2), n(3), n(4), n(5), n(6), n(6), n(7), n(7), n(8), n(1) * n(8)};
+        const ConvBackPlan p = plan_conv_back(g, v[0], n(9), v[10] & 1, v[10] & 2);
+        printf("%d %d %d %d %d %d %d %d %d %d %d %d %zu\n", p.kwt, p.nt, p.tj, p.kg, p.tiles, p.tiles_dt, p.cpt,
+               p.n_chunk, p.groups, p.waves, p.nsplit, p.rows_per_split, p.lds);
+    }
+}
+"""
+CONV_FIELDS = "kwt nt tj kg tiles tiles_dt cpt n_chunk groups waves nsplit rows_per_split lds".split()
+
+
+@pytest.fixture(scope="module")
+def conv_plan(tmp_path_factory):
+    def read(name):
+        with open(os.path.join(CSRC, name)) as f:
+            return f.read()
+    conv, kern = read("dstd_conv.hip"), read("dstd_kernels.h")
+    code = re.search(r"struct ConvBackPlan \{.*?\n\};", kern, re.S)[0] + "\n"
+    code += re.search(r"[^\n]*int g_table_len\(int M\)[^\n]*", read("dstd_back.h"))[0] + "\n"
+    code += re.search(r"constexpr int back_ring\(int kwt\)[^\n]*", conv)[0] + "\n"
+    code += "\n".join(re.findall(r"^constexpr int k(?:BackWaves|DwPairs) [^\n]*", conv, re.M)) + "\n"
+    code += conv[conv.index("constexpr int kBackLds "):
+                 conv.index("// ---- end of the launch rules of conv_back_kernel")]
+    d = tmp_path_factory.mktemp("conv_plan")
+    cpp, exe = str(d / "t.cpp"), str(d / "t")
+    with open(cpp, "w") as f:
+        f.write(CONV_HARNESS.replace("@CODE@", code))
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", exe, cpp], check=True)
+
+    def run(shapes):
+        text = "\n".join(" ".join(str(int(x)) for x in s) for s in shapes)
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, check=True)
+        out = [dict(zip(CONV_FIELDS, map(int, line.split()))) for line in r.stdout.splitlines()]
+        assert len(out) == len(shapes)
+        return out
+    return run
+
+
+def _conv_shapes(mode):
+    return [(B, ci, co, k, k, s, hw, (hw - 1) // s + 1, P, M, mode)
+            for B in (1, 16, 128) for ci in (1, 8, 9, 100) for co in (16, 64, 65, 512) for k in (1, 3, 7)
+            for s in (1, 2) for hw in (4, 28) for P in (1, 4) for M in (1, 32, 100, 150, 256)]
+
+
+def test_conv_plans_fit_hardware_and_workspace(conv_plan):
+    for mode in (1, 2, 3):
+        for s, p in zip(_conv_shapes(mode), conv_plan(_conv_shapes(mode))):
+            B, ci, co, k, _, st, hw, ho, P, M, _ = s
+            assert (p["kwt"], p["nt"], p["tj"]) in ((3, 2, 8), (3, 1, 16), (3, 1, 8), (1, 2, 16), (1, 2, 8),
+                                                    (1, 1, 16), (1, 1, 8)), (s, p)
+            assert p["kwt"] == 1 or (st == 1 and k > 1), (s, p)
+            assert p["tiles"] * p["nt"] * 64 >= co and p["kg"] * p["kwt"] >= k, (s, p)
+            assert p["cpt"] * p["tj"] >= ci and p["n_chunk"] == p["cpt"] * k * p["kg"], (s, p)
+            assert p["groups"] * p["waves"] >= p["n_chunk"] and 1 <= p["waves"] <= 12, (s, p)
+            assert (p["groups"] - 1) * p["waves"] < p["n_chunk"], (s, p)
+            assert p["nsplit"] * p["rows_per_split"] >= B * ho > (p["nsplit"] - 1) * p["rows_per_split"], (s, p)
+            assert p["lds"] + 1024 <= 160 * 1024 and p["nsplit"] <= 4096, (s, p)
+            assert 1 <= p["tiles_dt"] <= p["tiles"]
+            assert k * p["kg"] * p["tiles_dt"] <= max(k * k + 1, k * p["kg"]), (s, p)
+            if mode & 1 and p["nsplit"] > 1:
+                assert p["nsplit"] * k * k * ci * co * 4 <= 64 << 20, (s, p)
+
+
+def test_one_conv_gradient_alone_keeps_the_order_of_its_sums(conv_plan):
+    both = conv_plan(_conv_shapes(3))
+    for s, b, w, t in zip(_conv_shapes(3), both, conv_plan(_conv_shapes(1)), conv_plan(_conv_shapes(2))):
+        assert w["rows_per_split"] == b["rows_per_split"], s
+        assert all(t[f] == b[f] for f in ("kwt", "nt", "kg", "tiles", "tiles_dt")), s
+
+
+@pytest.mark.parametrize("B,ci,co,k,hw,P,M", [
+    (16, 16, 32, 3, 8, 1, 32), (4, 53, 101, 1, 5, 4, 21), (8, 160, 16, 1, 10, 1, 16), (5, 2, 132, 3, 5, 1, 64)])
+def test_small_conv_layers_take_every_row(conv_plan, B, ci, co, k, hw, P, M):
+    """A split per output row where there are fewer rows than CUs (16 positions or
+    more per split had left 1 to 32 blocks)."""
+    p, = conv_plan([(B, ci, co, k, k, 1, hw, hw, P, M, 3)])
+    assert p["nsplit"] >= min(B * hw, 256) / 2, p

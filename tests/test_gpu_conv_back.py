@@ -61,3 +61,66 @@ def test_conv_backward_interval_index_past_the_grid(dev, c_out):  # noqa: F811
     b = _gpu_backward(dev, (prm, c, tt, Wt, to, sl, past), g)
     assert all(np.isfinite(x).all() and x.any() for x in a)
     assert all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("B,cs,M,share", [
+    (3, _cs(1, 9, 11, 17, K=5), 12, 1.0),           # few pairs, one block of them
+    (2, _cs(30, 6, 7, 65), 16, 0.3),                # 270 pairs, two channel tiles, gaps
+    (2, _cs(7, 10, 12, 33, pool_in=2), 90, 0.05),   # four raw pixels, 32 channels per block
+    (3, _cs(20, 3, 4, 10, K=1, pad=0, pool_in=0), 16, 1.0),  # twelve raw pixels
+    (2, _cs(9, 9, 13, 70, stride=2), 256, 0.5),     # the longest grid
+    (4, _cs(70, 5, 5, 40, K=1, pad=0), 8, 0.5),
+    (2, _cs(3, 8, 66, 20), 20, 0.02),               # rows longer than 64 positions, most without
+])
+def test_conv_backward_alone_is_the_same(dev, B, cs, M, share):  # noqa: F811
+    """Each gradient alone has the bits that both together give it (dW alone runs
+    with the (tap, input) pairs along the lanes), and dW agrees with the oracle."""
+    p, t, W = _conv_case(81, B, cs, M, 1.0, 0.3, k=7.0)
+    rng = np.random.default_rng(82)
+    t = _special_inputs(t, p, rng)
+    gpu, h = _gpu_forward(dev, p, cs, t, W)
+    orc = oracle.conv_forward(p, cs, t, W)
+    mask, stats = check_forward(gpu, orc, None, _window(p), label="alone", taus=_taus(p))
+    g = rng.standard_normal(orc["t_out"].shape)
+    on = rng.random((B, 1) + g.shape[2:]) < share
+    g = np.where(mask | ~on, 0.0, g).astype(np.float32)
+    only_W, none = _gpu_backward(dev, h, g, need_t=False)
+    assert none is None
+    _conv_grad_check(p, cs, t, W, orc, mask, stats, g, only_W, None, "dW alone")
+    gW, gx = _gpu_backward(dev, h, g)
+    assert np.array_equal(only_W, gW)
+    assert np.array_equal(_gpu_backward(dev, h, g, need_W=False)[1], gx)
+    zW, _ = _gpu_backward(dev, h, np.zeros_like(g), need_t=False)
+    assert not zW.any()
+
+
+@pytest.mark.parametrize("C_in,K", [(1, 5), (12, 3)])
+def test_conv_dw_alone_costs_less_than_both(dev, C_in, K):  # noqa: F811
+    """A small layer's dW alone against both gradients: 0.34 and 0.62 of their time
+    (0.78 and 0.85 with a wave per input)."""
+    import torch
+    from paper_2607_14672_amd import dstd
+    gen = torch.Generator(device=dev).manual_seed(83)
+    cs = dstd.make_conv_shape(C_in, 28, 28, 32, K, K, 1, K // 2, 1)
+    prm = dstd.make_params(1.0, 0.3, 1.0, 32, 0.0, 1.0 / 32)
+    t = torch.rand((64, C_in, 28, 28), device=dev, generator=gen)
+    n = C_in * K * K
+    W = (6.0 / n) * (1 + 0.3 * n ** 0.5 * torch.randn((32, C_in, K, K), device=dev, generator=gen))
+    ws = dstd.workspace(dstd.dstd_lif_conv_backward_workspace_size(prm, cs, 64), dev)
+    r = dstd.conv_forward(prm, cs, t, W, ws=ws)
+    g = torch.randn(r[0].shape, device=dev, generator=gen)
+
+    def best(need_t):
+        out = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                dstd.conv_backward(prm, cs, t, W, *r, g, need_t_in=need_t, ws=ws)
+            b.record()
+            b.synchronize()
+            out.append(a.elapsed_time(b))
+        return min(out)
+    x, y = best(False), best(True)
+    print(f"dW alone / both {x / y:.2f}", flush=True)
+    assert x < 0.75 * y
