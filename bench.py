@@ -309,19 +309,25 @@ def layer_desc(lay):
     return f"{lay.n_in}->{lay.n_out} M={lay.M}"
 
 
-def kernel_algorithmic_flops(net, act, with_scan=True):
+def kernel_algorithmic_flops(net, act, with_scan=True, ran=()):
     """Algorithmic flops of one step, per kernel name (2-sparse events:
     FLOPS_PER_UPDATE per (sample, input with events, neuron)); the forward
     kernels, which run the interval scan of their neurons too, also count
     FLOPS_PER_SCAN_STEP per (neuron, grid point) when with_scan. A layer's dW
-    and dt_in come from one launch (back_dense, conv_back)."""
-    fl = {k: 0.0 for k in ("fwd_dense", "back_dense", "conv_fwd", "conv_back", "fwd_mfma")}
+    and dt_in come from one launch (back_dense, conv_back); the first layer's dW
+    alone has a kernel of its own (back_dw, conv_dw) where it is among those
+    that ran."""
+    fl = {k: 0.0 for k in ("fwd_dense", "back_dense", "back_dw", "conv_fwd", "conv_back", "conv_dw",
+                           "fwd_mfma")}
     for l, (e, a) in enumerate(zip(net.L, act)):
         upd = a["updates"]
         fwd, back = ("conv_fwd", "conv_back") if e["cs"] is not None else ("fwd_dense", "back_dense")
         fl[fwd] += FLOPS_PER_UPDATE * upd
         if with_scan:
             fl[fwd] += FLOPS_PER_SCAN_STEP * e["t_out"].numel() * (e["lay"].M + 1)
+        if l == 0:
+            alone = "conv_dw" if e["cs"] is not None else "back_dw"
+            back = alone if alone in ran else back
         fl[back] += FLOPS_PER_UPDATE * upd * (2 if l > 0 else 1)
     return fl
 
@@ -742,8 +748,8 @@ def measure(torch, dstd, wl, dev, steps, warmup, profile_steps, eager, contract=
     prof = dstd.profile_table()
     per_step = {k: v[1] / profile_steps for k, v in prof.items()}
     launches = {k: v[0] / profile_steps for k, v in prof.items()}
-    flops = kernel_algorithmic_flops(net, act)
-    contraction = kernel_algorithmic_flops(net, act, with_scan=False)
+    flops = kernel_algorithmic_flops(net, act, ran=per_step)
+    contraction = kernel_algorithmic_flops(net, act, with_scan=False, ran=per_step)
     if "fwd_mfma" in per_step and "fwd_dense" not in per_step:
         # the MFMA kernel only contracts; its scan runs in mfma_scan
         flops["fwd_mfma"] = contraction.pop("fwd_dense")

@@ -1591,6 +1591,36 @@ __global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst 
             });
         });
     });
+    // Infinite and NaN weights: a table without gradient is multiplied like any
+    // other, and 0 times such a weight would reach inputs that no position passes
+    // gradient to. They are taken out here (bit k of odd[i]: input k has one at tap
+    // i) and added tap by tap where the tap's own position has gradient for the
+    // input. (One tap per wave visits only such positions.)
+    unsigned odd[KWT];
+    bool any_odd = false;
+    static_for<KWT>([&](auto i) { odd[i] = 0u; });
+    if constexpr (DT && KWT > 1) {
+        static_for<TJ>([&](auto j) {
+            static_for<KWT>([&](auto i) {
+                static_for<NT>([&](auto c) {
+                    any_odd = any_odd || !(fabsf(w[j / kBackGroup][j % kBackGroup][i][c]) < INFINITY);
+                });
+            });
+        });
+        any_odd = __any(any_odd);
+        if (any_odd)
+            static_for<TJ>([&](auto j) {
+                static_for<KWT>([&](auto i) {
+                    bool bad = false;
+                    static_for<NT>([&](auto c) {
+                        float &x = w[j / kBackGroup][j % kBackGroup][i][c];
+                        bad = bad || !(fabsf(x) < INFINITY);
+                        x = fabsf(x) < INFINITY ? x : 0.f;
+                    });
+                    if (__any(bad)) odd[i] |= 1u << j;
+                });
+            });
+    }
     // gradient triples of the position whose triples start at p (scalar)
     unsigned tri_o[NT];
     bool ch_ok[NT];
@@ -1692,6 +1722,27 @@ __global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst 
                             if ((act >> (h * kBackGroup)) & 0xffu)
                                 tot[h] = back_group<NT, KWT, TJ, h, DW, DT>(gl, lane, act, ev[p], w[h], acc[h]);
                         });
+                        if (DT && KWT > 1 && any_odd)
+                            static_for<KWT>([&](auto i) {
+                                unsigned m = e[i] < 0 ? 0u : odd[i] & static_cast<unsigned>(__ballot(
+                                    lane < nj && static_cast<unsigned>(__float_as_int(ev[p].e[0])) <= static_cast<unsigned>(e[i])));
+                                for (; m; m &= m - 1) {
+                                    const int k = __builtin_ctz(m);
+                                    const float *q = gl[i] + __builtin_amdgcn_readlane(__float_as_int(ev[p].e[0]), k) * kRow;
+                                    const float dL = __shfl(ev[p].e[ev_reg<TJ>(3, 0)], ev_lane<TJ>(3, 0) + k);
+                                    const float dR = __shfl(ev[p].e[ev_reg<TJ>(4, 0)], ev_lane<TJ>(4, 0) + k);
+                                    const float *wp = a.Wt + (static_cast<int64_t>(ky * g.KW + kx0 + i) * g.C_in + ci0 + k) * g.C_out;
+                                    float v = 0.f;
+                                    for (int c = 0; c < NT; ++c) {
+                                        const float x = co + c < g.C_out ? wp[co + c] : 0.f;
+                                        if (!(fabsf(x) < INFINITY)) v += x * fmaf(dL, q[c], dR * q[kRow + c]);
+                                    }
+                                    for (int o = kWave / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+                                    static_for<kG>([&](auto h) {
+                                        if (k / kBackGroup == h && (lane >> 3) == k % kBackGroup) tot[h] += v;
+                                    });
+                                }
+                            });
                     }
                     if constexpr (DT) {
                         float v = tot[0];
@@ -2139,7 +2190,7 @@ hipError_t launch_conv_forward(const LifConst &C, const ConvGeom &g, int64_t B, 
 // NT = 1 or 2 channels per lane (2 only past 64), each as far as their G tables fit
 // kBackLds, TJ = 8 or 16 inputs per wave (KWT NT TJ <= 48 pairs per lane: their
 // sums and weights are two thirds of the 168 registers that three waves per SIMD
-// leave), up to 12 or 4 waves per block, and splits of the output
+// leave), up to 12, 8 or 4 waves per block, and splits of the output
 // rows (at most 4096, 64 MiB of partial sums), by the time they predict. A block
 // takes a fixed start and its weights, and per position its barrier, its share of
 // the table's rows, and per raw pixel a fixed part and its wave's inputs, in cycles
@@ -2207,7 +2258,7 @@ static ConvBackPlan conv_back_search(const ConvGeom &g, int64_t B, int M, bool d
                 const int occ = conv_back_occupancy(kwt, kwt * nt * tj, dw, dt);
                 const double item = kItem + static_cast<double>(g.C_in) / cpt * (kwt * nt * k_pair + kInput);
                 const double start = kStart + kStartPair * kwt * nt * tj;
-                for (int most = kBackWaves; most >= 4; most -= 8) {
+                for (const int most : {kBackWaves, 8, 4}) {
                     const int groups = (chunks + most - 1) / most;
                     const int even = (chunks + groups - 1) / groups;
                     // (one block over the chunks: also with waves that only write table

@@ -124,3 +124,49 @@ def test_conv_dw_alone_costs_less_than_both(dev, C_in, K):  # noqa: F811
     x, y = best(False), best(True)
     print(f"dW alone / both {x / y:.2f}", flush=True)
     assert x < 0.75 * y
+
+
+@pytest.mark.parametrize("B,cs,share", [
+    (48, _cs(5, 12, 12, 12), 0.05), (96, _cs(17, 8, 8, 70), 0.3), (96, _cs(9, 8, 8, 12), 0.1),
+    (64, _cs(9, 8, 8, 12, pool_in=2), 0.2), (128, _cs(5, 6, 6, 24, K=7), 0.05),
+    (3, _cs(6, 9, 15, 30, stride=2), 0.1)])
+def test_conv_backward_odd_weights_reach_only_their_inputs(dev, B, cs, share):  # noqa: F811
+    """Infinite and NaN weights: dt_in is not finite exactly where a position with
+    gradient up to the input's event row joins it through such a weight; elsewhere it
+    has the bits of the same weights at 0. (Three taps per wave, but for the last.)"""
+    import torch
+    from paper_2607_14672_amd import dstd
+    M, K, st, pad = 10, cs["KH"], cs["stride"], cs["pad"]
+    pool = cs["pool_in"]
+    p, t, W = _conv_case(85, B, cs, M, 1.0, 0.3, k=7.0)
+    gpu, h = _gpu_forward(dev, p, cs, t, W)
+    rng = np.random.default_rng(86)
+    g = rng.standard_normal(gpu["t_out"].shape).astype(np.float32)
+    g *= rng.random((B, 1) + g.shape[2:]) < share
+    odd = rng.random((1,) + W.shape[1:]) < 0.02  # (input channel, tap)s with one odd weight each
+    odd[0, 0, 0, 0] = True
+    at = rng.integers(0, W.shape[0], W.shape[1:])[None] == np.arange(W.shape[0])[:, None, None, None]
+    at = at & odd
+    Wo = np.where(at, rng.choice([np.inf, -np.inf, np.nan], W.shape), W).astype(np.float32)
+    prm, c, tt, _, to, sl, q = h
+    dev_w = [torch.from_numpy(np.ascontiguousarray(x, np.float32)).to(dev) for x in (Wo, np.where(at, 0.0, W))]
+    gW, gx = _gpu_backward(dev, (prm, c, tt, dev_w[0], to, sl, q), g)
+    zW, zx = _gpu_backward(dev, (prm, c, tt, dev_w[1], to, sl, q), g)
+    assert np.array_equal(gW, zW) and np.isfinite(zx).all()
+    # the last event row that meets gradient at each position (-1: none), and the inputs' rows
+    live = (gpu["q"] >= 0) & (g != 0)
+    last = np.where(live, gpu["q"] + 1, -1).max(axis=1)
+    row = np.floor(t.astype(np.float64) * M).astype(int) + 1
+    bad = np.zeros(t.shape, bool)
+    Hp, Wp = cs["H"] // pool, cs["W"] // pool
+    for ky in range(K):
+        for kx in range(K):
+            for oy in range(last.shape[1]):
+                for ox in range(last.shape[2]):
+                    y, x = oy * st - pad + ky, ox * st - pad + kx
+                    if 0 <= y < Hp and 0 <= x < Wp:
+                        s = np.s_[:, :, y * pool:(y + 1) * pool, x * pool:(x + 1) * pool]
+                        bad[s] |= (row[s] <= last[:, oy, ox][:, None, None, None]) & odd[0, :, ky, kx][None, :, None, None]
+    assert bad.any() and not bad.all()
+    assert np.array_equal(~np.isfinite(gx), bad)
+    assert np.array_equal(gx[~bad], zx[~bad])
