@@ -2247,8 +2247,11 @@ static ConvBackPlan conv_back_search(const ConvGeom &g, int64_t B, int M, bool d
             if (nt_given ? nt != nt_given : (nt == 2 && (g.C_out <= kWave || conv_back_lds(M, kwt, 2) > kBackLds))) continue;
             const int kg = (g.KW + kwt - 1) / kwt;
             const int tiles = (g.C_out + nt * kWave - 1) / (nt * kWave);
-            // dt_in entries per input: at most KH * KW + 1 at a time
-            const int tiles_dt = std::max(1, std::min(tiles, (g.KH * g.KW + 1) / (g.KH * kg)));
+            // dt_in entries per input: at most KH * KW + 1 at a time, or 32 MiB of them
+            // (132 -> 238, 6 x 6, stride 2, batch 54: one launch of both tiles for two)
+            const int64_t by_bytes = (int64_t{32} << 20) / std::max<int64_t>(1, 4 * B * g.Hp * g.Wp * g.PC * g.KH * kg);
+            const int tiles_dt = static_cast<int>(std::max<int64_t>(
+                1, std::min<int64_t>(tiles, std::max<int64_t>((g.KH * g.KW + 1) / (g.KH * kg), by_bytes))));
             const int launches = dt ? (tiles + tiles_dt - 1) / tiles_dt : 1;
             const int by_lds = std::max(1, (160 * 1024) / (conv_back_lds(M, kwt, nt) + 1024));
             const double steps = g.Wo + kwt - 1;

@@ -183,7 +183,8 @@ def test_conv_plans_fit_hardware_and_workspace(conv_plan):
             assert p["nsplit"] * p["rows_per_split"] >= B * ho > (p["nsplit"] - 1) * p["rows_per_split"], (s, p)
             assert p["lds"] + 1024 <= 160 * 1024 and p["nsplit"] <= 4096, (s, p)
             assert 1 <= p["tiles_dt"] <= p["tiles"]
-            assert k * p["kg"] * p["tiles_dt"] <= max(k * k + 1, k * p["kg"]), (s, p)
+            entries = k * p["kg"] * p["tiles_dt"]
+            assert entries <= max(k * k + 1, k * p["kg"]) or entries * B * hw * hw * ci * P * 4 <= 32 << 20, (s, p)
             if mode & 1 and p["nsplit"] > 1:
                 assert p["nsplit"] * k * k * ci * co * 4 <= 64 << 20, (s, p)
 
