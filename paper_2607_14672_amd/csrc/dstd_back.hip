@@ -515,7 +515,7 @@ static BackPlan back_search(const BackSize &z, int M, bool dw, bool dt, int nt_g
             const int chunks = static_cast<int>((z.N_in + tj - 1) / tj);
             const int slots = 4 * back_occupancy(nt * tj, dw && dt);
             const double item = static_cast<double>(z.F) * tj * k_input * (nt == 2 ? kWide : 1.);
-            for (int most = kBackWavesMax; most >= 2; most /= 2) {
+            for (const int most : {kBackWavesMax, 12, 8, 6, 4, 2}) {
                 const int groups = std::max(1, (chunks + most - 1) / most);
                 // (one block over the inputs: also with waves that only write table rows)
                 const int even = std::max(1, (chunks + groups - 1) / groups);

@@ -1509,6 +1509,50 @@ constexpr int kBackRowList = 256;  // output rows listed at a time
 // G tables: those of a step and the next one's
 constexpr int back_ring(int kwt) { return kwt == 1 ? 2 : 4; }
 
+// What a wave of conv_back_kernel leaves out: its taps kx0 .. kx0 + taps - 1 of
+// kernel row ky with an infinite or NaN weight to one of channels co0 .. co0 + nco
+// - 1, each added to the input's entry where the tap's own position passes gradient
+// to the input's event row. By one wave, input by input, from memory.
+__device__ __forceinline__ void odd_weights(const LifConst &C, const ConvGeom &g, const ConvBackArgs &a,
+                                         const float2 *tab, int r_lo, int r_hi, int ky, int kx0, int taps,
+                                         int ci0, int nj, int co0, int nco, int entries, int entry) {
+    const int lane = threadIdx.x & (kWave - 1);
+    __threadfence_block();  // the entries that the other lanes wrote
+    for (int x = 0; x < nj * taps; ++x) {
+        const int kx = kx0 + x % taps, ci = ci0 + x / taps;
+        const float *wp = a.Wt + (static_cast<int64_t>(ky * g.KW + kx) * g.C_in + ci) * g.C_out;
+        bool bad = false;
+        for (int c = co0 + lane; c < min(co0 + nco, g.C_out); c += kWave) bad = bad || !(fabsf(wp[c]) < INFINITY);
+        if (!__any(bad)) continue;
+        for (int s = r_lo * g.Wo; s < r_hi * g.Wo; ++s) {
+            const int rw = s / g.Wo, b = rw / g.Ho;
+            const int py = (rw - b * g.Ho) * g.stride - g.pad + ky, px = (s - rw * g.Wo) * g.stride - g.pad + kx;
+            const int last = a.rend[s];
+            if (last < 0 || py < 0 || py >= g.Hp || px < 0 || px >= g.Wp || !a.cr_live[b * g.Hp + py]) continue;
+            const int64_t cell = (static_cast<int64_t>(b) * g.Hp + py) * g.Wp + px;
+            for (int d = 0; d < g.P; ++d) {
+                const float *ev = a.ev + (cell * g.P + d) * kEvFields * g.C_in + ci;
+                const int r = __float_as_int(ev[0]);
+                if (r < 0 || r > last) continue;
+                const float dL = ev[3 * g.C_in], dR = ev[4 * g.C_in];
+                float v = 0.f;
+                for (int c = co0 + lane; c < min(co0 + nco, g.C_out); c += kWave) {
+                    if (fabsf(wp[c]) < INFINITY) continue;
+                    const float *t = a.tri + static_cast<int64_t>(s) * 3 * g.C_out + c;
+                    const int q = __float_as_int(t[2 * g.C_out]);
+                    auto at = [&](int row) {  // as g_rows writes it
+                        const float2 e = tab[q + C.M + 3 - row];
+                        return row >= 1 && q >= row - 1 ? fmaf(t[0], e.x, t[g.C_out] * e.y) : 0.f;
+                    };
+                    v += wp[c] * fmaf(dL, at(r), dR * at(r + 1));
+                }
+                for (int o = kWave / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+                if (lane == 0) a.P[(cell * entries + entry) * g.PC + d * g.C_in + ci] += v;
+            }
+        }
+    }
+}
+
 template <int KWT, int NT, int TJ, bool DW, bool DT>
 __global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst C, ConvGeom g,
                                                                        ConvBackArgs a) {
@@ -1593,31 +1637,25 @@ __global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst 
     });
     // Infinite and NaN weights: a table without gradient is multiplied like any
     // other, and 0 times such a weight would reach inputs that no position passes
-    // gradient to. They are taken out here (bit k of odd[i]: input k has one at tap
-    // i) and added tap by tap where the tap's own position has gradient for the
-    // input. (One tap per wave visits only such positions.)
-    unsigned odd[KWT];
-    bool any_odd = false;
-    static_for<KWT>([&](auto i) { odd[i] = 0u; });
+    // gradient to. A wave that has any takes them as 0 and adds them at the end
+    // (odd_weights). (One tap per wave visits only positions with gradient.)
+    bool odd = false;
     if constexpr (DT && KWT > 1) {
         static_for<TJ>([&](auto j) {
             static_for<KWT>([&](auto i) {
                 static_for<NT>([&](auto c) {
-                    any_odd = any_odd || !(fabsf(w[j / kBackGroup][j % kBackGroup][i][c]) < INFINITY);
+                    odd = odd || !(fabsf(w[j / kBackGroup][j % kBackGroup][i][c]) < INFINITY);
                 });
             });
         });
-        any_odd = __any(any_odd);
-        if (any_odd)
+        odd = __any(odd);
+        if (odd)
             static_for<TJ>([&](auto j) {
                 static_for<KWT>([&](auto i) {
-                    bool bad = false;
                     static_for<NT>([&](auto c) {
                         float &x = w[j / kBackGroup][j % kBackGroup][i][c];
-                        bad = bad || !(fabsf(x) < INFINITY);
                         x = fabsf(x) < INFINITY ? x : 0.f;
                     });
-                    if (__any(bad)) odd[i] |= 1u << j;
                 });
             });
     }
@@ -1722,27 +1760,6 @@ __global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst 
                             if ((act >> (h * kBackGroup)) & 0xffu)
                                 tot[h] = back_group<NT, KWT, TJ, h, DW, DT>(gl, lane, act, ev[p], w[h], acc[h]);
                         });
-                        if (DT && KWT > 1 && any_odd)
-                            static_for<KWT>([&](auto i) {
-                                unsigned m = e[i] < 0 ? 0u : odd[i] & static_cast<unsigned>(__ballot(
-                                    lane < nj && static_cast<unsigned>(__float_as_int(ev[p].e[0])) <= static_cast<unsigned>(e[i])));
-                                for (; m; m &= m - 1) {
-                                    const int k = __builtin_ctz(m);
-                                    const float *q = gl[i] + __builtin_amdgcn_readlane(__float_as_int(ev[p].e[0]), k) * kRow;
-                                    const float dL = __shfl(ev[p].e[ev_reg<TJ>(3, 0)], ev_lane<TJ>(3, 0) + k);
-                                    const float dR = __shfl(ev[p].e[ev_reg<TJ>(4, 0)], ev_lane<TJ>(4, 0) + k);
-                                    const float *wp = a.Wt + (static_cast<int64_t>(ky * g.KW + kx0 + i) * g.C_in + ci0 + k) * g.C_out;
-                                    float v = 0.f;
-                                    for (int c = 0; c < NT; ++c) {
-                                        const float x = co + c < g.C_out ? wp[co + c] : 0.f;
-                                        if (!(fabsf(x) < INFINITY)) v += x * fmaf(dL, q[c], dR * q[kRow + c]);
-                                    }
-                                    for (int o = kWave / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-                                    static_for<kG>([&](auto h) {
-                                        if (k / kBackGroup == h && (lane >> 3) == k % kBackGroup) tot[h] += v;
-                                    });
-                                }
-                            });
                     }
                     if constexpr (DT) {
                         float v = tot[0];
@@ -1796,6 +1813,9 @@ __global__ __launch_bounds__(kBackWaves * kWave) void conv_back_kernel(LifConst 
                 });
             });
         });
+    }
+    if constexpr (DT && KWT > 1) {
+        if (odd) odd_weights(C, g, a, tab, r_lo, r_hi, ky, kx0, min(KWT, g.KW - kx0), ci0, nj, tile * kRow, kRow, entries, entry);
     }
 }
 
