@@ -497,10 +497,10 @@ static BackPlan back_search(const BackSize &z, int M, bool dw, bool dt, int nt_g
     constexpr double kPerUs = 2400., kShare = 0.053, kWide = 1.27;
     constexpr double kSumUs = 3., kSumUsPerMB = 0.68, kSumUsPerPart = 0.18;
     const double k_input = (dw && dt) ? 109. : dt ? 105. : 57.;
-    const int64_t Bn = std::max<int64_t>(z.B, 1);
+    const int Bn = static_cast<int>(std::max<int64_t>(z.B, 1));
     const double dw_mb = 4e-6 * static_cast<double>(z.N_in) * static_cast<double>(z.N_out);
     const double dt_mb = 4e-6 * static_cast<double>(z.B) * static_cast<double>(z.N_in * z.F);
-    const int64_t most_split = dw ? std::max<int64_t>(1, std::min(z.cap, Bn)) : std::min<int64_t>(Bn, 256);
+    const int most_split = dw ? std::max(1, std::min(static_cast<int>(z.cap), Bn)) : std::min(Bn, 256);
     // (one tile needs no dt_in buffers to add up: 64 < N_out <= 128 takes NT = 2)
     const int nt_most = (z.N_out > kWave && back_lds(M, 2, 1) <= kBackLdsDense) ? 2 : 1;
     if (nt_most == 2 && z.N_out <= 2 * kWave) nt_given = 2;
@@ -524,14 +524,14 @@ static BackPlan back_search(const BackSize &z, int M, bool dw, bool dt, int nt_g
                 const int64_t blocks = static_cast<int64_t>(groups) * std::max(1, per_launch);
                 const double sample = item + kBarrier + (z.mem_g ? kRowMem : kRow) * nt * (M + 3) / w;
                 const double start = kStart + kStartM * M / w;
-                for (int64_t want = 1;; want = std::min(2 * want, most_split)) {
-                    const int64_t bps = bps_given ? bps_given : (Bn + want - 1) / want;
-                    const int64_t ns = (Bn + bps - 1) / bps;
-                    const int64_t tot = blocks * ns, full = tot / (kBackCUs * per);
+                for (int want = 1;; want = std::min(2 * want, most_split)) {
+                    const int bps = bps_given ? bps_given : (Bn + want - 1) / want;
+                    const int ns = (Bn + bps - 1) / bps;
+                    const int64_t tot = blocks * ns, full = tot < kBackCUs * per ? 0 : tot / (kBackCUs * per);
                     const int64_t rest = tot - full * kBackCUs * per;
                     const double alone = start + static_cast<double>(bps) * sample;
                     double us = static_cast<double>(full) * (1. + kShare * per * w);
-                    if (rest > 0) us += 1. + kShare * static_cast<double>((rest + kBackCUs - 1) / kBackCUs) * w;
+                    if (rest > 0) us += 1. + kShare * static_cast<double>((static_cast<int>(rest) + kBackCUs - 1) / kBackCUs) * w;
                     us *= alone * std::max(1, launches) / kPerUs;
                     if (dw && ns > 1)
                         us += kSumUs + std::max(kSumUsPerMB * static_cast<double>(ns + 1) * dw_mb,
@@ -545,8 +545,8 @@ static BackPlan back_search(const BackSize &z, int M, bool dw, bool dt, int nt_g
                         p.tiles = tiles;
                         p.groups = groups;
                         p.waves = w;
-                        p.nsplit = static_cast<int>(ns);
-                        p.b_per_split = static_cast<int>(bps);
+                        p.nsplit = ns;
+                        p.b_per_split = bps;
                     }
                     if (bps_given || want >= most_split) break;
                 }

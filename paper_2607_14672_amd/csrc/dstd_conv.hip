@@ -2247,17 +2247,17 @@ static ConvBackPlan conv_back_search(const ConvGeom &g, int64_t B, int M, bool d
     constexpr double kPerUs = 2400., kShare = 0.0346, kPartUsPerMB = 1.92, kPartUsPerSplit = 0.0134, kEntryUsPerMB = 0.76;
     const double k_pair = (dw && dt) ? 38. : dt ? 33.7 : 10.1;
     const int64_t nw = static_cast<int64_t>(g.KH) * g.KW * g.C_in * g.C_out;
-    const int64_t rows = std::max<int64_t>(1, B * g.Ho);
+    const int rows = static_cast<int>(std::max<int64_t>(1, B * g.Ho));
     const double dw_mb = 4e-6 * static_cast<double>(nw);
     const double in_mb = 4e-6 * static_cast<double>(B * g.Hp) * g.Wp * g.PC;
-    int64_t most_split = std::min<int64_t>(rows, kConvMaxSplit);
-    if (dw) most_split = std::max<int64_t>(1, std::min(most_split, (int64_t{64} << 20) / (4 * std::max<int64_t>(nw, 1))));
+    int most_split = std::min(rows, kConvMaxSplit);
+    if (dw) most_split = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(most_split, (int64_t{64} << 20) / (4 * std::max<int64_t>(nw, 1)))));
     // (dW alone of a layer whose pairs are one block of conv_dw_kernel needs 1024
     // splits, of 16 positions at least, to fill the chip: 1 -> 32, 5 x 5, 28 x 28, batch 64 250 -> 122 us, both
     // gradients 324 -> 360)
-    const int64_t least_split =
+    const int least_split =
         (dw && g.KH * g.KW * g.C_in <= kDwPairs && g.C_out <= kWave)
-            ? std::max<int64_t>(1, std::min<int64_t>({1024, most_split, rows * g.Wo / 16})) : 1;
+            ? static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({1024, most_split, static_cast<int64_t>(rows) * g.Wo / 16}))) : 1;
     ConvBackPlan p{};
     double best = -1.;
     for (int kwt = 3; kwt >= 1; kwt -= 2) {
@@ -2291,12 +2291,13 @@ static ConvBackPlan conv_back_search(const ConvGeom &g, int64_t B, int M, bool d
                         const int per = std::max(1, std::min(w <= 2 ? 4 * occ / w : occ / ((w + 3) / 4), by_lds));
                         const double step = g.P * item + kStep + kRow * nt * (M + 3) / w;
                         const int64_t blocks = static_cast<int64_t>(groups) * ((tiles + launches - 1) / launches);
-                        for (int64_t want = least_split;; want = std::min(2 * want, most_split)) {
-                            const int64_t rps = rows_given ? rows_given : (rows + want - 1) / want;
-                            const int64_t ns = (rows + rps - 1) / rps, tot = blocks * ns;
-                            const int64_t full = tot / (kConvCUs * per), rest = tot - full * kConvCUs * per;
+                        for (int want = least_split;; want = std::min(2 * want, most_split)) {
+                            const int rps = rows_given ? rows_given : (rows + want - 1) / want;
+                            const int ns = (rows + rps - 1) / rps;
+                            const int64_t tot = blocks * ns, full = tot < kConvCUs * per ? 0 : tot / (kConvCUs * per);
+                            const int64_t rest = tot - full * kConvCUs * per;
                             double us = static_cast<double>(full) * (1. + kShare * per * w);
-                            if (rest > 0) us += 1. + kShare * static_cast<double>((rest + kConvCUs - 1) / kConvCUs) * w;
+                            if (rest > 0) us += 1. + kShare * static_cast<double>((static_cast<int>(rest) + kConvCUs - 1) / kConvCUs) * w;
                             us *= launches * (start + static_cast<double>(rps) * steps * step) / kPerUs;
                             if (dw) us += std::max(kPartUsPerMB * static_cast<double>(ns) * dw_mb,
                                                    kPartUsPerSplit * static_cast<double>(ns));
@@ -2304,7 +2305,7 @@ static ConvBackPlan conv_back_search(const ConvGeom &g, int64_t B, int M, bool d
                             if (best < 0. || us < best) {
                                 best = us;
                                 p = ConvBackPlan{kwt, nt, tj, kg, tiles, tiles_dt, cpt, chunks, groups, w,
-                                                 static_cast<int>(ns), static_cast<int>(rps),
+                                                 ns, rps,
                                                  static_cast<size_t>(conv_back_lds(M, kwt, nt))};
                             }
                             if (rows_given || want >= most_split) break;
