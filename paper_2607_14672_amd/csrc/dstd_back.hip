@@ -19,9 +19,10 @@
 // cycles at 4 waves per SIMD). Against the kernels before it (dW with lanes =
 // inputs, two G rows gathered from LDS per lane and neuron; dt_in with a weight
 // row loaded and a block reduced per record), forward and backward of a layer:
-// 4096 -> 4096, batch 256, M = 64, bf16 weights 3.20 -> 2.17 ms; 6000 -> 1000,
-// batch 100 585 -> 407 us; 784 -> 1000, batch 128 114 -> 105 us; the
-// multi-spike layer 784 x 4 -> 1000, batch 128 752 -> 372 us.
+// 4096 -> 4096, batch 256, M = 64, bf16 weights 3.20 -> 2.06 ms; 6000 -> 1000,
+// batch 100 585 -> 406 us; 784 -> 1000, batch 128 114 -> 105 us; the
+// multi-spike layer 784 x 4 -> 1000, batch 128 754 -> 347 us. dW alone of larger
+// TTFS layers has back_dw_kernel: there the LDS reads bound this one.
 #include "dstd_back.h"
 #include "dstd_internal.h"
 #include "dstd_kernels.h"
