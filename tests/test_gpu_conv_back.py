@@ -71,6 +71,18 @@ def test_conv_backward_interval_index_past_the_grid(dev, c_out):  # noqa: F811
     (2, _cs(9, 9, 13, 70, stride=2), 256, 0.5),     # the longest grid
     (4, _cs(70, 5, 5, 40, K=1, pad=0), 8, 0.5),
     (2, _cs(3, 8, 66, 20), 20, 0.02),               # rows longer than 64 positions, most without
+    # batches that choose each of the contraction's other tiles (taps, channels and
+    # inputs per lane or wave), both together and each alone
+    (64, _cs(9, 2, 2, 3, K=5), 8, 0.6),
+    (128, _cs(9, 28, 28, 3, K=1, pad=0), 8, 0.3),
+    (64, _cs(1, 4, 4, 65), 8, 1.0),
+    (64, _cs(1, 12, 12, 65, K=1, pad=0), 16, 0.3),
+    (64, _cs(17, 4, 4, 65), 90, 0.6),
+    (64, _cs(1, 12, 12, 3), 8, 0.6),
+    (64, _cs(1, 4, 4, 3, K=5), 90, 1.0),
+    (128, _cs(9, 4, 4, 3, K=5), 90, 0.6),
+    (64, _cs(1, 12, 12, 65), 16, 0.3),
+    (128, _cs(1, 4, 4, 65, K=5), 16, 1.0),
 ])
 def test_conv_backward_alone_is_the_same(dev, B, cs, M, share):  # noqa: F811
     """Each gradient alone has the bits that both together give it (dW alone runs
