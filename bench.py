@@ -80,7 +80,7 @@ class Net:
                                  lay.t_max, flags)
             p_b = p
             if lay.kind == "conv" and l > 0:
-                # the forward keeps its binned, sorted inputs in the backward's
+                # the forward keeps its inputs' events in the backward's
                 # workspace, and the backward reuses them (the first layer's
                 # backward computes no dt_in, so it needs no sort)
                 p = dstd.make_params(lay.tau_m, lay.tau_s, lay.threshold, lay.M, lay.t0, lay.dt,

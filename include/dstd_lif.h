@@ -89,8 +89,8 @@ typedef enum { DSTD_F32 = 0, DSTD_BF16 = 1 } dstd_dtype;
  *                 measured faster). Both set: DSTD_ERR_PARAM.
  *                 Conv calls take instead (see dstd_lif_conv_forward /
  *                 _backward):
- *                  DSTD_FLAG_CONV_KEEP (forward): keep the binned, sorted
- *                    inputs for the backward;
+ *                  DSTD_FLAG_CONV_KEEP (forward): keep the inputs' cell-major
+ *                    events and the weights' layout for the backward;
  *                  DSTD_FLAG_CONV_REUSE (backward): use what a forward with
  *                    DSTD_FLAG_CONV_KEEP kept.
  *                 A flag a call does not take gives DSTD_ERR_UNSUPPORTED.
@@ -227,11 +227,11 @@ size_t dstd_lif_conv_backward_workspace_size(const dstd_lif_params *p, const dst
  * With p->flags = DSTD_FLAG_CONV_KEEP the workspace must have
  * dstd_lif_conv_backward_workspace_size bytes (else DSTD_ERR_WORKSPACE): the
  * call also leaves there what the layer's backward would derive from t_in
- * and W again -- the inputs binned to their events and sorted, with the
- * event weights' derivatives (the events s_jm of Eq. (DSTD_kernel) and
- * ds/dt depend on t_in alone), the cell-major events for dW and the
- * weights' layout -- for a dstd_lif_conv_backward with
- * DSTD_FLAG_CONV_REUSE on the same workspace.
+ * and W again -- the inputs binned to their events, in cell-major order,
+ * with the event weights and their derivatives (the events s_jm of
+ * Eq. (DSTD_kernel) and ds/dt depend on t_in alone), and the weights'
+ * layout -- for a dstd_lif_conv_backward with DSTD_FLAG_CONV_REUSE on the
+ * same workspace.
  * B = 0 is a valid no-op.
  */
 dstd_status dstd_lif_conv_forward(const dstd_lif_params *p, const dstd_conv_shape *cs, int64_t B,
